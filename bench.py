@@ -20,7 +20,6 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-PEAK = {"fp64": 78.6, "fp32": 157.3}          # dense MFMA TFLOP/s, MI355X
 HBM_PEAK = 8000.0                              # GB/s
 
 
@@ -104,7 +103,7 @@ def cpu_baseline(prob, ncols: int, nrows: int = 16384):
             "seconds_estimated": t_iter, "cpu_model": model, "physical_cores": phys}
 
 
-def profiled_traffic(tag: str, sources=("hx.hip", "common.hpp")):
+def profiled_traffic(tag: str, sources=("kron.hip", "common.hpp")):
     """HBM bytes per launch of the dominant kernel from the committed rocprofv3
     counter summary profiles/<tag>.md, or None when that summary is missing or
     the kernel source changed since the counters were taken."""
@@ -151,35 +150,6 @@ def batch_throughput(args):
         Xs.append(workload.start_block_device(pr.n_dof, pr.nblock, pr.x0_seed, device=dev))
         Ns.append(pr.nstates)
     torch.cuda.synchronize()
-    # autotuned cell-kernel tile per degree (FP32 filter): timed once per p on
-    # a scratch copy of one problem's block, then set on every context of that p
-    from paper_1903_10959_amd import autotune as AT
-
-    tiles = {}
-    t_tune = time.time()
-    for i, pr in enumerate(probs):
-        if pr.p not in tiles:
-            c = ctxs[i]
-            scratch = Xs[i].clone()
-            b = c.upper_bound
-            tiles[pr.p] = AT.tune_tile_variant(c, scratch, (0.5 * b, b, -50.0), prec="fp32", refresh=True)
-            del scratch
-        ctxs[i].set_tile_variant(tiles[pr.p])
-    # cells per work-group per (degree, block size): blocks of few columns pad
-    # fewer MFMA columns with more cells per tile
-    cpts = {}
-    for i, pr in enumerate(probs):
-        key = (pr.p, pr.nblock)
-        if key not in cpts:
-            c = ctxs[i]
-            scratch = Xs[i].clone()
-            b = c.upper_bound
-            cpts[key] = AT.tune_cells_per_tile(c, scratch, (0.5 * b, b, -50.0), prec="fp32", refresh=True)
-            del scratch
-        ctxs[i].set_cells_per_tile(cpts[key])
-    torch.cuda.synchronize()
-    print(f"[bench] batch: tile variants per degree {tiles}, cells per tile per (p, N_b) {cpts} "
-          f"(tuned in {time.time() - t_tune:.1f} s)", file=sys.stderr, flush=True)
     tot_dofs = sum(pr.n_dof for pr in probs)
     print(f"[bench] batch: {len(probs)} problems, {tot_dofs} DoFs in all, setup {time.time() - t0:.1f} s",
           file=sys.stderr, flush=True)
@@ -205,9 +175,7 @@ def batch_throughput(args):
            "vs_baseline": None, "dtype": "fp32-filter/f64", "data": "synthetic",
            "config": {"workload": "batch: 64 problems, n_el in 4..12, p in 4..7, N in 16..256, L = 2.5 n_el, "
                                   f"{tot_dofs} DoFs in all, Chebyshev degree 20"},
-           "one_at_a_time_seconds": t_seq, "batch_seconds": t_batch, "speedup_vs_one_at_a_time": t_seq / t_batch,
-           "tile_variant_per_degree": {str(k): v for k, v in sorted(tiles.items())},
-           "cells_per_tile_per_degree_and_block": {f"p{k[0]}/nb{k[1]}": v for k, v in sorted(cpts.items())}}
+           "one_at_a_time_seconds": t_seq, "batch_seconds": t_batch, "speedup_vs_one_at_a_time": t_seq / t_batch}
     print(json.dumps(out), flush=True)
     for c in ctxs:
         c.close()
@@ -471,8 +439,8 @@ def kpoint_bench(args, prob):
     """Complex Bloch operator (Sec. 2.1 eq. ksproblemPer) on the periodic cell
     with the workload's element size and degree: Y = Htilde_k X for a complex
     block of 64 vectors (one filter block of 128 real columns), timed with HIP
-    events on the context's stream.  Roofline: FP64 MFMA, algorithmic flops =
-    8 n_loc^2 per cell per complex vector (A Xr + B Xi and A Xi - B Xr)."""
+    events on the context's stream.  Roofline: HBM, algorithmic bytes = 32 per
+    complex DoF-vec (read X, write Y)."""
     import torch
 
     import numpy as np
@@ -500,12 +468,11 @@ def kpoint_bench(args, prob):
     e1.record()
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1) / reps
-    flops = 8.0 * ctx.n_loc ** 2 * ctx.n_cells * nc
-    tf = flops / (ms * 1e-3) / 1e12
+    gbs = 32.0 * ctx.n_dof * nc / (ms * 1e-3) / 1e9   # read X, write Y
     dv = ctx.n_dof * nc / (ms * 1e-3)
     del X, Y
     # a k-point group (2 x 2 x 2 Monkhorst-Pack set) on a batch-sized periodic
-    # mesh: one launch per colour for all k-points vs one context per k-point
+    # mesh: one launch for all k-points vs one context per k-point
     Lg, neg, pg = 20.0, 8, 5
     kk = [(2 * np.pi / Lg) * np.array([sx, sy, sz]) / 4 for sx in (-1, 1) for sy in (-1, 1) for sz in (-1, 1)]
     grp = P.Context(0).set_mesh(Lg, neg, pg, periodic=True)
@@ -542,10 +509,10 @@ def kpoint_bench(args, prob):
            "data": "synthetic", "dtype": "f64 (complex128)",
            "config": {"workload": f"periodic [0,{prob.L})^3, {prob.n_el}^3 cells, p={prob.p}, {ctx.n_dof} DoFs, "
                                   f"k={list(k)}, {nc} complex vectors", "steps": args.steps},
-           "roofline": {"bound": "mfma", "achieved": tf, "peak": 78.6, "unit": "TFLOP/s", "frac": tf / 78.6,
-                        "traffic": profiled_traffic(f"hx_cells_cplx_periodic_p{prob.p}"),
-                        "kernel": "hx_cells_cplx_kernel", "avg_apply_ms": ms, "launches_per_apply": 8,
-                        "flop_per_cell_complex_vec": 8 * ctx.n_loc ** 2},
+           "roofline": {"bound": "hbm", "achieved": gbs, "peak": HBM_PEAK, "unit": "GB/s", "frac": gbs / HBM_PEAK,
+                        "traffic": profiled_traffic(f"kron_cplx_periodic_p{prob.p}"),
+                        "kernel": "kron_kernel (complex)", "avg_apply_ms": ms, "launches_per_apply": 1,
+                        "bytes_per_complex_dofvec": 32},
            "kpoint_group": {"mesh": f"periodic [0,{Lg})^3, {neg}^3 cells, p={pg}", "nk": len(kk),
                             "complex_vectors_per_k": nc, "ms_group": ms_group, "ms_one_context_per_k": ms_single,
                             "speedup": ms_single / ms_group}}
@@ -706,10 +673,8 @@ def main():
         print(f"[bench] warmup {w}: {time.time() - t0:.3f} s, max wanted resid {np.max(rs[:prob.nstates]):.3e}",
               file=sys.stderr, flush=True)
 
-    # timed region: the cell-product launches are bracketed by HIP events --
-    # in FP64 every launch of the step (the filter's and the Rayleigh-Ritz
-    # applications, all the same kernel), in a reduced precision the filter's
-    # launches only (the Rayleigh-Ritz applications run the FP64 kernel)
+    # timed region: the filter's step launches are bracketed by HIP events (the
+    # Rayleigh-Ritz applications, which have no previous block, are not)
     ctx.set_timing(True)
     ctx.reset_timing()
     t_filter = 0.0
@@ -719,8 +684,7 @@ def main():
         ts = time.time()
         ctx.chebyshev_filter(X, prob.degree, float(ev[-1]), b, float(ev[0]), prec=args.prec, block_width=bw)
         t_filter += time.time() - ts   # filter returns after its finiteness check (synchronised)
-        if args.prec != "fp64":
-            ctx.set_timing(False)
+        ctx.set_timing(False)
         ctx.orthonormalize(X, mixed=args.mixed_cholgs)
         ev, rs = ctx.rayleigh_ritz(X)
         ctx.set_timing(True)
@@ -733,21 +697,13 @@ def main():
     ms_step = dt / args.steps * 1e3
     dofvecs_step = prob.n_dof * nb * (prob.degree + 1)
     value = dofvecs_step / (dt / args.steps)
-    n_loc = (prob.p + 1) ** 3
-    n_cells = prob.n_el ** 3
     avg_launch_ms = tim["ms"] / max(tim["launches"], 1)
-    if args.prec in ("fp64", "fp32"):
-        # MFMA-bound: the method's dense cell products, 2 n_loc^2 flops per cell-vector
-        flops = 2.0 * n_loc * n_loc * tim["cell_vecs"]
-        achieved = flops / (tim["ms"] * 1e-3) / 1e12
-        peak, bound, unit = PEAK[args.prec], "mfma", "TFLOP/s"
-        kname = f"hx_cells_kernel<{'double' if args.prec == 'fp64' else 'float'},{(n_loc + 15) // 16 * 16}>"
-    else:
-        # HBM-bound: 3 x 4 B of FP32 recursion state per DoF-vec (read X_k, X_k-1, write X_k+1)
-        dofvecs = tim["cell_vecs"] * prob.n_dof / n_cells
-        achieved = 12.0 * dofvecs / (tim["ms"] * 1e-3) / 1e9
-        peak, bound, unit = HBM_PEAK, "hbm", "GB/s"
-        kname = f"hx_cells_bf16_kernel<{(n_loc + 31) // 32 * 32},{'true' if args.prec == 'bf16x3' else 'false'}>"
+    # HBM-bound: a filter step reads X_k and X_k-1 and writes X_k+1 (the first
+    # one has no X_k-1)
+    elem = 8 if args.prec == "fp64" else 4
+    bytes_dofvec = elem * (3.0 * prob.degree - 1.0) / prob.degree
+    achieved = bytes_dofvec * tim["cell_vecs"] * prob.n_dof / prob.n_el ** 3 / (tim["ms"] * 1e-3) / 1e9
+    kname = f"kron_kernel<{'double' if args.prec == 'fp64' else 'float'}, p = {prob.p}>"
     out = {
         "metric": "ChFSI H.X DoF-vecs/s (whole ChFSI iteration: filter + CholGS + RR)",
         "value": value,
@@ -765,12 +721,12 @@ def main():
                                f"{prob.n_dof} DoFs, {prob.n_wells} seeded Gaussian wells, N={prob.nstates}, "
                                f"N_b={nb}, Chebyshev degree {prob.degree}, filter block {bw}",
                    "filter_precision": args.prec, "mixed_cholgs": bool(args.mixed_cholgs)},
-        "roofline": {"bound": bound, "achieved": achieved, "peak": peak, "unit": unit,
-                     "frac": achieved / peak,
-                     "traffic": profiled_traffic(f"hx_cells_{prob.name}_{args.prec}"),
+        "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK, "unit": "GB/s",
+                     "frac": achieved / HBM_PEAK,
+                     "traffic": profiled_traffic(f"kron_{prob.name}_{'fp64' if args.prec == 'fp64' else 'fp32'}"),
                      "kernel": kname,
                      "launches": tim["launches"], "avg_launch_ms": avg_launch_ms,
-                     "flop_per_cell_vec": 2 * n_loc * n_loc},
+                     "bytes_per_dofvec": bytes_dofvec},
         "filter_dofvecs_per_s": prob.n_dof * nb * prob.degree / (t_filter / args.steps),
         "max_wanted_resid": float(np.max(rs[:prob.nstates])),
     }

@@ -11,8 +11,10 @@
  * elements of degree p on Gauss-Lobatto-Legendre nodes, homogeneous Dirichlet
  * boundary (boundary nodes carry no unknown).  K is the stiffness of
  * -1/2 Laplacian (eq. discreteHam); GLL quadrature makes M diagonal, so
- * Htilde X = M^-1/2 (sum_e P_e^T K_e P_e) M^-1/2 X + V .* X, applied cell by
- * cell (Sec. 3.3, practical implementation of Chebyshev filtering).
+ * Htilde X = M^-1/2 (sum_e P_e^T K_e P_e) M^-1/2 X + V .* X (Sec. 3.3, practical
+ * implementation of Chebyshev filtering), on the uniform mesh a Kronecker sum
+ * of 1D operators, A (x) I (x) I + I (x) A (x) I + I (x) I (x) A + diag(V), and
+ * applied in that form.
  *
  * Conventions used by every call:
  *  - Return value: 0 = OK, < 0 = error (CHFSI_ERR_*), > 0 = warning.  No C++
@@ -42,10 +44,11 @@ extern "C" {
 
 typedef struct chfsi_ctx chfsi_ctx;   /* opaque; owned by the library */
 
-/* Arithmetic of the filter's cell products.  FP64 = the paper's precision.
- * FP32: recursion state and products in FP32.  BF16: products with BF16
- * inputs and FP32 accumulation, recursion state FP32.  BF16X3: BF16 hi/lo
- * split of both operands, three products accumulated in FP32. */
+/* Arithmetic of the filter's products.  FP64 = the paper's precision.
+ * FP32: recursion state and products in FP32.  BF16: the block's values enter
+ * the products rounded to BF16, FP32 accumulation, recursion state FP32.
+ * BF16X3: products at least as exact as a BF16 hi/lo split of both operands
+ * with three products accumulated in FP32 (the library runs them in FP32). */
 typedef enum {
     CHFSI_FP64 = 0,
     CHFSI_FP32 = 1,
@@ -81,9 +84,8 @@ int chfsi_destroy(chfsi_ctx *ctx);
  * K1 = D^T W D, W = diag of GLL weights), the cell->dof map, the 8-colour
  * cell colouring (ex&1)+2(ey&1)+4(ez&1) and the diagonal mass M (GLL rule),
  * and upload them.  Resets any potential set before.  Requires n_el*p >= 2.
- * Degrees 8..12 (n_loc = 729..2197) run the FP64/FP32 cell products in groups
- * of 224 output rows per work-group; the BF16 products, the complex
- * k-point operator and the batch session need p <= 7 (CHFSI_ERR_ARG). */
+ * The BF16 products, the complex k-point operator and the batch session need
+ * p <= 7 (CHFSI_ERR_ARG). */
 int chfsi_set_mesh(chfsi_ctx *ctx, double L, int n_el, int p);
 int chfsi_get_sizes(const chfsi_ctx *ctx, int64_t *n_dof, int64_t *n_cells, int *n_loc);
 /* Host copies of the tables built by set_mesh (caller-owned host buffers). */
@@ -101,9 +103,9 @@ int chfsi_get_cell_matrix(const chfsi_ctx *ctx, double *host_k);      /* [n_loc*
 int chfsi_set_potential(chfsi_ctx *ctx, const double *v, int64_t n_dof, int v_on_device);
 int chfsi_get_upper_bound(const chfsi_ctx *ctx, double *b);
 
-/* ---- Htilde X (Sec. 3.3: cell-level products, assembled) -----------------
+/* ---- Htilde X (Sec. 3.3) ----------------------------------------------------
  * Y = Htilde X for ncols columns.  X, Y: device, [n_dof x ld], must not alias.
- * prec selects the cell-product arithmetic (X, Y stay FP64). */
+ * prec selects the products' arithmetic (X, Y stay FP64). */
 int chfsi_apply(chfsi_ctx *ctx, const double *X, double *Y, int64_t ld, int ncols, chfsi_prec prec);
 
 /* One recursion step (eq. chebFilter, normalised form):
@@ -115,8 +117,8 @@ int chfsi_cheb_step(chfsi_ctx *ctx, const double *X, const double *Xprev, double
 /* ---- chebyshevFilter (Sec. 3.3 eq. chebFilter) ----------------------------
  * In place: X <- T_m(Hbar) X / T_m(xi0), Hbar = (Htilde - c)/e,
  * c = (a+b)/2, e = (b-a)/2, xi0 = (a0-c)/e, requires a0 < a < b.
- * Vectors are filtered in blocks of block_width columns (0 = library default)
- * with three rotating buffers per block.  Returns CHFSI_ERR_NONFINITE if the
+ * Vectors are filtered in blocks of block_width columns (0 = library default),
+ * two buffers alternating (FP64: X and one of the library's).  Returns CHFSI_ERR_NONFINITE if the
  * result holds NaN/Inf. */
 int chfsi_chebyshev_filter(chfsi_ctx *ctx, double *X, int64_t ld, int ncols, int degree,
                            double a, double b, double a0, chfsi_prec prec, int block_width);
@@ -196,9 +198,7 @@ int chfsi_set_kpoint(chfsi_ctx *ctx, double kx, double ky, double kz);
 /* chfsi_apply_complex: Y = Htilde_k X for complex blocks (interleaved re, im
  * FP64 pairs, i.e. complex128), DoF-major: element (dof i, column j) at
  * X[i*ld + j], ld and ncols in complex elements (ld >= ncols).  X and Y are
- * caller-owned device arrays that must not overlap.  The cell products run on
- * FP64 MFMA as one real contraction of length 2 n_loc per output (A on the
- * columns, B on the swapped (re, im) pairs).  Errors: CHFSI_ERR_STATE without
+ * caller-owned device arrays that must not overlap.  Errors: CHFSI_ERR_STATE without
  * a periodic mesh and potential, CHFSI_ERR_ARG for bad block arguments. */
 int chfsi_apply_complex(chfsi_ctx *ctx, const void *X, void *Y, int64_t ld, int ncols);
 
@@ -214,8 +214,7 @@ int chfsi_apply_complex(chfsi_ctx *ctx, const void *X, void *Y, int64_t ld, int 
  *   potential (host eigensolve of each 1D operator; above 200 nodes per
  *   direction a Gershgorin bound).
  * chfsi_chebyshev_filter_complex: in place, X <- T_m(Hbar_k) X / T_m(xi0) with
- *   Hbar_k = (Htilde_k - c)/e as for chfsi_chebyshev_filter (real coefficients,
- *   the complex cell kernel); CHFSI_ERR_NONFINITE on NaN/Inf.
+ *   Hbar_k = (Htilde_k - c)/e as for chfsi_chebyshev_filter (real coefficients); CHFSI_ERR_NONFINITE on NaN/Inf.
  * chfsi_orthonormalize_complex: CholGS in complex arithmetic, S = X^H X =
  *   L L^H, X <- X L^-H (X^H X = I); CHFSI_ERR_NOT_SPD as the real call.
  * chfsi_rayleigh_ritz_complex: for orthonormal X, Hhat = X^H Htilde_k X
@@ -237,12 +236,11 @@ int chfsi_orthonormalize_complex(chfsi_ctx *ctx, void *X, int64_t ld, int ncols)
 int chfsi_rayleigh_ritz_complex(chfsi_ctx *ctx, void *X, int64_t ld, int ncols, double *evals, double *resid,
                                 void *HX_out);
 /* A group of k-points on one periodic mesh (the paper's k-point
- * parallelisation, Sec. 3.7, as one launch per colour): chfsi_set_kpoints
- * takes nk wave vectors (host, 3 nk values, k-point g at k[3g .. 3g+2]) and
- * uploads one cell operator each; chfsi_apply_complex_kpoints computes
+ * parallelisation, Sec. 3.7, as one launch): chfsi_set_kpoints takes nk wave
+ * vectors (host, 3 nk values, k-point g at k[3g .. 3g+2]); chfsi_apply_complex_kpoints computes
  * Y_g = Htilde_{k_g} X_g for all g, block g at X + g*stride (and Y + g*stride),
  * stride in complex elements (>= n_dof * ld), layout as chfsi_apply_complex.
- * Work items (k-point, cell, column tile) share the mesh tables.  A new mesh
+ * The k-points share the mesh tables.  A new mesh
  * clears the group.  Errors: CHFSI_ERR_STATE without a periodic mesh (or
  * without a group for the apply), CHFSI_ERR_ARG for nk < 1, non-finite k,
  * stride < n_dof * ld or overlapping X and Y. */
@@ -347,8 +345,8 @@ int chfsi_solve_complex(chfsi_ctx *ctx, const chfsi_opts *o, void *X, int64_t ld
  * Every problem uses the same Chebyshev degree; each follows its own ladder
  * of BF16, BF16X3, FP32 and FP64 filter rungs (CholGS/RR are FP64; BF16 rungs
  * need p <= 7, else CHFSI_ERR_ARG).  Each pass runs one
- * Chebyshev step of all active problems in shared launches (one per padded
- * cell size and colour) captured once per active set in a HIP graph, then
+ * Chebyshev step of all active problems in shared launches (one per degree)
+ * captured once per active set in a HIP graph, then
  * CholGS + RR per problem on host threads; a problem leaves the batch when its
  * wanted residuals are <= opts[i].tol or after opts[i].max_iter passes.
  * X[i]: device [n_dof_i x ld[i]] start block in, Ritz vectors out;
@@ -365,9 +363,9 @@ int chfsi_solve_batch(chfsi_ctx *const *ctxs, int n, const chfsi_opts *opts, dou
  * block and host result arrays must stay valid until it leaves); it starts at
  * the next pass with CholGS + RR of its block (a warm start needs nothing
  * else).  chfsi_batch_pass runs one pass for every problem in the session:
- * a degree-m filter (problems on a BF16 or BF16X3 rung share one
- * graph-captured sweep, problems on their FP32 rung another, problems on the
- * FP64 rung a third), then CholGS + RR per problem;
+ * a degree-m filter (problems on a BF16, BF16X3 or FP32 rung share one
+ * graph-captured sweep, problems on the FP64 rung another), then CholGS + RR
+ * per problem;
  * problems whose wanted residuals are <= tol, or that reached max_iter, leave
  * and their ids are written to done_ids (at most max_done; the rest are
  * reported by later calls).  Each problem follows its own precision ladder
@@ -412,33 +410,27 @@ size_t chfsi_footprint_bytes(int n_el, int p, int nblock, int block_width, chfsi
 int chfsi_device_bytes(const chfsi_ctx *ctx, size_t *bytes);
 const char *chfsi_status_string(int status);
 const char *chfsi_last_error(const chfsi_ctx *ctx);
-/* Timing of the cell-product kernel (the filter's dominant kernel): when
+/* Timing of the Chebyshev-step kernel (the filter's dominant kernel): when
  * enabled, every launch of it is bracketed by HIP events on the context
  * stream.  chfsi_last_filter_timing synchronises the stream and returns the
  * summed device time (ms) and the launch count since the last reset, plus
- * the cell-product work in those launches as cell-vector products
- * (cells x columns, so flops = 2 n_loc^2 x that count). */
+ * the work in those launches as cell-vectors (cells x columns). */
 int chfsi_set_timing(chfsi_ctx *ctx, int enable);
 int chfsi_reset_timing(chfsi_ctx *ctx);
 int chfsi_last_filter_timing(chfsi_ctx *ctx, double *ms_cells, int *n_launches, int64_t *cell_vecs);
-/* Tile configuration of the cell-product kernel (the filter's work-group
- * shape; Sec. 3.3 leaves the blocking of the cell-level products to the
- * implementation): -1 = built-in choice (default), 0 = four waves with two
- * 16-column blocks each, 1 = eight waves with one block each (more resident
- * waves, fewer accumulators).  Every variant computes the same products; an
- * autotuner times them per degree and precision and sets the faster.
- * Applies to later filter/apply calls and to batch sweeps built after it
- * (set it before adding the context to a batch session).  Errors:
- * CHFSI_ERR_ARG for a null ctx or a variant outside -1..1. */
+/* Tile of the Chebyshev-step kernel (Sec. 3.3 leaves the blocking to the
+ * implementation): -1 = built-in choice (default), 0 = 2 x 2 cells per
+ * work-group, 1 = 4 x 2 cells where that tile exists (FP64, degrees 3..5; else
+ * as 0).  Every variant computes the same bits; an autotuner times them per
+ * degree and precision and sets the faster.  Applies to later filter/apply
+ * calls and to batch sweeps built after it (set it before adding the context
+ * to a batch session).  Errors: CHFSI_ERR_ARG for a null ctx or a variant
+ * outside -1..1. */
 int chfsi_set_tile_variant(chfsi_ctx *ctx, int variant);
-/* Cells per work-group of the FP64/FP32 cell-product kernel (p <= 6; one
- * cell above): the tile's 64 columns are split over 1, 2 or 4 cells of one
- * colour, so a block of few columns pads fewer of them (24 columns fill a
- * 64-column tile to 37 %, and two 16-column groups of four cells to 75 %);
- * 0 (default) picks the count that pads the fewest columns, ties to fewer
- * cells.  Every setting computes the same products.  Applies to later
- * filter/apply calls and to batch sweeps built after it.  Errors:
- * CHFSI_ERR_ARG for a value other than 0, 1, 2, 4. */
+/* A hint for how many cells share a work-group's columns (0, 1, 2 or 4).  The
+ * step kernel's tile splits its lanes over cells by itself, so every setting
+ * runs the same kernel.  Errors: CHFSI_ERR_ARG for a value other than 0, 1, 2,
+ * 4. */
 int chfsi_set_cells_per_tile(chfsi_ctx *ctx, int cpt);
 /* How rayleighRitz (both forms) obtains Htilde times the rotated columns for
  * the residuals (Sec. 3.5 step iii leaves this open): 0 = cost model

@@ -566,7 +566,7 @@ class Context:
 
     # ---- timing of the cell-product kernel ---------------------------------
     def set_tile_variant(self, variant: int = -1):
-        """Cell-kernel tile configuration: -1 built-in, 0 four-wave, 1 eight-wave."""
+        """Tile of the step kernel: -1 built-in, 0 2 x 2 cells, 1 4 x 2 where available."""
         self._check(self._lib.chfsi_set_tile_variant(self._h, int(variant)), "set_tile_variant")
         self.tile_variant = int(variant)
         return self
@@ -583,7 +583,7 @@ class Context:
         return int(b.value)
 
     def set_cells_per_tile(self, cpt: int = 0):
-        """Cells per work-group of the cell kernel: 0 chosen from the column count, or 1, 2, 4."""
+        """Hint for the cells per work-group (0, 1, 2, 4); every setting runs the same kernel."""
         self._check(self._lib.chfsi_set_cells_per_tile(self._h, int(cpt)), "set_cells_per_tile")
         self.cells_per_tile = int(cpt)
         return self

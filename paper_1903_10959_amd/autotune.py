@@ -1,17 +1,15 @@
-"""Autotuner for the filter: vector-block width, cell-kernel tile and cells per tile.
+"""Autotuner for the filter: vector-block width, step-kernel tile and cells per tile.
 
 The paper picks its filtering block size B^f by experiment (Sec. 3.3: too small
 wastes memory bandwidth and latency, too large costs memory and batched-GEMM
 efficiency).  Here the same trade-off is measured on the device: for a live
 problem, a short filter (a few Chebyshev steps) is timed at each candidate
 width and the fastest is cached per (architecture, degree p, block size N_b,
-precision).  The cell kernel's work-group tile (four waves with two column
-blocks each, or eight waves with one) is chosen the same way, per
-(architecture, degree p, precision), and so is the number of cells a
-work-group holds (1, 2 or 4, the tile's 64 columns split over them), per
-(architecture, degree p, column count, precision): few columns per block
-waste fewer MFMA columns with more cells per tile.  Timing is wall time
-around the filter call, which returns synchronised.
+precision).  The step kernel's work-group tile (2 x 2 cells, or 4 x 2 where
+that tile exists) is chosen the same way, per (architecture, degree p,
+precision), and so is the cells-per-tile hint, per (architecture, degree p,
+column count, precision), which no kernel of this build depends on.  Timing is
+wall time around the filter call, which returns synchronised.
 """
 from __future__ import annotations
 
@@ -99,7 +97,7 @@ def tune_block_width(ctx, X, bounds, prec: str = "fp64", steps: int = 3, arch: s
 
 def tune_tile_variant(ctx, X, bounds, prec: str = "fp32", steps: int = 4, arch: str = None,
                       cache_path: str = DEFAULT_CACHE, refresh: bool = False, timer=None, apply: bool = True):
-    """Fastest cell-kernel tile variant for ctx's degree and precision; sets it
+    """Fastest step-kernel tile variant for ctx's degree and precision; sets it
     on ctx when apply is true.  X (device, DoF-major) is filtered in place by
     each trial, so pass a scratch copy.  `timer(variant) -> seconds` replaces
     the device measurement (used by the tests)."""

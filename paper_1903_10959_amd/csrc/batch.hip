@@ -1,9 +1,9 @@
 // Batched ChFSI over many independent problems (the paper's k-point groups,
 // placed on one device), as a session whose membership changes between passes
 // (continuous batching).  One Chebyshev step of every problem in a precision
-// group (BF16 / BF16x3, FP32, FP64) runs in shared launches, one per (padded
-// cell size, colour), from a device work list of (problem, cell, column tile)
-// items.  The degree-m sweep
+// group (FP32 state: BF16, BF16x3 and FP32 rungs; FP64) runs in shared
+// launches, one per degree, from a device work list of (problem, tile, z chunk,
+// column group) items.  The degree-m sweep
 // of a group is captured once per membership in a HIP graph and replayed each
 // pass; only the per-problem recursion coefficients change between passes and
 // are copied to the device before the replay.  CholGS and Rayleigh-Ritz run
@@ -71,7 +71,6 @@ int n_rungs(const Prob &p) { return std::max(1, std::min(p.o.n_ladder, 4)); }
 int mixed_now(const Prob &p) {
   return (p.o.mixed_cholgs && (p.o.n_ladder <= 1 || p.rung + 1 < n_rungs(p))) ? 1 : 0;
 }
-bool bf16_rung(const Prob &p) { return rung_prec(p) == CHFSI_BF16 || rung_prec(p) == CHFSI_BF16X3; }
 double rung_tol(const Prob &p) {
   if (p.o.ladder_tol[p.rung] > 0) return p.o.ladder_tol[p.rung];
   const chfsi_prec pr = rung_prec(p);
@@ -84,31 +83,13 @@ double max_wanted(const Prob &p) {
   return m;
 }
 
-// recursion roles at step k: (cur, prev, out) of the three buffers
-void roles(int degree, std::vector<int> &cur, std::vector<int> &prev, std::vector<int> &out, int &final_buf) {
-  int c = 0, p = -1;
-  cur.clear();
-  prev.clear();
-  out.clear();
-  for (int k = 0; k < degree; ++k) {
-    int o = 0;
-    while (o == c || o == p) ++o;
-    cur.push_back(c);
-    prev.push_back(p);
-    out.push_back(o);
-    p = c;
-    c = o;
-  }
-  final_buf = c;
-}
-
 template <typename T>
 struct Sweep {
   DevBuf probs, work, coef;
-  std::vector<int> members;      // problem ids of the captured graph (BF16: 2 id + split)
+  std::vector<int> members;      // 2 id + (on a BF16 rung) of the captured graph's problems
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
-  std::vector<T> hcoef;
+  std::vector<double> hcoef;
   void drop_graph() {
     if (exec) (void)hipGraphExecDestroy(exec);
     if (graph) (void)hipGraphDestroy(graph);
@@ -134,8 +115,7 @@ struct chfsi_batch {
   std::vector<Prob> probs;       // indexed by id
   std::deque<int> finished;      // ids that left and are not reported yet
   Sweep<double> s64;
-  Sweep<float> s32;
-  Sweep<float> sbf;              // BF16 and BF16x3 rungs (FP32 recursion state)
+  Sweep<float> s32;              // BF16, BF16x3 and FP32 rungs (FP32 recursion state)
   bool verbose = false;
   int threads = 8;               // host threads for the per-problem CholGS / Rayleigh-Ritz
   // shared Jacobi eigensolve of the projected Hamiltonians
@@ -191,198 +171,106 @@ int build_sweep(chfsi_batch *B, Sweep<T> &S, const std::vector<int> &ids, const 
   S.drop_graph();
   if (ids.empty()) return 0;
   const bool f64 = sizeof(T) == 8;
-  std::vector<BatchProblem<T>> hp;
-  // (np, (tile variant + 1) * 8 + cells per tile, colour) -> work items
-  std::map<std::tuple<int, int, int>, std::vector<int4>> lists;
-  for (size_t m = 0; m < ids.size(); ++m) {
-    Prob &p = B->probs[ids[m]];
-    chfsi_ctx *c = p.c;
-    const int nb = p.o.nblock;
-    BatchProblem<T> P;
-    P.buf[0] = f64 ? (T *)p.X : c->fbuf[0].as<T>();
-    P.ld[0] = f64 ? p.ld : nb;
-    P.buf[1] = c->fbuf[1].as<T>();
-    P.buf[2] = c->fbuf[2].as<T>();
-    P.ld[1] = P.ld[2] = nb;
-    P.K = f64 ? (const T *)c->K64.p : (const T *)c->K32.p;
-    P.cmap = c->cmap.as<int32_t>();
-    P.minv = f64 ? (const T *)c->minv64.p : (const T *)c->minv32.p;
-    P.V = f64 ? (const T *)c->V64.p : (const T *)c->V32.p;
-    P.coef = nullptr;
-    P.cells = c->cells.as<int32_t>();
-    P.n_loc = c->mesh.n_loc;
-    P.q = c->mesh.q;
-    P.n_el = c->mesh.n_el;
-    P.ncols = nb;
-    hp.push_back(P);
-    const int cpt = cells_per_tile(c, nb, hx_tile_width<T>(c->mesh.np, c->tile_variant, 1));
-    const int cw = hx_tile_width<T>(c->mesh.np, c->tile_variant, cpt);
-    if (cw <= 0) return bfail(B, CHFSI_ERR_ARG, "batch: no cell kernel for a problem's degree");
-    const int ntiles = (nb + cw - 1) / cw;
-    for (int col = 0; col < 8; ++col) {
-      const int e0 = c->mesh.color_offset[col], e1 = c->mesh.color_offset[col + 1];
-      for (int s = e0; s < e1; s += cpt)
-        for (int t = 0; t < ntiles; ++t)
-          lists[{c->mesh.np, (c->tile_variant + 1) * 8 + cpt, col}].push_back(
-              make_int4((int)m, s, t, std::min(cpt, e1 - s)));
-    }
-  }
-  BCHK(B, S.coef.ensure((size_t)3 * B->degree * ids.size() * sizeof(T)));
-  for (size_t m = 0; m < hp.size(); ++m) hp[m].coef = S.coef.template as<T>() + (size_t)3 * B->degree * m;
-  std::vector<int4> all;
-  std::vector<std::tuple<int, int, int>> groups;  // (np, (tile variant + 1) * 8 + cells per tile, offset)
-  std::vector<int> counts;
-  // colour-major launch order: every problem sees its colours in order 0..7
-  for (int col = 0; col < 8; ++col)
-    for (auto &kv : lists)
-      if (std::get<2>(kv.first) == col) {
-        groups.push_back({std::get<0>(kv.first), std::get<1>(kv.first), (int)all.size()});
-        counts.push_back((int)kv.second.size());
-        all.insert(all.end(), kv.second.begin(), kv.second.end());
-      }
-  BCHK(B, S.probs.ensure(hp.size() * sizeof(BatchProblem<T>)));
-  BCHK(B, S.work.ensure(all.size() * sizeof(int4)));
-  BCHK(B, hipMemcpyAsync(S.probs.p, hp.data(), hp.size() * sizeof(BatchProblem<T>), hipMemcpyHostToDevice, B->stream));
-  BCHK(B, hipMemcpyAsync(S.work.p, all.data(), all.size() * sizeof(int4), hipMemcpyHostToDevice, B->stream));
-  BCHK(B, hipStreamSynchronize(B->stream));
-  std::vector<int> cur, prev, out;
-  int final_buf = 0;
-  roles(B->degree, cur, prev, out, final_buf);
-  BCHK(B, hipStreamBeginCapture(B->stream, hipStreamCaptureModeThreadLocal));
-  if (!f64)
-    for (int id : ids) {
-      Prob &p = B->probs[id];
-      copy_cols_launch<double, float>(p.X, p.ld, p.c->fbuf[0].as<float>(), p.o.nblock, p.c->mesh.n_dof, p.o.nblock,
-                                      B->stream);
-    }
-  int lerr = 0;
-  for (int k = 0; k < B->degree; ++k)
-    for (size_t g = 0; g < groups.size(); ++g)
-      lerr |= hx_cells_batch_launch<T>(std::get<0>(groups[g]), std::get<1>(groups[g]) / 8 - 1,
-                                       std::get<1>(groups[g]) % 8, S.probs.template as<BatchProblem<T>>(),
-                                       S.work.template as<int4>() + std::get<2>(groups[g]), counts[g], k, cur[k],
-                                       prev[k], out[k], B->stream);
-  for (size_t m = 0; m < ids.size(); ++m) {
-    Prob &p = B->probs[ids[m]];
-    if (!f64)
-      copy_cols_launch<float, double>((const float *)hp[m].buf[final_buf], hp[m].ld[final_buf], p.X, p.ld,
-                                      p.c->mesh.n_dof, p.o.nblock, B->stream);
-    else if (final_buf != 0)
-      copy_cols_launch<double, double>((const double *)hp[m].buf[final_buf], hp[m].ld[final_buf], p.X, p.ld,
-                                       p.c->mesh.n_dof, p.o.nblock, B->stream);
-  }
-  hipError_t ce = hipStreamEndCapture(B->stream, &S.graph);
-  if (ce != hipSuccess) return bfail(B, CHFSI_ERR_HIP, std::string("graph capture: ") + hipGetErrorString(ce));
-  if (lerr) return bfail(B, CHFSI_ERR_ARG, "batch: no cell kernel for a problem's degree");
-  BCHK(B, hipGraphInstantiate(&S.exec, S.graph, nullptr, nullptr, 0));
-  S.members = key;
-  return 0;
-}
-
-// The BF16 sweep: BF16 (or hi/lo split) cell products on FP32 recursion
-// state, one launch per (padded size, split, colour) and step; one cell x 64
-// columns per work item.
-int build_sweep_bf16(chfsi_batch *B, Sweep<float> &S, const std::vector<int> &ids, const std::vector<int> &key) {
-  S.drop_graph();
-  if (ids.empty()) return 0;
-  constexpr int TWB = 64;
-  std::vector<BatchProblemBf16> hp;
-  // (npb, split, colour) -> work items
-  std::map<std::tuple<int, int, int>, std::vector<int4>> lists;
-  for (size_t m = 0; m < ids.size(); ++m) {
-    Prob &p = B->probs[ids[m]];
-    chfsi_ctx *c = p.c;
-    const int nb = p.o.nblock;
-    if (c->npb <= 0) return bfail(B, CHFSI_ERR_ARG, "batch: no BF16 cell kernel for a problem's degree");
-    BatchProblemBf16 P;
-    for (int k = 0; k < 3; ++k) {
-      P.buf[k] = c->fbuf[k].as<float>();
-      P.ld[k] = nb;
-    }
-    P.Kh = c->Kbh.as<const __bf16>();
-    P.Kl = c->Kbl.as<const __bf16>();
-    P.cmap = c->cmap.as<int32_t>();
-    P.cells = c->cells.as<int32_t>();
-    P.minv = c->minv32.as<float>();
-    P.V = c->V32.as<float>();
-    P.coef = nullptr;
-    P.n_loc = c->mesh.n_loc;
-    P.q = c->mesh.q;
-    P.n_el = c->mesh.n_el;
-    P.ncols = nb;
-    hp.push_back(P);
-    const int split = rung_prec(p) == CHFSI_BF16X3 ? 1 : 0;
-    const int ntiles = (nb + TWB - 1) / TWB;
-    for (int col = 0; col < 8; ++col)
-      for (int e = c->mesh.color_offset[col]; e < c->mesh.color_offset[col + 1]; ++e)
-        for (int t = 0; t < ntiles; ++t) lists[{c->npb, split, col}].push_back(make_int4((int)m, e, t, 1));
-  }
-  BCHK(B, S.coef.ensure((size_t)3 * B->degree * ids.size() * sizeof(float)));
-  for (size_t m = 0; m < hp.size(); ++m) hp[m].coef = S.coef.as<float>() + (size_t)3 * B->degree * m;
-  std::vector<int4> all;
-  std::vector<std::tuple<int, int, int>> groups;  // (npb, split, offset)
-  std::vector<int> counts;
-  for (int col = 0; col < 8; ++col)
-    for (auto &kv : lists)
-      if (std::get<2>(kv.first) == col) {
-        groups.push_back({std::get<0>(kv.first), std::get<1>(kv.first), (int)all.size()});
-        counts.push_back((int)kv.second.size());
-        all.insert(all.end(), kv.second.begin(), kv.second.end());
-      }
-  BCHK(B, S.probs.ensure(hp.size() * sizeof(BatchProblemBf16)));
-  BCHK(B, S.work.ensure(all.size() * sizeof(int4)));
-  BCHK(B, hipMemcpyAsync(S.probs.p, hp.data(), hp.size() * sizeof(BatchProblemBf16), hipMemcpyHostToDevice,
-                         B->stream));
-  BCHK(B, hipMemcpyAsync(S.work.p, all.data(), all.size() * sizeof(int4), hipMemcpyHostToDevice, B->stream));
-  BCHK(B, hipStreamSynchronize(B->stream));
-  std::vector<int> cur, prev, out;
-  int final_buf = 0;
-  roles(B->degree, cur, prev, out, final_buf);
-  BCHK(B, hipStreamBeginCapture(B->stream, hipStreamCaptureModeThreadLocal));
+  // Buffers: FP64 alternates the caller's block with one of the session's,
+  // FP32 (and an FP64 block whose rows are too far apart for the tile kernel)
+  // two of the session's, converted on the way in and out.
+  std::vector<KronBatchProblem<T>> hp;
+  std::vector<int> copied;
+  int64_t total = 0;                               // planes of all tiles, for the z chunks
   for (int id : ids) {
     Prob &p = B->probs[id];
-    copy_cols_launch<double, float>(p.X, p.ld, p.c->fbuf[0].as<float>(), p.o.nblock, p.c->mesh.n_dof, p.o.nblock,
-                                    B->stream);
+    chfsi_ctx *c = p.c;
+    const int nb = p.o.nblock;
+    const bool direct = f64 && kron_tiled(c->mesh.p, c->mesh.n, std::max<int64_t>(p.ld, 32), sizeof(T));
+    KronBatchProblem<T> P;
+    P.buf[0] = direct ? row_major<T>(c, (T *)p.X, p.ld) : work_block<T>(c, c->fbuf[1].as<T>(), nb);
+    P.buf[1] = work_block<T>(c, c->fbuf[0].as<T>(), nb);
+    P.V = c->V64.as<double>();
+    P.ae = c->ae64.as<double>();
+    P.coef = nullptr;
+    P.n_el = c->mesh.n_el;
+    P.n = c->mesh.n;
+    P.periodic = c->mesh.periodic;
+    P.ncols = nb;
+    P.bf16 = !f64 && rung_prec(p) == CHFSI_BF16;
+    hp.push_back(P);
+    copied.push_back(!direct);
+    const int v = kron_batch_variant<T>(c->mesh.p, c->tile_variant, c->mesh.n_el, nb);
+    const int64_t tiles = kron_batch_tiles<T>(c->mesh.p, v, c->mesh.n_el, nb);
+    if (tiles < 0) return bfail(B, CHFSI_ERR_ARG, "batch: no step kernel for a problem's degree");
+    total += tiles * c->mesh.n_el * c->mesh.p;
+  }
+  BCHK(B, S.coef.ensure((size_t)3 * B->degree * ids.size() * sizeof(double)));
+  for (size_t m = 0; m < hp.size(); ++m) hp[m].coef = S.coef.template as<double>() + (size_t)3 * B->degree * m;
+  // (degree, tile variant) -> work items; a problem's z chunks as if it had its
+  // share of the chip
+  std::map<std::pair<int, int>, std::vector<int4>> lists;
+  for (size_t m = 0; m < ids.size(); ++m) {
+    const Prob &p = B->probs[ids[m]];
+    const MeshTables &M = p.c->mesh;
+    const int v = kron_batch_variant<T>(M.p, p.c->tile_variant, M.n_el, p.o.nblock);
+    const int64_t tiles = kron_batch_tiles<T>(M.p, v, M.n_el, p.o.nblock);
+    const int64_t share = std::max<int64_t>(1, total / (M.n_el * M.p));   // tiles of this mesh with as much work as the batch
+    kron_batch_work<T>(M.p, v, M.n_el, p.o.nblock, (int)m, kron_zlen(M.n_el, M.p, std::max(tiles, share)),
+                       lists[{M.p, v}]);
+  }
+  std::vector<int4> all;
+  struct Group {
+    int p, variant, first, count;
+  };
+  std::vector<Group> groups;
+  for (auto &kv : lists) {
+    groups.push_back({kv.first.first, kv.first.second, (int)all.size(), (int)kv.second.size()});
+    all.insert(all.end(), kv.second.begin(), kv.second.end());
+  }
+  BCHK(B, S.probs.ensure(hp.size() * sizeof(KronBatchProblem<T>)));
+  BCHK(B, S.work.ensure(all.size() * sizeof(int4)));
+  BCHK(B, hipMemcpyAsync(S.probs.p, hp.data(), hp.size() * sizeof(KronBatchProblem<T>), hipMemcpyHostToDevice, B->stream));
+  BCHK(B, hipMemcpyAsync(S.work.p, all.data(), all.size() * sizeof(int4), hipMemcpyHostToDevice, B->stream));
+  BCHK(B, hipStreamSynchronize(B->stream));
+  BCHK(B, hipStreamBeginCapture(B->stream, hipStreamCaptureModeThreadLocal));
+  for (size_t m = 0; m < ids.size(); ++m) {
+    const Prob &p = B->probs[ids[m]];
+    if (copied[m])
+      copy_cols_launch<double, T>(ColBuf<double>{p.X, p.ld, 0}, INT32_MAX, hp[m].buf[0], group_of(p.c, sizeof(T)),
+                                  p.c->mesh.n_dof, p.o.nblock, B->stream);
   }
   int lerr = 0;
   for (int k = 0; k < B->degree; ++k)
-    for (size_t g = 0; g < groups.size(); ++g)
-      lerr |= hx_cells_bf16_batch_launch(std::get<0>(groups[g]), std::get<1>(groups[g]),
-                                         S.probs.as<BatchProblemBf16>(), S.work.as<int4>() + std::get<2>(groups[g]),
-                                         counts[g], k, cur[k], prev[k], out[k], B->stream);
+    for (const Group &g : groups)
+      lerr |= kron_batch_launch<T>(g.p, g.variant, S.probs.template as<KronBatchProblem<T>>(),
+                                   S.work.template as<int4>() + g.first, g.count, k, B->stream);
   for (size_t m = 0; m < ids.size(); ++m) {
-    Prob &p = B->probs[ids[m]];
-    copy_cols_launch<float, double>((const float *)hp[m].buf[final_buf], hp[m].ld[final_buf], p.X, p.ld,
-                                    p.c->mesh.n_dof, p.o.nblock, B->stream);
+    const Prob &p = B->probs[ids[m]];
+    const int last = B->degree & 1;
+    if (copied[m] || last)
+      copy_cols_launch<T, double>(hp[m].buf[last], group_of(p.c, sizeof(T)), ColBuf<double>{p.X, p.ld, 0}, INT32_MAX,
+                                  p.c->mesh.n_dof, p.o.nblock, B->stream);
   }
   hipError_t ce = hipStreamEndCapture(B->stream, &S.graph);
   if (ce != hipSuccess) return bfail(B, CHFSI_ERR_HIP, std::string("graph capture: ") + hipGetErrorString(ce));
-  if (lerr) return bfail(B, CHFSI_ERR_ARG, "batch: no BF16 cell kernel for a problem's degree");
+  if (lerr) return bfail(B, CHFSI_ERR_ARG, "batch: no step kernel for a problem's degree");
   BCHK(B, hipGraphInstantiate(&S.exec, S.graph, nullptr, nullptr, 0));
   S.members = key;
   return 0;
 }
 
 // One pass of a precision group's sweep: (re)captures the graph when the
-// membership (for the BF16 group: with each member's split) changed, then
-// uploads the recursion coefficients and replays it.
+// membership or a member's rounding to BF16 changed, then uploads the
+// recursion coefficients and replays it.
 template <typename T>
-int run_sweep(chfsi_batch *B, Sweep<T> &S, const std::vector<int> &ids, float *ms_out, bool bf16 = false) {
+int run_sweep(chfsi_batch *B, Sweep<T> &S, const std::vector<int> &ids, float *ms_out) {
   *ms_out = 0;
   if (ids.empty()) return 0;
   std::vector<int> key(ids);
-  if (bf16)
-    for (size_t m = 0; m < ids.size(); ++m) key[m] = 2 * ids[m] + (rung_prec(B->probs[ids[m]]) == CHFSI_BF16X3);
+  for (size_t m = 0; m < ids.size(); ++m) key[m] = 2 * ids[m] + (rung_prec(B->probs[ids[m]]) == CHFSI_BF16);
   if (key != S.members) {
     const auto t0 = std::chrono::steady_clock::now();
-    int r;
-    if constexpr (sizeof(T) == 4) r = bf16 ? build_sweep_bf16(B, S, ids, key) : build_sweep<T>(B, S, ids, key);
-    else r = build_sweep<T>(B, S, ids, key);
-    if (r) return r;
+    if (int r = build_sweep<T>(B, S, ids, key)) return r;
     B->build_ms += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
   }
   const int m_deg = B->degree;
-  S.hcoef.assign((size_t)3 * m_deg * ids.size(), T(0));
+  S.hcoef.assign((size_t)3 * m_deg * ids.size(), 0.0);
   for (size_t m = 0; m < ids.size(); ++m) {
     Prob &p = B->probs[ids[m]];
     const int nb = p.o.nblock;
@@ -391,7 +279,7 @@ int run_sweep(chfsi_batch *B, Sweep<T> &S, const std::vector<int> &ids, float *m
     // normalised recursion: rho_1 = 1/xi0, rho_{k+1} = 1/(2 xi0 - rho_k)
     const double cc = 0.5 * (a + b), e = 0.5 * (b - a), xi0 = (a0 - cc) / e;
     double rho = 1.0 / xi0;
-    T *tc = S.hcoef.data() + (size_t)3 * m_deg * m;
+    double *tc = S.hcoef.data() + (size_t)3 * m_deg * m;
     for (int k = 0; k < m_deg; ++k) {
       double s1, s2;
       if (k == 0) {
@@ -403,12 +291,12 @@ int run_sweep(chfsi_batch *B, Sweep<T> &S, const std::vector<int> &ids, float *m
         s2 = -rn * rho;
         rho = rn;
       }
-      tc[3 * k] = (T)s1;
-      tc[3 * k + 1] = (T)s2;
-      tc[3 * k + 2] = (T)cc;
+      tc[3 * k] = s1;
+      tc[3 * k + 1] = s2;
+      tc[3 * k + 2] = cc;
     }
   }
-  BCHK(B, hipMemcpyAsync(S.coef.p, S.hcoef.data(), S.hcoef.size() * sizeof(T), hipMemcpyHostToDevice, B->stream));
+  BCHK(B, hipMemcpyAsync(S.coef.p, S.hcoef.data(), S.hcoef.size() * sizeof(double), hipMemcpyHostToDevice, B->stream));
   hipEvent_t e0, e1;
   BCHK(B, hipEventCreate(&e0));
   BCHK(B, hipEventCreate(&e1));
@@ -514,7 +402,6 @@ extern "C" int chfsi_batch_destroy(chfsi_batch *b) {
   (void)hipStreamSynchronize(b->stream);
   b->s64.release();
   b->s32.release();
-  b->sbf.release();
   b->jac_table.release();
   b->jac_norms.release();
   (void)hipStreamDestroy(b->stream);
@@ -538,15 +425,17 @@ extern "C" int chfsi_batch_add(chfsi_batch *b, chfsi_ctx *c, const chfsi_opts *o
     const chfsi_prec pr = o->n_ladder > 0 ? o->ladder[k] : CHFSI_FP64;
     if (pr != CHFSI_FP64 && pr != CHFSI_FP32 && pr != CHFSI_BF16 && pr != CHFSI_BF16X3)
       return bfail(b, CHFSI_ERR_ARG, "batch: unknown ladder precision");
-    if ((pr == CHFSI_BF16 || pr == CHFSI_BF16X3) && c->npb <= 0)
+    if ((pr == CHFSI_BF16 || pr == CHFSI_BF16X3) && c->mesh.p > 7)
       return bfail(b, CHFSI_ERR_ARG, "batch: BF16 rungs need degree p <= 7");
   }
   for (const Prob &p : b->probs)
     if (!p.done && p.c == c) return bfail(b, CHFSI_ERR_ARG, "batch: the context is already in the session");
   if (int r = ensure_small(c, o->nblock)) return bfail(b, r, "batch: " + c->err);
-  const size_t bytes = (size_t)c->mesh.n_dof * o->nblock * sizeof(double);  // FP64-sized for any rung
+  const size_t bytes = (size_t)c->mesh.n_dof * o->nblock * sizeof(double);
+  // FP64-sized for any rung, columns padded to whole groups
+  const size_t wbytes = std::max(work_bytes(c, o->nblock, sizeof(double)), work_bytes(c, o->nblock, sizeof(float)));
   for (int k = 0; k < 3; ++k)
-    if (c->fbuf[k].ensure(bytes) != hipSuccess) return bfail(b, CHFSI_ERR_OOM, "batch: filter buffers");
+    if (c->fbuf[k].ensure(wbytes) != hipSuccess) return bfail(b, CHFSI_ERR_OOM, "batch: filter buffers");
   if (c->HX.ensure(bytes) != hipSuccess) return bfail(b, CHFSI_ERR_OOM, "batch: HX buffer");
   Prob p;
   p.id = (int)b->probs.size();
@@ -582,7 +471,7 @@ extern "C" int chfsi_batch_pass(chfsi_batch *b, int *done_ids, int *n_done, int 
   }
   // 2. filter sweeps, one per precision group; a problem whose Ritz values do
   // not give valid filter bounds (a0 < a < b) leaves with CHFSI_ERR_NONFINITE
-  std::vector<int> gbf, g32, g64;
+  std::vector<int> g32, g64;
   for (Prob &p : b->probs) {
     if (p.done) continue;
     const int nb = p.o.nblock;
@@ -591,21 +480,19 @@ extern "C" int chfsi_batch_pass(chfsi_batch *b, int *done_ids, int *n_done, int 
       finish_prob(b, p, CHFSI_ERR_NONFINITE);
       continue;
     }
-    (bf16_rung(p) ? gbf : rung_prec(p) == CHFSI_FP32 ? g32 : g64).push_back(p.id);
+    (rung_prec(p) == CHFSI_FP64 ? g64 : g32).push_back(p.id);
   }
-  float msbf = 0, ms32 = 0, ms64 = 0;
+  float ms32 = 0, ms64 = 0;
   b->build_ms = 0;
   const auto t_sw = std::chrono::steady_clock::now();
-  if (int r = run_sweep<float>(b, b->sbf, gbf, &msbf, true)) return r;
   if (int r = run_sweep<float>(b, b->s32, g32, &ms32)) return r;
   if (int r = run_sweep<double>(b, b->s64, g64, &ms64)) return r;
   // 3. CholGS + RR of every swept problem
-  std::vector<int> swept(gbf);
-  swept.insert(swept.end(), g32.begin(), g32.end());
+  std::vector<int> swept(g32);
   swept.insert(swept.end(), g64.begin(), g64.end());
   for (int id : swept) {
     Prob &p = b->probs[id];
-    p.rep.t_filter += (bf16_rung(p) ? msbf : rung_prec(p) == CHFSI_FP32 ? ms32 : ms64) * 1e-3;
+    p.rep.t_filter += (rung_prec(p) == CHFSI_FP64 ? ms64 : ms32) * 1e-3;
     p.rep.dofvecs += p.c->mesh.n_dof * (int64_t)p.o.nblock * b->degree;
   }
   const auto t_ss = std::chrono::steady_clock::now();
@@ -622,9 +509,9 @@ extern "C" int chfsi_batch_pass(chfsi_batch *b, int *done_ids, int *n_done, int 
     double worst = 0;
     for (int id : swept) worst = std::max(worst, b->probs[id].res);
     std::fprintf(stderr,
-                 "[chfsi] batch pass: %zu BF16 + %zu FP32 + %zu FP64 problems swept (%.2f + %.2f + %.2f ms on the "
+                 "[chfsi] batch pass: %zu BF16/FP32 + %zu FP64 problems swept (%.2f + %.2f ms on the "
                  "device, %.2f ms wall incl. %.2f ms graph builds), CholGS/RR %.2f ms, %d remain, max residual %.3e\n",
-                 gbf.size(), g32.size(), g64.size(), msbf, ms32, ms64,
+                 g32.size(), g64.size(), ms32, ms64,
                  std::chrono::duration<double, std::milli>(t_ss - t_sw).count(), b->build_ms,
                  std::chrono::duration<double, std::milli>(t_end - t_ss).count(), remaining, worst);
     std::fflush(stderr);
@@ -679,19 +566,19 @@ extern "C" int chfsi_batch_set_threads(chfsi_batch *b, int threads) {
 
 extern "C" size_t chfsi_batch_footprint_bytes(int n_el, int p, int nblock) {
   if (n_el < 1 || p < 1 || p > 7 || nblock < 1) return 0;
-  const size_t n = (size_t)n_el * p - 1, nd = n * n * n, ncell = (size_t)n_el * n_el * n_el;
+  const size_t n = (size_t)n_el * p - 1, nd = n * n * n;
   if (nd < (size_t)nblock) return 0;
-  const size_t nl = (size_t)(p + 1) * (p + 1) * (p + 1), np = (nl + 15) / 16 * 16, npb = (nl + 31) / 32 * 32;
   const size_t nb = (size_t)nblock, nb32 = (nb + 31) / 32;
   // mesh and potential tables (set_mesh, set_potential)
-  size_t b = ncell * nl * 4 + ncell * 4 + np * np * 12 + nd * 24 + npb * npb * 4;
+  size_t b = nd * 16 + (size_t)16 * (p + 1) * (p + 1);
   // workspaces of the CholGS / Rayleigh-Ritz steps (ensure_small)
   b += 3 * nb * nb * 8 + nb32 * 32 * 32 * 8 + jacobi_work_elems(nblock) * 8 + 3 * nb * 8 + 4 * sizeof(int) +
        nb32 * 8;
   b += rmul_scratch_elems((int64_t)nd, nblock) * 8;
   b += gram_part_elems_slots((int64_t)nd, nblock, 512) * 8;       // 256 CUs x 2 resident gram work-groups
   b += (size_t)resid_nchunk((int64_t)nd) * nb * 8;
-  // the session's three recursion buffers (FP64-sized for either rung) and HX
-  b += 4 * nd * nb * 8;
+  // the session's three recursion buffers (FP64-sized for either rung, columns
+  // in whole groups) and HX
+  b += 3 * nd * std::max((nb + 15) / 16 * 16 * 8, (nb + 31) / 32 * 32 * 4) + nd * nb * 8;
   return b;
 }

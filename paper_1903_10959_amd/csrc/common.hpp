@@ -7,7 +7,6 @@ namespace chfsi {
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
 // 16x16x4 MFMA tiles.  Lane l supplies A[i = l%16][k = l/16] and
 // B[k = l/16][j = l%16].  Accumulator element r (0..3) of lane l holds
@@ -19,12 +18,6 @@ __device__ __forceinline__ v4d mfma16x4(double a, double b, v4d c) {
 __device__ __forceinline__ v4f mfma16x4(float a, float b, v4f c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
-// 16x16x32 BF16 tile, FP32 accumulation.  Lane l supplies
-// A[i = l%16][k = 8*(l/16) + t] and B[k = 8*(l/16) + t][j = l%16], t = 0..7.
-__device__ __forceinline__ v4f mfma16x32bf(v8bf a, v8bf b, v4f c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
-
 template <typename T> __device__ __forceinline__ int acc_row(int kq, int r);
 template <> __device__ __forceinline__ int acc_row<double>(int kq, int r) { return kq + 4 * r; }
 template <> __device__ __forceinline__ int acc_row<float>(int kq, int r) { return 4 * kq + r; }

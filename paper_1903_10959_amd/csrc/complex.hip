@@ -15,7 +15,7 @@
 //    whose eigenvalues are those of Hhat, each twice; a selection kernel
 //    picks one complex eigenvector per pair (herm_select_launch) and builds
 //    emb(Q), so the rotation R emb(Q) is X Q.
-// The Chebyshev filter is the real recursion with the complex cell kernel.
+// The Chebyshev filter is the real recursion with the complex step kernel.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -139,50 +139,16 @@ int check_complex(chfsi_ctx *c, const void *X, int64_t ld, int ncols) {
   return 0;
 }
 
-// Y = s1 (Htilde_k - shift) X + s2 Xp on complex blocks (ld, ncols in complex elements).
-int cheb_step_c(chfsi_ctx *c, const double *X, int64_t ldx, const double *Xp, int64_t ldp, double *Y, int64_t ldy,
-                int ncols, double s1, double s2, double shift) {
-  const MeshTables &M = c->mesh;
-  HxArgs<double> a;
-  a.X = X;
-  a.ldx = 2 * ldx;
-  a.Xp = Xp;
-  a.ldp = 2 * ldp;
-  a.Y = Y;
-  a.ldy = 2 * ldy;
-  a.K = c->Kc64.as<double>();
-  a.cmap = c->cmap.as<int32_t>();
-  a.n_loc = M.n_loc;
-  a.np = M.np;
-  a.q = M.q;
-  a.n_el = M.n_el;
-  a.cells = c->cells.as<int32_t>();
-  a.minv = c->minv64.as<double>();
-  a.V = c->V64.as<double>();
-  a.ncols = 2 * ncols;
-  a.s1 = s1;
-  a.s2 = s2;
-  // the diagonal of Htilde_k is V + |k|^2 / 2; the epilogue adds s1 (V - shift) X
-  a.shift = shift - 0.5 * (c->kvec[0] * c->kvec[0] + c->kvec[1] * c->kvec[1] + c->kvec[2] * c->kvec[2]);
-  a.variant = c->tile_variant;
-  for (int col = 0; col < 8; ++col)
-    if (hx_cells_cplx_launch(a, M.color_offset[col], M.color_offset[col + 1], c->stream) != 0)
-      return fail(c, CHFSI_ERR_ARG, "complex step: unsupported cell size");
-  if (c->timing) c->cell_vecs += (int64_t)M.n_cells * 2 * ncols;
-  HIPCHK(c, hipGetLastError());
-  return 0;
-}
-
 int filter_c(chfsi_ctx *c, double *X, int64_t ld, int ncols, int degree, double a, double b, double a0, int bw) {
   const double cc = 0.5 * (a + b), e = 0.5 * (b - a), xi0 = (a0 - cc) / e;
   const int64_t nd = c->mesh.n_dof;
   bw = std::min(bw > 0 ? bw : 64, ncols);
-  for (int i = 0; i < 3; ++i) HIPCHK(c, c->fbuf[i].ensure((size_t)nd * bw * 16));
+  HIPCHK(c, c->fbuf[0].ensure(work_bytes(c, 2 * bw, sizeof(double))));
   for (int j0 = 0; j0 < ncols; j0 += bw) {
     const int w = std::min(bw, ncols - j0);
-    double *buf[3] = {X + 2 * j0, c->fbuf[1].as<double>(), c->fbuf[2].as<double>()};
-    const int64_t lds[3] = {ld, w, w};
-    int cur = 0, prev = -1;
+    // two buffers alternate, Z_{k+1} overwriting Z_{k-1} (complex w columns are 2 w doubles)
+    const ColBuf<double> buf[2] = {row_major<double>(c, X + 2 * j0, 2 * ld),
+                                   work_block<double>(c, c->fbuf[0].as<double>(), 2 * w, 2 * ld)};
     double rho = 1.0 / xi0;
     for (int k = 0; k < degree; ++k) {
       double s1, s2;
@@ -195,16 +161,12 @@ int filter_c(chfsi_ctx *c, double *X, int64_t ld, int ncols, int degree, double 
         s2 = -rn * rho;
         rho = rn;
       }
-      int out = 0;
-      while (out == cur || out == prev) ++out;
-      if (int r = cheb_step_c(c, buf[cur], lds[cur], prev >= 0 ? buf[prev] : nullptr, prev >= 0 ? lds[prev] : 0,
-                              buf[out], lds[out], w, s1, s2, cc))
-        return r;
-      prev = cur;
-      cur = out;
+      const ColBuf<double> &in = buf[k & 1], &out = buf[(k & 1) ^ 1];
+      if (int r = cheb_step_c(c, {in.p, in.ld, in.cg}, k > 0 ? out.p : nullptr, out, w, s1, s2, cc)) return r;
     }
-    // complex w columns are 2 w doubles
-    if (cur != 0) copy_cols_launch<double, double>(buf[cur], 2 * lds[cur], X + 2 * j0, 2 * ld, nd, 2 * w, c->stream);
+    if (degree & 1)
+      copy_cols_launch<double, double>(buf[1], group_of(c, sizeof(double), 2 * ld), buf[0], INT32_MAX, nd, 2 * w,
+                                       c->stream);
   }
   HIPCHK(c, c->flag.ensure(4 * sizeof(int)));
   zero_int_launch(c->flag.as<int>(), 1, c->stream);
@@ -223,7 +185,9 @@ int rr_c(chfsi_ctx *c, double *X, int64_t ld, int N, double *HX, int64_t ldh, do
   if (int r = ensure_small(c, n2)) return r;
   HIPCHK(c, c->csel.ensure((size_t)N * sizeof(double) + 16));
   // step i: HX = Htilde_k X, Hhat = X^H HX (as the embedding of the real Gram)
-  if (int r = cheb_step_c(c, X, ld, nullptr, 0, HX, ldh, N, 1.0, 0.0, 0.0)) return r;
+  if (int r = cheb_step_c(c, row_major<const double>(c, X, 2 * ld), nullptr, row_major<double>(c, HX, 2 * ldh), N, 1.0, 0.0,
+                          0.0))
+    return r;
   gram_launch(X, 2 * ld, HX, 2 * ldh, nd, n2, c->gram_part.as<double>(), c->Zmat.as<double>(), 0, c->stream);
   herm_embed_launch(c->Zmat.as<double>(), n2, c->Smat.as<double>(), c->stream);
   // step ii: eigenpairs of emb(Hhat), one complex eigenvector per pair
@@ -249,8 +213,10 @@ int rr_c(chfsi_ctx *c, double *X, int64_t ld, int N, double *HX, int64_t ldh, do
   const size_t se = c->rscratch.bytes / sizeof(double);
   if (rmul_cols_launch(X, 2 * ld, nd, n2, Qe, n2, n2, 0, 0, 0, scr, se, c->stream) != 0)
     return fail(c, CHFSI_ERR_ARG, "complex Rayleigh-Ritz: block too wide for the row-panel kernel");
-  if (rr_reapply(c, N)) {
-    if (int r = cheb_step_c(c, X, ld, nullptr, 0, HX, ldh, N, 1.0, 0.0, 0.0)) return r;
+  if (rr_reapply(c, n2)) {
+    if (int r = cheb_step_c(c, row_major<const double>(c, X, 2 * ld), nullptr, row_major<double>(c, HX, 2 * ldh), N, 1.0, 0.0,
+                          0.0))
+    return r;
   } else if (rmul_cols_launch(HX, 2 * ldh, nd, n2, Qe, n2, n2, 0, 0, 0, scr, se, c->stream) != 0) {
     return fail(c, CHFSI_ERR_ARG, "complex Rayleigh-Ritz: block too wide for the row-panel kernel");
   }

@@ -21,25 +21,6 @@
 
 using namespace chfsi;
 
-namespace {
-
-// FP32 -> BF16 bits, round to nearest even (finite inputs)
-static uint16_t bf16_rne(float f) {
-  uint32_t u;
-  std::memcpy(&u, &f, 4);
-  const uint32_t lsb = (u >> 16) & 1u;
-  u += 0x7FFFu + lsb;
-  return (uint16_t)(u >> 16);
-}
-static float bf16_to_float(uint16_t h) {
-  uint32_t u = (uint32_t)h << 16;
-  float f;
-  std::memcpy(&f, &u, 4);
-  return f;
-}
-
-}  // namespace
-
 namespace chfsi {
 int fail(chfsi_ctx *c, int code, const std::string &msg) {
   if (c) c->err = msg;
@@ -54,6 +35,41 @@ int set_dev(chfsi_ctx *c) {
   return 0;
 }
 }  // namespace chfsi
+
+// ---------------------------------------------------------------------------
+// Blocks as the step kernels see them
+// ---------------------------------------------------------------------------
+namespace {
+
+// The arguments that come from the context.
+template <typename T>
+KronArgs<T> kron_args(const chfsi_ctx *c, int ncols) {
+  const MeshTables &M = c->mesh;
+  KronArgs<T> a;
+  a.X = ColBuf<const T>{nullptr, 0, 0};
+  a.Xp = nullptr;
+  a.Y = ColBuf<T>{nullptr, 0, 0};
+  a.V = c->V64.as<double>();
+  a.ae = c->ae64.as<double>();
+  a.n_el = M.n_el;
+  a.p = M.p;
+  a.n = M.n;
+  a.periodic = M.periodic;
+  a.ncols = ncols;
+  a.s1 = 1;
+  a.s2 = 0;
+  a.shift = 0;
+  a.variant = c->tile_variant;
+  return a;
+}
+
+}  // namespace
+
+size_t chfsi::work_bytes(const chfsi_ctx *c, int w, size_t elem) {
+  const int g = kron_group(c->mesh.p, elem);
+  const size_t cols = g ? (size_t)(w + g - 1) / g * g : (size_t)w;
+  return (size_t)c->mesh.n_dof * cols * elem;
+}
 
 // ---------------------------------------------------------------------------
 // lifetime
@@ -117,8 +133,6 @@ extern "C" const char *chfsi_status_string(int s) {
 // ---------------------------------------------------------------------------
 // setMesh / setPotential
 // ---------------------------------------------------------------------------
-static int upload_kpoint(chfsi_ctx *c);
-
 static int set_mesh_impl(chfsi_ctx *c, double L, int n_el, int p, bool periodic) {
   if (!c) return CHFSI_ERR_ARG;
   if (c->device >= 0)
@@ -133,68 +147,18 @@ static int set_mesh_impl(chfsi_ctx *c, double L, int n_el, int p, bool periodic)
     return 0;
   }
   const MeshTables &M = c->mesh;
-  // the cell matrix, padded: np x np for the single-tile kernels (p <= 7);
-  // np x npr, npr a whole number of 224-row groups, for the row-group kernel
-  // of degrees 8..12
-  const size_t nl = M.n_loc, np = M.np, npr = M.p > 7 ? (size_t)hx_rows_padded(M.n_loc) : np;
-  HIPCHK(c, c->cmap.ensure(M.cmap.size() * sizeof(int32_t)));
-  HIPCHK(c, c->cells.ensure(M.cell_order.size() * sizeof(int32_t)));
-  HIPCHK(c, c->K64.ensure(np * npr * sizeof(double)));
-  HIPCHK(c, c->K32.ensure(np * npr * sizeof(float)));
-  HIPCHK(c, c->minv64.ensure(M.n_dof * sizeof(double)));
-  HIPCHK(c, c->minv32.ensure(M.n_dof * sizeof(float)));
-  std::vector<double> kp(np * npr, 0.0);
-  std::vector<float> kp32(np * npr, 0.f);
-  for (size_t i = 0; i < nl; ++i)
-    for (size_t j = 0; j < nl; ++j) {
-      kp[i * npr + j] = M.kcell[i * nl + j];
-      kp32[i * npr + j] = (float)M.kcell[i * nl + j];
-    }
+  std::vector<double> ae(M.ae);
+  ae.insert(ae.end(), M.ce.begin(), M.ce.end());
+  HIPCHK(c, c->ae64.ensure(ae.size() * sizeof(double)));
+  HIPCHK(c, hipMemcpyAsync(c->ae64.p, ae.data(), ae.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
   std::vector<double> mi(M.n_dof);
-  std::vector<float> mi32(M.n_dof);
-  for (int64_t i = 0; i < M.n_dof; ++i) {
-    mi[i] = 1.0 / std::sqrt(M.mass[i]);
-    mi32[i] = (float)mi[i];
-  }
-  HIPCHK(c, hipMemcpyAsync(c->cmap.p, M.cmap.data(), M.cmap.size() * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
-  HIPCHK(c, hipMemcpyAsync(c->cells.p, M.cell_order.data(), M.cell_order.size() * sizeof(int32_t),
-                           hipMemcpyHostToDevice, c->stream));
-  HIPCHK(c, hipMemcpyAsync(c->K64.p, kp.data(), kp.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
-  HIPCHK(c, hipMemcpyAsync(c->K32.p, kp32.data(), kp32.size() * sizeof(float), hipMemcpyHostToDevice, c->stream));
+  for (int64_t i = 0; i < M.n_dof; ++i) mi[i] = 1.0 / std::sqrt(M.mass[i]);
+  HIPCHK(c, c->minv64.ensure(M.n_dof * sizeof(double)));
   HIPCHK(c, hipMemcpyAsync(c->minv64.p, mi.data(), mi.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
-  HIPCHK(c, hipMemcpyAsync(c->minv32.p, mi32.data(), mi32.size() * sizeof(float), hipMemcpyHostToDevice, c->stream));
-  c->kc_stride = (int)npr;
-  if (M.p > 7) {
-    // no BF16 or complex cell kernel above p = 7
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-    c->npb = 0;
-    c->kvec[0] = c->kvec[1] = c->kvec[2] = 0.0;
-    c->kin_k = 3.0 * c->mesh.lam1d_max;
-    c->nk = 0;
-    c->has_mesh = true;
-    return 0;
-  }
-  // BF16 hi/lo split of the cell matrix, padded to a multiple of 32 (BF16 MFMA depth)
-  c->npb = (int)((nl + 31) / 32 * 32);
-  const size_t nb2 = (size_t)c->npb * c->npb;
-  std::vector<uint16_t> kh(nb2, 0), kl(nb2, 0);
-  for (size_t i = 0; i < nl; ++i)
-    for (size_t j = 0; j < nl; ++j) {
-      const float x = (float)M.kcell[i * nl + j];
-      const uint16_t h = bf16_rne(x);
-      kh[i * c->npb + j] = h;
-      kl[i * c->npb + j] = bf16_rne(x - bf16_to_float(h));
-    }
-  HIPCHK(c, c->Kbh.ensure(nb2 * 2));
-  HIPCHK(c, c->Kbl.ensure(nb2 * 2));
-  HIPCHK(c, hipMemcpyAsync(c->Kbh.p, kh.data(), nb2 * 2, hipMemcpyHostToDevice, c->stream));
-  HIPCHK(c, hipMemcpyAsync(c->Kbl.p, kl.data(), nb2 * 2, hipMemcpyHostToDevice, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));  // host staging vectors go out of scope
+  HIPCHK(c, hipStreamSynchronize(c->stream));    // host staging vectors go out of scope
   c->kvec[0] = c->kvec[1] = c->kvec[2] = 0.0;
   c->kin_k = 3.0 * c->mesh.lam1d_max;            // k = 0: the real periodic operator's bound
   c->nk = 0;                                     // a k-point group belongs to its mesh
-  if (M.periodic)
-    if (int r = upload_kpoint(c)) return r;
   c->has_mesh = true;
   return 0;
 }
@@ -205,34 +169,10 @@ extern "C" int chfsi_set_mesh_periodic(chfsi_ctx *c, double L, int n_el, int p) 
   return set_mesh_impl(c, L, n_el, p, true);
 }
 
-// The complex cell matrix of Htilde_k as the real contraction operator of the
-// interleaved layout: H^e = A - i B with A the stiffness of -1/2 Laplacian and
-// B = k.G; for Y = H^e X with X = Xr + i Xi, Y_re = A Xr + B Xi and
-// Y_im = A Xi - B Xr.  Stored as [A ; B^T] (2 np x np, row kappa holds the
-// weights of contraction index kappa for every output row), so the second half
-// of the contraction runs over the gathered X with its (re, im) pairs swapped
-// and the imaginary outputs negated.
-static int upload_kpoint(chfsi_ctx *c) {
-  const MeshTables &M = c->mesh;
-  const size_t nl = M.n_loc, np = M.np;
-  std::vector<double> kc(2 * np * np, 0.0);
-  for (size_t i = 0; i < nl; ++i)
-    for (size_t j = 0; j < nl; ++j) {
-      kc[i * np + j] = M.kcell[i * nl + j];
-      const double b = c->kvec[0] * M.gcell[0][i * nl + j] + c->kvec[1] * M.gcell[1][i * nl + j] +
-                       c->kvec[2] * M.gcell[2][i * nl + j];
-      kc[(np + j) * np + i] = b;                   // B^T: row kappa = j, output i
-    }
-  HIPCHK(c, c->Kc64.ensure(kc.size() * sizeof(double)));
-  HIPCHK(c, hipMemcpyAsync(c->Kc64.p, kc.data(), kc.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
-  return 0;
-}
-
 extern "C" int chfsi_set_kpoint(chfsi_ctx *c, double kx, double ky, double kz) {
   if (!c) return CHFSI_ERR_ARG;
   if (!c->has_mesh || !c->mesh.periodic) return fail(c, CHFSI_ERR_STATE, "set_kpoint: needs a periodic mesh");
-  if (c->mesh.p > 7) return fail(c, CHFSI_ERR_ARG, "set_kpoint: the complex cell kernel needs p <= 7");
+  if (c->mesh.p > 7) return fail(c, CHFSI_ERR_ARG, "set_kpoint: the complex step kernel needs p <= 7");
   if (!std::isfinite(kx) || !std::isfinite(ky) || !std::isfinite(kz))
     return fail(c, CHFSI_ERR_ARG, "set_kpoint: k must be finite");
   c->kvec[0] = kx;
@@ -248,15 +188,13 @@ extern "C" int chfsi_set_kpoint(chfsi_ctx *c, double kx, double ky, double kz) {
     kin += same >= 0 ? bloch_1d_max(c->mesh, std::fabs(c->kvec[same])) : bloch_1d_max(c->mesh, kd);
   }
   c->kin_k = kin;
-  if (c->device < 0) return 0;
-  if (int r = set_dev(c)) return r;
-  return upload_kpoint(c);
+  return 0;
 }
 
 extern "C" int chfsi_set_kpoints(chfsi_ctx *c, int nk, const double *k) {
   if (!c) return CHFSI_ERR_ARG;
   if (!c->has_mesh || !c->mesh.periodic) return fail(c, CHFSI_ERR_STATE, "set_kpoints: needs a periodic mesh");
-  if (c->mesh.p > 7) return fail(c, CHFSI_ERR_ARG, "set_kpoints: the complex cell kernel needs p <= 7");
+  if (c->mesh.p > 7) return fail(c, CHFSI_ERR_ARG, "set_kpoints: the complex step kernel needs p <= 7");
   if (nk < 1 || !k) return fail(c, CHFSI_ERR_ARG, "set_kpoints: need nk >= 1 and a host array of 3 nk values");
   for (int i = 0; i < 3 * nk; ++i)
     if (!std::isfinite(k[i])) return fail(c, CHFSI_ERR_ARG, "set_kpoints: k must be finite");
@@ -264,24 +202,9 @@ extern "C" int chfsi_set_kpoints(chfsi_ctx *c, int nk, const double *k) {
   c->nk = nk;
   if (c->device < 0) return 0;
   if (int r = set_dev(c)) return r;
-  const MeshTables &M = c->mesh;
-  const size_t nl = M.n_loc, np = M.np, per = 2 * np * np;
-  std::vector<double> kc(per * nk, 0.0), sh(nk);
-  for (int g = 0; g < nk; ++g) {
-    const double *kv = k + 3 * g;
-    double *o = kc.data() + g * per;
-    for (size_t i = 0; i < nl; ++i)
-      for (size_t j = 0; j < nl; ++j) {
-        o[i * np + j] = M.kcell[i * nl + j];
-        o[(np + j) * np + i] =
-            kv[0] * M.gcell[0][i * nl + j] + kv[1] * M.gcell[1][i * nl + j] + kv[2] * M.gcell[2][i * nl + j];
-      }
-    sh[g] = -0.5 * (kv[0] * kv[0] + kv[1] * kv[1] + kv[2] * kv[2]);
-  }
-  HIPCHK(c, c->Kcg.ensure(kc.size() * sizeof(double)));
-  HIPCHK(c, c->kshift.ensure(sh.size() * sizeof(double)));
-  HIPCHK(c, hipMemcpyAsync(c->Kcg.p, kc.data(), kc.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
-  HIPCHK(c, hipMemcpyAsync(c->kshift.p, sh.data(), sh.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
+  HIPCHK(c, c->kgroup_d.ensure((size_t)3 * nk * sizeof(double)));
+  HIPCHK(c, hipMemcpyAsync(c->kgroup_d.p, c->kgroup.data(), (size_t)3 * nk * sizeof(double), hipMemcpyHostToDevice,
+                           c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   return 0;
 }
@@ -296,31 +219,12 @@ extern "C" int chfsi_apply_complex_kpoints(chfsi_ctx *c, const void *X, void *Y,
   const char *xb = static_cast<const char *>(X), *yb = static_cast<const char *>(Y);
   const int64_t span = (int64_t)(c->nk - 1) * stride * 16 + M.n_dof * ld * 16;
   if (yb < xb + span && xb < yb + span) return fail(c, CHFSI_ERR_ARG, "apply_complex_kpoints: Y overlaps X");
-  HxArgs<double> a;
-  a.X = static_cast<const double *>(X);
-  a.ldx = 2 * ld;
-  a.Xp = nullptr;
-  a.ldp = 0;
-  a.Y = static_cast<double *>(Y);
-  a.ldy = 2 * ld;
-  a.K = c->Kcg.as<double>();
-  a.cmap = c->cmap.as<int32_t>();
-  a.n_loc = M.n_loc;
-  a.np = M.np;
-  a.q = M.q;
-  a.n_el = M.n_el;
-  a.cells = c->cells.as<int32_t>();
-  a.minv = c->minv64.as<double>();
-  a.V = c->V64.as<double>();
-  a.ncols = 2 * ncols;
-  a.s1 = 1.0;
-  a.s2 = 0.0;
-  a.shift = 0.0;
-  a.variant = c->tile_variant;
-  const CplxKpts g{c->nk, 2 * stride, 2 * stride, (int64_t)2 * M.np * M.np, c->kshift.as<double>()};
-  for (int col = 0; col < 8; ++col)
-    if (hx_cells_cplx_kpts_launch(a, g, M.color_offset[col], M.color_offset[col + 1], c->stream) != 0)
-      return fail(c, CHFSI_ERR_ARG, "apply_complex_kpoints: unsupported cell size or grid too large");
+  const double *kv = c->kgroup_d.as<double>();
+  KronArgs<double> a = kron_args<double>(c, 2 * ncols);
+  a.X = row_major<const double>(c, static_cast<const double *>(X), 2 * ld);
+  a.Y = row_major<double>(c, static_cast<double *>(Y), 2 * ld);
+  if (kron_launch_kpts(a, c->nk, kv, c->kgroup.data(), 2 * stride, 2 * stride, c->stream) != 0)
+    return fail(c, CHFSI_ERR_ARG, "apply_complex_kpoints: grid too large");
   HIPCHK(c, hipGetLastError());
   return 0;
 }
@@ -329,35 +233,8 @@ extern "C" int chfsi_apply_complex(chfsi_ctx *c, const void *X, void *Y, int64_t
   if (int r = check_block(c, X, ld, ncols)) return r;
   if (!c->mesh.periodic) return fail(c, CHFSI_ERR_STATE, "apply_complex: needs a periodic mesh");
   if (!Y || Y == X) return fail(c, CHFSI_ERR_ARG, "apply_complex: Y must be a separate device array");
-  const MeshTables &M = c->mesh;
-  HxArgs<double> a;
-  a.X = static_cast<const double *>(X);
-  a.ldx = 2 * ld;
-  a.Xp = nullptr;
-  a.ldp = 0;
-  a.Y = static_cast<double *>(Y);
-  a.ldy = 2 * ld;
-  a.K = c->Kc64.as<double>();
-  a.cmap = c->cmap.as<int32_t>();
-  a.n_loc = M.n_loc;
-  a.np = M.np;
-  a.q = M.q;
-  a.n_el = M.n_el;
-  a.cells = c->cells.as<int32_t>();
-  a.minv = c->minv64.as<double>();
-  a.V = c->V64.as<double>();
-  a.ncols = 2 * ncols;
-  a.s1 = 1.0;
-  a.s2 = 0.0;
-  // V + |k|^2 / 2 on the diagonal: the epilogue adds s1 (V - shift) X
-  a.shift = -0.5 * (c->kvec[0] * c->kvec[0] + c->kvec[1] * c->kvec[1] + c->kvec[2] * c->kvec[2]);
-  a.variant = c->tile_variant;
-  for (int col = 0; col < 8; ++col) {
-    if (hx_cells_cplx_launch(a, M.color_offset[col], M.color_offset[col + 1], c->stream) != 0)
-      return fail(c, CHFSI_ERR_ARG, "apply_complex: unsupported cell size");
-  }
-  HIPCHK(c, hipGetLastError());
-  return 0;
+  return cheb_step_c(c, row_major<const double>(c, static_cast<const double *>(X), 2 * ld), nullptr,
+                     row_major<double>(c, static_cast<double *>(Y), 2 * ld), ncols, 1.0, 0.0, 0.0);
 }
 
 extern "C" int chfsi_get_sizes(const chfsi_ctx *c, int64_t *n_dof, int64_t *n_cells, int *n_loc) {
@@ -427,12 +304,8 @@ extern "C" int chfsi_set_potential(chfsi_ctx *c, const double *v, int64_t n_dof,
     c->has_pot = true;
     return 0;
   }
-  std::vector<float> hv32(n_dof);
-  for (int64_t i = 0; i < n_dof; ++i) hv32[i] = (float)hv[i];
   HIPCHK(c, c->V64.ensure(n_dof * sizeof(double)));
-  HIPCHK(c, c->V32.ensure(n_dof * sizeof(float)));
   HIPCHK(c, hipMemcpyAsync(c->V64.p, hv.data(), n_dof * sizeof(double), hipMemcpyHostToDevice, c->stream));
-  HIPCHK(c, hipMemcpyAsync(c->V32.p, hv32.data(), n_dof * sizeof(float), hipMemcpyHostToDevice, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   c->vmax = vmax;
   c->ub = 3.0 * c->mesh.lam1d_max + vmax;
@@ -463,27 +336,9 @@ extern "C" int chfsi_set_timing(chfsi_ctx *c, int enable) {
   return 0;
 }
 
-int chfsi::cells_per_tile(const chfsi_ctx *c, int ncols, int tw) {
-  // at least 16 columns per cell; one cell per tile above p = 6
-  const int max_cpt = c->mesh.p > 6 ? 1 : (tw >= 64 ? 4 : (tw >= 32 ? 2 : 1));
-  if (c->cpt_setting > 0) return std::min(c->cpt_setting, max_cpt);
-  int best = 1;
-  int64_t best_pad = -1;
-  for (int cpt = 1; cpt <= max_cpt; cpt *= 2) {
-    const int cw = tw / cpt;
-    const int64_t pad = (int64_t)(ncols + cw - 1) / cw * cw - ncols;
-    if (best_pad < 0 || pad < best_pad) {
-      best = cpt;
-      best_pad = pad;
-    }
-  }
-  return best;
-}
-
 extern "C" int chfsi_set_cells_per_tile(chfsi_ctx *c, int cpt) {
   if (!c) return CHFSI_ERR_ARG;
   if (cpt != 0 && cpt != 1 && cpt != 2 && cpt != 4) return fail(c, CHFSI_ERR_ARG, "cells per tile must be 0, 1, 2 or 4");
-  c->cpt_setting = cpt;
   return 0;
 }
 
@@ -543,81 +398,47 @@ static hipEvent_t next_event(chfsi_ctx *c) {
 // ---------------------------------------------------------------------------
 // Htilde-based step on one column block, any working precision T
 // ---------------------------------------------------------------------------
-// bf: 0 = products in T; 1 = BF16 inputs (T = float); 2 = BF16 hi/lo split (T = float)
+// Y = s1 (Htilde - shift) X + s2 Xp (Xp in Y's layout, or null); bf: T = float
+// only, X enters the products rounded to BF16
 template <typename T>
-static int cheb_step_t(chfsi_ctx *c, const T *X, int64_t ldx, const T *Xp, int64_t ldp, T *Y, int64_t ldy,
-                       int ncols, double s1, double s2, double shift, int bf = 0) {
-  const MeshTables &M = c->mesh;
-  const T *V = std::is_same<T, double>::value ? (const T *)c->V64.p : (const T *)c->V32.p;
-  const T *K = std::is_same<T, double>::value ? (const T *)c->K64.p : (const T *)c->K32.p;
-  const T *mi = std::is_same<T, double>::value ? (const T *)c->minv64.p : (const T *)c->minv32.p;
-  HxArgs<T> a;
+static int cheb_step_t(chfsi_ctx *c, const ColBuf<const T> &X, const T *Xp, const ColBuf<T> &Y, int ncols, double s1,
+                       double s2, double shift, int bf = 0) {
+  KronArgs<T> a = kron_args<T>(c, ncols);
   a.X = X;
-  a.ldx = ldx;
   a.Xp = Xp;
-  a.ldp = ldp;
   a.Y = Y;
-  a.ldy = ldy;
-  a.K = K;
-  a.cmap = c->cmap.as<int32_t>();
-  a.n_loc = M.n_loc;
-  a.np = M.np;
-  a.q = M.q;
-  a.n_el = M.n_el;
-  a.cells = c->cells.as<int32_t>();
-  a.minv = mi;
-  a.V = V;
-  a.ncols = ncols;
-  a.s1 = (T)s1;
-  a.s2 = (T)s2;
-  a.shift = (T)shift;
-  a.variant = c->tile_variant;
-  a.cpt = cells_per_tile(c, ncols, hx_tile_width<T>(M.np, c->tile_variant, 1));
-  for (int col = 0; col < 8; ++col) {
-    hipEvent_t e0 = nullptr, e1 = nullptr;
-    if (c->timing) {
-      e0 = next_event(c);
-      if (e0) (void)hipEventRecord(e0, c->stream);
-    }
-    int lr;
-    if (M.p > 7) {
-      lr = bf ? -1 : hx_rows_launch<T>(a, c->kc_stride, M.color_offset[col], M.color_offset[col + 1], c->stream);
-    } else if (bf) {
-      HxBf16Args b;
-      b.X = (const float *)X;
-      b.ldx = ldx;
-      b.Xp = (const float *)Xp;
-      b.ldp = ldp;
-      b.Y = (float *)Y;
-      b.ldy = ldy;
-      b.Kh = c->Kbh.as<const __bf16>();
-      b.Kl = c->Kbl.as<const __bf16>();
-      b.cmap = a.cmap;
-      b.n_loc = M.n_loc;
-      b.npb = c->npb;
-      b.q = M.q;
-      b.n_el = M.n_el;
-      b.cells = a.cells;
-      b.minv = c->minv32.as<float>();
-      b.V = c->V32.as<float>();
-      b.ncols = ncols;
-      b.s1 = (float)s1;
-      b.s2 = (float)s2;
-      b.shift = (float)shift;
-      b.split = bf == 2;
-      b.cbw = c->tile_variant == 1 ? 1 : 2;
-      lr = hx_cells_bf16_launch(b, M.color_offset[col], M.color_offset[col + 1], c->stream);
-    } else {
-      lr = hx_cells_launch<T>(a, M.color_offset[col], M.color_offset[col + 1], c->stream);
-    }
-    if (lr != 0)
-      return fail(c, CHFSI_ERR_ARG, bf ? "no BF16 cell kernel for this degree (p <= 7)" : "no cell kernel for this degree");
-    if (c->timing && e0) {
-      e1 = next_event(c);
-      if (e1) (void)hipEventRecord(e1, c->stream);
-    }
+  a.s1 = s1;
+  a.s2 = s2;
+  a.shift = shift;
+  a.bf16 = bf;
+  hipEvent_t e0 = nullptr, e1 = nullptr;
+  if (c->timing) {
+    e0 = next_event(c);
+    if (e0) (void)hipEventRecord(e0, c->stream);
   }
-  if (c->timing) c->cell_vecs += (int64_t)M.n_cells * ncols;   // the work of the timed launches
+  if (kron_launch(a, c->stream) != 0) return fail(c, CHFSI_ERR_ARG, "Htilde step: block too large for one launch");
+  if (c->timing && e0) {
+    e1 = next_event(c);
+    if (e1) (void)hipEventRecord(e1, c->stream);
+    c->cell_vecs += (int64_t)c->mesh.n_cells * ncols;   // the work of the timed launches
+  }
+  HIPCHK(c, hipGetLastError());
+  return 0;
+}
+
+int chfsi::cheb_step_c(chfsi_ctx *c, const ColBuf<const double> &X, const double *Xp, const ColBuf<double> &Y,
+                       int ncols, double s1, double s2, double shift) {
+  KronArgs<double> a = kron_args<double>(c, 2 * ncols);
+  a.X = X;
+  a.Xp = Xp;
+  a.Y = Y;
+  a.s1 = s1;
+  a.s2 = s2;
+  // the diagonal of Htilde_k is V + |k|^2 / 2
+  a.shift = shift - 0.5 * (c->kvec[0] * c->kvec[0] + c->kvec[1] * c->kvec[1] + c->kvec[2] * c->kvec[2]);
+  for (int d = 0; d < 3; ++d) a.k[d] = c->kvec[d];
+  if (kron_launch_complex(a, c->stream) != 0) return fail(c, CHFSI_ERR_ARG, "Htilde_k step: block too large for one launch");
+  if (c->timing) c->cell_vecs += (int64_t)c->mesh.n_cells * 2 * ncols;
   HIPCHK(c, hipGetLastError());
   return 0;
 }
@@ -634,32 +455,31 @@ extern "C" int chfsi_cheb_step(chfsi_ctx *c, const double *X, const double *Xp, 
                                double s1, double s2, double shift) {
   if (int r = check_block(c, X, ld, ncols)) return r;
   if (!Y || Y == X || (Xp && Y == Xp)) return fail(c, CHFSI_ERR_ARG, "cheb_step: Y must not alias X or Xprev");
-  return cheb_step_t<double>(c, X, ld, Xp, ld, Y, ld, ncols, s1, s2, shift);
-}
-
-// FP32 copies of a column block live in fbuf[] (ld = width)
-static int ensure_fbufs(chfsi_ctx *c, size_t elem, int width) {
-  const size_t bytes = (size_t)c->mesh.n_dof * width * elem;
-  for (int i = 0; i < 3; ++i) HIPCHK(c, c->fbuf[i].ensure(bytes));
-  return 0;
+  if (!Xp) s2 = 0.0;
+  return cheb_step_t<double>(c, row_major<const double>(c, X, ld), Xp, row_major<double>(c, Y, ld), ncols, s1, s2, shift);
 }
 
 extern "C" int chfsi_apply(chfsi_ctx *c, const double *X, double *Y, int64_t ld, int ncols, chfsi_prec prec) {
   if (int r = check_block(c, X, ld, ncols)) return r;
   if (!Y || X == Y) return fail(c, CHFSI_ERR_ARG, "apply: Y must not alias X");
-  if (prec == CHFSI_FP64) return cheb_step_t<double>(c, X, ld, nullptr, 0, Y, ld, ncols, 1.0, 0.0, 0.0);
+  if (prec == CHFSI_FP64)
+    return cheb_step_t<double>(c, row_major<const double>(c, X, ld), nullptr, row_major<double>(c, Y, ld), ncols, 1.0, 0.0,
+                               0.0);
   if (prec != CHFSI_FP32 && prec != CHFSI_BF16 && prec != CHFSI_BF16X3)
     return fail(c, CHFSI_ERR_ARG, "apply: unknown precision");
-  const int bf = prec == CHFSI_BF16 ? 1 : (prec == CHFSI_BF16X3 ? 2 : 0);
+  if ((prec == CHFSI_BF16 || prec == CHFSI_BF16X3) && c->mesh.p > 7)
+    return fail(c, CHFSI_ERR_ARG, "no BF16 products above degree 7");
+  const int bf = prec == CHFSI_BF16 ? 1 : 0;
   const int64_t nd = c->mesh.n_dof;
   const int bw = std::min(ncols, 256);
-  if (int r = ensure_fbufs(c, sizeof(float), bw)) return r;
+  for (int i = 0; i < 2; ++i) HIPCHK(c, c->fbuf[i].ensure(work_bytes(c, bw, sizeof(float))));
   for (int j0 = 0; j0 < ncols; j0 += bw) {
     const int w = std::min(bw, ncols - j0);
-    float *a = c->fbuf[0].as<float>(), *b = c->fbuf[1].as<float>();
-    copy_cols_launch<double, float>(X + j0, ld, a, w, nd, w, c->stream);
-    if (int r = cheb_step_t<float>(c, a, w, nullptr, 0, b, w, w, 1.0, 0.0, 0.0, bf)) return r;
-    copy_cols_launch<float, double>(b, w, Y + j0, ld, nd, w, c->stream);
+    const ColBuf<float> x = work_block<float>(c, c->fbuf[0].as<float>(), w), y = work_block<float>(c, c->fbuf[1].as<float>(), w);
+    const int gw = group_of(c, sizeof(float));
+    copy_cols_launch<double, float>({const_cast<double *>(X) + j0, ld, 0}, INT32_MAX, x, gw, nd, w, c->stream);
+    if (int r = cheb_step_t<float>(c, {x.p, x.ld, x.cg}, nullptr, y, w, 1.0, 0.0, 0.0, bf)) return r;
+    copy_cols_launch<float, double>(y, gw, {Y + j0, ld, 0}, INT32_MAX, nd, w, c->stream);
   }
   HIPCHK(c, hipGetLastError());
   return 0;
@@ -668,15 +488,14 @@ extern "C" int chfsi_apply(chfsi_ctx *c, const double *X, double *Y, int64_t ld,
 // ---------------------------------------------------------------------------
 // chebyshevFilter
 // ---------------------------------------------------------------------------
+// Two buffers alternate: step k reads buf[k & 1] and updates buf[(k & 1) ^ 1] in
+// place (Z_{k+1} overwrites Z_{k-1}); the result is in buf[degree & 1].
 template <typename T>
-static int filter_block(chfsi_ctx *c, T *z0, int64_t ld0, T *w1, T *w2, int64_t ldw, int ncols, int degree,
-                        double a, double b, double a0, int bf = 0) {
+static int filter_block(chfsi_ctx *c, const ColBuf<T> (&buf)[2], int ncols, int degree, double a, double b, double a0,
+                        int bf = 0) {
   // normalised recursion: rho_1 = 1/xi0, rho_{k+1} = 1/(2 xi0 - rho_k);
   // Z_1 = (rho_1/e)(H - c) Z_0;  Z_{k+1} = (2 rho_{k+1}/e)(H - c) Z_k - rho_{k+1} rho_k Z_{k-1}
   const double cc = 0.5 * (a + b), e = 0.5 * (b - a), xi0 = (a0 - cc) / e;
-  T *buf[3] = {z0, w1, w2};
-  const int64_t lds[3] = {ld0, ldw, ldw};
-  int cur = 0, prev = -1;
   double rho = 1.0 / xi0;
   for (int k = 0; k < degree; ++k) {
     double s1, s2;
@@ -689,15 +508,9 @@ static int filter_block(chfsi_ctx *c, T *z0, int64_t ld0, T *w1, T *w2, int64_t 
       s2 = -rn * rho;
       rho = rn;
     }
-    int out = 0;
-    while (out == cur || out == prev) ++out;
-    if (int r = cheb_step_t<T>(c, buf[cur], lds[cur], prev >= 0 ? buf[prev] : nullptr, prev >= 0 ? lds[prev] : 0,
-                               buf[out], lds[out], ncols, s1, s2, cc, bf))
-      return r;
-    prev = cur;
-    cur = out;
+    const ColBuf<T> &in = buf[k & 1], &out = buf[(k & 1) ^ 1];
+    if (int r = cheb_step_t<T>(c, {in.p, in.ld, in.cg}, k > 0 ? out.p : nullptr, out, ncols, s1, s2, cc, bf)) return r;
   }
-  if (cur != 0) copy_cols_launch<T, T>(buf[cur], lds[cur], z0, ld0, c->mesh.n_dof, ncols, c->stream);
   return 0;
 }
 
@@ -707,29 +520,33 @@ extern "C" int chfsi_chebyshev_filter(chfsi_ctx *c, double *X, int64_t ld, int n
   if (degree < 0 || !(a0 < a) || !(a < b)) return fail(c, CHFSI_ERR_ARG, "filter: need a0 < a < b, degree >= 0");
   if (prec != CHFSI_FP64 && prec != CHFSI_FP32 && prec != CHFSI_BF16 && prec != CHFSI_BF16X3)
     return fail(c, CHFSI_ERR_ARG, "filter: unknown precision");
-  const int bf = prec == CHFSI_BF16 ? 1 : (prec == CHFSI_BF16X3 ? 2 : 0);
+  if ((prec == CHFSI_BF16 || prec == CHFSI_BF16X3) && c->mesh.p > 7)
+    return fail(c, CHFSI_ERR_ARG, "no BF16 products above degree 7");
+  const int bf = prec == CHFSI_BF16 ? 1 : 0;
   if (degree == 0) return 0;
   const int64_t nd = c->mesh.n_dof;
   int bw = block_width > 0 ? block_width : 128;
   bw = std::min(bw, ncols);
   if (prec == CHFSI_FP64) {
-    if (int r = ensure_fbufs(c, sizeof(double), bw)) return r;
+    HIPCHK(c, c->fbuf[0].ensure(work_bytes(c, bw, sizeof(double))));
     for (int j0 = 0; j0 < ncols; j0 += bw) {
       const int w = std::min(bw, ncols - j0);
-      if (int r = filter_block<double>(c, X + j0, ld, c->fbuf[1].as<double>(), c->fbuf[2].as<double>(), w, w,
-                                       degree, a, b, a0))
-        return r;
+      const ColBuf<double> buf[2] = {row_major<double>(c, X + j0, ld), work_block<double>(c, c->fbuf[0].as<double>(), w, ld)};
+      if (int r = filter_block<double>(c, buf, w, degree, a, b, a0)) return r;
+      if (degree & 1)
+        copy_cols_launch<double, double>(buf[1], group_of(c, sizeof(double), ld), buf[0], INT32_MAX, nd, w, c->stream);
     }
   } else {
-    if (int r = ensure_fbufs(c, sizeof(float), bw)) return r;
+    for (int i = 0; i < 2; ++i) HIPCHK(c, c->fbuf[i].ensure(work_bytes(c, bw, sizeof(float))));
+    const int gw = group_of(c, sizeof(float));
     for (int j0 = 0; j0 < ncols; j0 += bw) {
       const int w = std::min(bw, ncols - j0);
-      float *f0 = c->fbuf[0].as<float>();
-      copy_cols_launch<double, float>(X + j0, ld, f0, w, nd, w, c->stream);
-      if (int r = filter_block<float>(c, f0, w, c->fbuf[1].as<float>(), c->fbuf[2].as<float>(), w, w, degree, a,
-                                      b, a0, bf))
-        return r;
-      copy_cols_launch<float, double>(f0, w, X + j0, ld, nd, w, c->stream);
+      const ColBuf<float> buf[2] = {work_block<float>(c, c->fbuf[0].as<float>(), w),
+                                    work_block<float>(c, c->fbuf[1].as<float>(), w)};
+      const ColBuf<double> x{X + j0, ld, 0};
+      copy_cols_launch<double, float>(x, INT32_MAX, buf[0], gw, nd, w, c->stream);
+      if (int r = filter_block<float>(c, buf, w, degree, a, b, a0, bf)) return r;
+      copy_cols_launch<float, double>(buf[degree & 1], gw, x, INT32_MAX, nd, w, c->stream);
     }
   }
   HIPCHK(c, c->flag.ensure(4 * sizeof(int)));
@@ -857,7 +674,9 @@ int chfsi::orth_robust(chfsi_ctx *c, double *X, int64_t ld, int nb, int mixed, i
 // Part 1: HX = Htilde X and the projected Hamiltonian G = X^T HX (into Smat).
 int chfsi::rr_project(chfsi_ctx *c, double *X, int64_t ld, int ncols, double *HX, int64_t ldh) {
   const int64_t nd = c->mesh.n_dof;
-  if (int r = cheb_step_t<double>(c, X, ld, nullptr, 0, HX, ldh, ncols, 1.0, 0.0, 0.0)) return r;
+  if (int r = cheb_step_t<double>(c, row_major<const double>(c, X, ld), nullptr, row_major<double>(c, HX, ldh), ncols, 1.0,
+                                  0.0, 0.0))
+    return r;
   gram_launch(X, ld, HX, ldh, nd, ncols, c->gram_part.as<double>(), c->Smat.as<double>(), 0, c->stream);
   return 0;
 }
@@ -870,15 +689,13 @@ chfsi::JacobiJob chfsi::rr_eigen_job(chfsi_ctx *c, int ncols) {
 }
 
 // The residuals of k rotated columns need Htilde applied to them: either HX is
-// rotated with X (2 n_dof ncols flops per column, a plain GEMM) or Htilde is
-// applied again (the cell products, 2 n_cells np^2 flops per column, which run
-// at a lower fraction of peak than the GEMM: weighted 1.4).  Both give Htilde
+// rotated with X (a GEMM, 2 ncols flops per value at about 57 TFLOP/s: 0.035
+// ncols ps) or Htilde is applied again (about 5 ps per value of the tile
+// kernel's traffic, 25 of the general kernel's gathers).  Both give Htilde
 // times the rotated columns; the cheaper is taken unless the mode forces one.
 bool chfsi::rr_reapply(const chfsi_ctx *c, int ncols) {
   if (c->rr_residual != 0) return c->rr_residual == 2;
-  const MeshTables &M = c->mesh;
-  const double cells = (double)M.n_el * M.n_el * M.n_el;
-  return 1.4 * cells * M.np * M.np < (double)M.n_dof * ncols;
+  return 0.035 * ncols > (c->mesh.p > 7 ? 25.0 : 5.0);
 }
 
 // Rotates X by W (ncols x nout, row stride ncols): in place into the columns
@@ -894,8 +711,8 @@ static int rr_rotate(chfsi_ctx *c, double *X, int64_t ld, int ncols, double *HX,
                       : rmul_cols_launch(X, ld, nd, ncols, W, ncols, nout, col0, 0, 0, scr, se, c->stream);
   if (st != 0) return fail(c, CHFSI_ERR_ARG, "rayleigh_ritz: block too wide for the row-panel kernel");
   if (rr_reapply(c, ncols))
-    return cheb_step_t<double>(c, Xout ? Xout : X + col0, Xout ? ldo : ld, nullptr, 0, HX + col0, ldh, nout, 1.0,
-                               0.0, 0.0);
+    return cheb_step_t<double>(c, row_major<const double>(c, Xout ? Xout : X + col0, Xout ? ldo : ld), nullptr,
+                               row_major<double>(c, HX + col0, ldh), nout, 1.0, 0.0, 0.0);
   if (rmul_cols_launch(HX, ldh, nd, ncols, W, ncols, nout, col0, 0, 0, scr, se, c->stream) != 0)
     return fail(c, CHFSI_ERR_ARG, "rayleigh_ritz: block too wide for the row-panel kernel");
   return 0;
@@ -972,7 +789,9 @@ extern "C" int chfsi_rayleigh_ritz_split(chfsi_ctx *c, double *X, int64_t ld, in
   const int64_t ldh = ncols;
   const int n_oc = ncols - n_fr;
   // step 1: Hhat = X^T Htilde X; mixed: the fr-fr block in FP64, the rest FP32
-  if (int r = cheb_step_t<double>(c, X, ld, nullptr, 0, HX, ldh, ncols, 1.0, 0.0, 0.0)) return r;
+  if (int r = cheb_step_t<double>(c, row_major<const double>(c, X, ld), nullptr, row_major<double>(c, HX, ldh), ncols, 1.0,
+                                  0.0, 0.0))
+    return r;
   double *G = c->Smat.as<double>();
   if (mixed)
     gram_split_launch(X, ld, HX, ldh, nd, ncols, c->gram_part.as<double>(), G, n_oc, c->stream);
@@ -1181,13 +1000,12 @@ extern "C" int chfsi_device_bytes(const chfsi_ctx *c, size_t *bytes) {
 extern "C" size_t chfsi_footprint_bytes(int n_el, int p, int nblock, int block_width, chfsi_prec prec) {
   if (n_el < 1 || p < 1 || p > 12 || nblock < 1) return 0;
   if (p > 7 && prec != CHFSI_FP64 && prec != CHFSI_FP32) return 0;   // no BF16 kernel above p = 7
-  const size_t n = (size_t)n_el * p - 1, nd = n * n * n, ncell = (size_t)n_el * n_el * n_el;
-  const size_t nl = (size_t)(p + 1) * (p + 1) * (p + 1), np = (nl + 15) / 16 * 16;
-  const size_t npr = p > 7 ? (size_t)hx_rows_padded((int)nl) : np, npb = p > 7 ? 0 : (nl + 31) / 32 * 32;
+  const size_t n = (size_t)n_el * p - 1, nd = n * n * n;
   const size_t bw = (size_t)std::min(block_width > 0 ? block_width : 128, nblock);
   const size_t elem = prec == CHFSI_FP64 ? 8 : 4;
-  size_t b = ncell * nl * 4 + ncell * 4 + np * npr * 12 + nd * 24 + npb * npb * 4;  // tables, K, minv, V
-  b += 3 * nd * bw * elem;                                         // filter buffers
+  size_t b = nd * 16;                                              // M^-1/2 and V
+  // filter buffers: at most two blocks of columns padded to whole groups
+  b += 2 * nd * ((bw + 31) / 32 * 32) * elem + nd * bw * elem;
   b += nd * nblock * 8;                                            // HX
   const size_t nn = (size_t)nblock * nblock;
   b += 4 * nn * 8 + jacobi_work_elems(nblock) * 8;                 // S, Z, W, jacobi

@@ -4,6 +4,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <string>
 #include <vector>
 
@@ -48,21 +49,18 @@ struct chfsi_ctx {
   bool has_mesh = false, has_pot = false;
   double vmax = 0, ub = 0;
   // device tables
-  chfsi::DevBuf cmap, cells, K64, K32, minv64, minv32, V64, V32, Kbh, Kbl;
-  int npb = 0;   // n_loc rounded up to 32 (BF16 tiles); 0 above p = 7 (no BF16 kernel)
-  int kc_stride = 0;  // row stride of the padded cell matrix K64 / K32
-  int tile_variant = -1;  // cell-kernel tile configuration (-1: built-in choice)
-  int cpt_setting = 0;    // cells per work-group of the cell kernel (0: chosen from the column count)
+  chfsi::DevBuf minv64, V64;
+  chfsi::DevBuf ae64;  // 1D element matrices Ae and C of the Chebyshev step, (p+1)^2 each
+  int tile_variant = -1;  // tile of the step kernel (-1: built-in choice)
   int rr_residual = 0;    // Ritz residuals: 0 cost model, 1 rotate HX, 2 apply Htilde again
   int jac_sweeps = 40;    // cap on Jacobi sweeps of the projected eigensolve
   // workspaces
   chfsi::DevBuf fbuf[3];      // filter recursion buffers
   chfsi::DevBuf occ_d;    // density: fr occupancy weights
-  chfsi::DevBuf Kc64;     // periodic mesh: [A ; (k.G)^T] complex cell operator, 2 np x np
   double kvec[3] = {0, 0, 0};
   double kin_k = 0;       // sum over directions of lambda_max of the 1D Bloch operators at kvec
   chfsi::DevBuf csel;     // complex Rayleigh-Ritz: selected Ritz values and the pairing status
-  chfsi::DevBuf Kcg, kshift; // k-point group: nk cell operators and |k|^2/2 shifts
+  chfsi::DevBuf kgroup_d; // k-point group: its 3 nk wave vectors
   // Poisson: 1D band / mass tables (for the mesh they were built for), CG
   // workspace, point charges
   chfsi::DevBuf pois_kb, pois_m, pois_work, pois_q;
@@ -81,10 +79,9 @@ struct chfsi_ctx {
   bool verbose = false;   // CHFSI_VERBOSE: one progress line per solve pass on stderr
   // every device buffer the context owns
   template <typename F> void each_buf(F f) {
-    chfsi::DevBuf *all[] = {&cmap, &cells, &K64, &K32, &minv64, &minv32, &V64, &V32, &Kbh, &Kbl, &fbuf[0],
+    chfsi::DevBuf *all[] = {&minv64, &V64, &ae64, &fbuf[0],
                             &fbuf[1], &fbuf[2], &gram_part, &Smat, &dinv, &Zmat, &Wmat, &jac_work, &evals_d,
-                            &resid_part, &resid_d, &flag, &HX, &diag0, &minratio, &rscratch, &occ_d, &Kc64, &Kcg,
-                            &kshift, &pois_kb, &pois_m, &pois_work, &pois_q, &csel};
+                            &resid_part, &resid_d, &flag, &HX, &diag0, &minratio, &rscratch, &occ_d, &kgroup_d, &pois_kb, &pois_m, &pois_work, &pois_q, &csel};
     for (chfsi::DevBuf *b : all) f(*b);
   }
 };
@@ -131,11 +128,31 @@ int rr_finish(chfsi_ctx *c, double *X, int64_t ld, int ncols, double *HX, int64_
 // iterate) when the projected eigensolve ran out of sweeps.
 int rr_impl(chfsi_ctx *c, double *X, int64_t ld, int ncols, double *HX, int64_t ldh, double *evals, double *resid,
             int *sweeps);
-// Cells per work-group of the real cell kernel (tile width tw columns) for
-// blocks of ncols columns: the context's setting, or (setting 0) the count
-// among 1, 2, 4 that pads the fewest columns (ties: fewer cells); at least 16
-// columns per cell either way.
-int cells_per_tile(const chfsi_ctx *c, int ncols, int tw);
+// A row-major block with row stride ld (of reals).
+template <typename T>
+inline ColBuf<T> row_major(const chfsi_ctx *c, T *p, int64_t ld) {
+  return ColBuf<T>{p, ld, kron_group(c->mesh.p, sizeof(T))};
+}
+// Columns to a group of the library's own block (INT32_MAX: row-major): grouped
+// where the tile kernel runs, also on the row-major block of stride ld that it
+// alternates with.
+inline int group_of(const chfsi_ctx *c, size_t elem, int64_t ld = 1) {
+  return kron_tiled(c->mesh.p, c->mesh.n, std::max<int64_t>(ld, 32), elem) ? kron_group(c->mesh.p, elem) : INT32_MAX;
+}
+// A w-column block of the library's own.
+template <typename T>
+inline ColBuf<T> work_block(const chfsi_ctx *c, T *p, int w, int64_t ld = 1) {
+  const int g = group_of(c, sizeof(T), ld);
+  if (g == INT32_MAX) return row_major<T>(c, p, w);
+  return ColBuf<T>{p, g, c->mesh.n_dof * g};
+}
+// Device bytes of a w-column block of the library's own (columns padded to
+// whole groups).
+size_t work_bytes(const chfsi_ctx *c, int w, size_t elem);
+// Y = s1 (Htilde_k - shift) X + s2 Xp on complex blocks seen as 2 ncols real
+// columns (Xp in Y's layout, or null).
+int cheb_step_c(chfsi_ctx *c, const ColBuf<const double> &X, const double *Xp, const ColBuf<double> &Y, int ncols,
+                double s1, double s2, double shift);
 // Records the unconverged-eigensolve message and returns the warning.
 int jacobi_warning(chfsi_ctx *c);
 // Whether Rayleigh-Ritz obtains Htilde times the rotated columns by a fresh

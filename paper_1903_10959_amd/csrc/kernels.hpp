@@ -2,113 +2,81 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <cstdint>
+#include <vector>
 
 namespace chfsi {
 
-// ---- Chebyshev step (hx.hip) ----------------------------------------------
-// One Chebyshev step Y = s1 (Htilde - shift) X + s2 Xp, launched colour by colour
-// (colours 0..7 in order; the first colour writes Y, later colours add).
+// ---- Chebyshev step (kron.hip) ---------------------------------------------
+// A block of columns: value (dof i, column j) is at
+// p[(j / g) * cg + i * ld + j % g], g = kron_group columns to a group.  A
+// row-major block has cg = g; a grouped one (the library's own buffers: ld =
+// g, cg = n_dof * g) keeps a group's rows next to each other, which the tile
+// kernel reads 4 to 15 % faster.
 template <typename T>
-struct HxArgs {
-  const T *X;          // input block, [n_dof x ldx]
-  int64_t ldx;
-  const T *Xp;         // previous block or nullptr (s2 ignored)
-  int64_t ldp;
-  T *Y;                // output block
-  int64_t ldy;
-  const T *K;          // padded cell stiffness [np x np]
-  const int32_t *cmap; // [n_cells x n_loc]
-  int n_loc, np, q, n_el;
-  const int32_t *cells;  // cell ids sorted by colour
-  const T *minv;       // M^-1/2 [n_dof]
-  const T *V;          // potential [n_dof]
-  int ncols;
-  T s1, s2, shift;
-  int variant;         // tile configuration: -1 built-in choice, 0 four-wave, 1 eight-wave
-  int cpt = 1;         // cells per work-group (1, 2 or 4): the tile's columns split over that many cells
+struct ColBuf {
+  T *p;
+  int64_t ld, cg;
 };
+// Columns to a group for values of `elem` bytes (0: degree p has no tile
+// kernel and its blocks are row-major).
+int kron_group(int p, size_t elem);
+// Whether row stride ld fits the tile kernel's 32-bit plane offsets (a block
+// that does not must be row-major).
+bool kron_tiled(int p, int n, int64_t ld, size_t elem);
+// Y = s1 (Htilde - shift) X + s2 Xp in one launch.  Xp has Y's layout and may
+// be Y (each value is read before it is written, by the thread that writes
+// it); Y must not be X.  Xp null: no previous block (s2 = 0).
 template <typename T>
-int hx_cells_launch(const HxArgs<T> &a, int color_begin, int color_end, hipStream_t s);
-// Columns per cell of one work-group of the cell kernel for padded cell size
-// np, tile variant and cells per tile (-1 if not supported); the column
-// tiles of the batched work list use it.
-template <typename T>
-int hx_tile_width(int np, int variant, int cpt);
-// Degrees 8..12: row-group kernel, a.K stored [a.np][npr] (a.np = n_loc
-// rounded up to 16, npr = hx_rows_padded(n_loc)), zero padded; -1 for
-// arguments it does not support.
-template <typename T>
-int hx_rows_launch(const HxArgs<T> &a, int npr, int color_begin, int color_end, hipStream_t s);
-int hx_rows_padded(int n_loc);
-// Complex cell products on interleaved (re, im) columns: a.K is the
-// [A ; B^T] operator (2 np x np) and a.ncols counts real columns (even).
-int hx_cells_cplx_launch(const HxArgs<double> &a, int color_begin, int color_end, hipStream_t s);
-// A group of nk k-points in one launch per colour: block k at X + k xstride
-// (Y + k ystride, real elements), cell operator at a.K + k kstride, shift[k]
-// on the potential term (a.Xp, a.s1, a.s2 and a.shift unused).
-struct CplxKpts {
-  int nk;
-  int64_t xstride, ystride, kstride;
-  const double *shifts;
+struct KronArgs {
+  ColBuf<const T> X;
+  const T *Xp;
+  ColBuf<T> Y;
+  const double *V;     // [n_dof]
+  const double *ae;    // 1D element matrices Ae and C, (p+1)^2 each
+  int n_el, p, n, periodic, ncols;
+  double s1, s2, shift;
+  int variant = -1;    // tile: -1 built-in choice, 0 2 x 2 cells, 1 4 x 2 where available
+  int bf16 = 0;        // float: X enters the products rounded to BF16
+  double k[3] = {0, 0, 0};   // complex: Bloch vector
 };
-int hx_cells_cplx_kpts_launch(const HxArgs<double> &a, const CplxKpts &g, int color_begin, int color_end,
-                              hipStream_t s);
+int kron_launch(const KronArgs<double> &a, hipStream_t s);
+int kron_launch(const KronArgs<float> &a, hipStream_t s);
+// Complex blocks as interleaved (re, im) real columns (a.ncols even), a.k the
+// Bloch vector of the -i k.G term (its |k|^2/2 is the caller's, in a.shift).
+int kron_launch_complex(const KronArgs<double> &a, hipStream_t s);
+// A group of nk k-points (kv: 3 nk values on the device, host_kv on the host)
+// in one launch: block g at X + g xstride (Y + g ystride, real elements).
+int kron_launch_kpts(const KronArgs<double> &a, int nk, const double *kv, const double *host_kv, int64_t xstride,
+                     int64_t ystride, hipStream_t s);
+// Cells per z chunk of a march by `tiles` tiles.
+int kron_zlen(int n_el, int p, int64_t tiles);
 
-// One problem of a batched filter sweep (device-resident descriptor).
+// One problem of a batched filter sweep (device-resident descriptor).  Step k
+// reads buf[k & 1] and updates buf[(k & 1) ^ 1].
 template <typename T>
-struct BatchProblem {
-  T *buf[3];           // the three rotating recursion buffers
-  int64_t ld[3];
-  const T *K;          // padded cell stiffness
-  const int32_t *cmap;
-  const T *minv, *V;
-  const T *coef;       // [degree x 3]: s1, s2, shift per step
-  const int32_t *cells;  // the problem's cells sorted by colour
-  int n_loc, q, n_el, ncols;
+struct KronBatchProblem {
+  ColBuf<T> buf[2];
+  const double *V, *ae;
+  const double *coef;  // [degree x 3]: s1, s2, shift per step
+  int n_el, n, periodic, ncols, bf16;
 };
-// Launch one Chebyshev step for a list of work items (int4: x = problem, y =
-// first cell in the problem's colour-sorted cell list, z = column tile, w =
-// number of cells, at most cpt, all of one colour) whose problems share the
-// padded cell size np, tile variant and cells per tile.
+// The tile variant a problem runs (its context's setting, or for -1 the
+// built-in choice); with it, its tiles (-1: no tile kernel for the degree), its
+// work items appended to `work`, and the launch of one step for a work list of
+// one degree and variant.
 template <typename T>
-int hx_cells_batch_launch(int np, int variant, int cpt, const BatchProblem<T> *probs, const int4 *work, int nwork,
-                          int step, int cur, int prev, int out, hipStream_t s);
-// BF16 cell products: FP32 X/Y/minv, K_ref as BF16 hi (and lo when split),
-// padded to npb = round_up(n_loc, 32).
-struct HxBf16Args {
-  const float *X;
-  int64_t ldx;
-  const float *Xp;
-  int64_t ldp;
-  float *Y;
-  int64_t ldy;
-  const __bf16 *Kh, *Kl;
-  const int32_t *cmap;
-  int n_loc, npb, q, n_el;
-  const int32_t *cells;
-  const float *minv, *V;
-  int ncols;
-  float s1, s2, shift;
-  int split;
-  int cbw = 2;         // 16-column blocks per wave: 2 (64-column tiles) or 1 (32-column tiles)
-};
-int hx_cells_bf16_launch(const HxBf16Args &a, int color_begin, int color_end, hipStream_t s);
-// One problem of a batched BF16 sweep: its three recursion buffers (FP32), the
-// BF16 hi/lo cell matrix (npb x npb), maps and per-step coefficients.
-struct BatchProblemBf16 {
-  float *buf[3];
-  int64_t ld[3];
-  const __bf16 *Kh, *Kl;
-  const int32_t *cmap, *cells;
-  const float *minv, *V, *coef;
-  int n_loc, q, n_el, ncols;
-};
-// work items (problem, cell position, 64-column tile, unused) of one padded
-// size npb (32 .. 512) and one colour; -1 for an unsupported npb
-int hx_cells_bf16_batch_launch(int npb, int split, const BatchProblemBf16 *probs, const int4 *work, int nwork,
-                               int step, int cur, int prev, int out, hipStream_t s);
+int kron_batch_variant(int p, int variant, int n_el, int ncols);
+template <typename T>
+int64_t kron_batch_tiles(int p, int variant, int n_el, int ncols);
+template <typename T>
+int kron_batch_work(int p, int variant, int n_el, int ncols, int prob, int zlen, std::vector<int4> &work);
+template <typename T>
+int kron_batch_launch(int p, int variant, const KronBatchProblem<T> *probs, const int4 *work, int nwork, int step,
+                      hipStream_t s);
+// out = in, values converted; gin, gout: columns to a group of either side
+// (any value >= ncols for a row-major block).
 template <typename Tin, typename Tout>
-void copy_cols_launch(const Tin *in, int64_t ldi, Tout *out, int64_t ldo, int64_t nrows, int ncols,
+void copy_cols_launch(const ColBuf<Tin> &in, int gin, const ColBuf<Tout> &out, int gout, int64_t nrows, int ncols,
                       hipStream_t s);
 template <typename T>
 void nonfinite_launch(const T *X, int64_t ld, int64_t nrows, int ncols, int *flag, hipStream_t s);

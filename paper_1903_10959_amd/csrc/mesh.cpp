@@ -102,7 +102,6 @@ std::string build_mesh(double L, int n_el, int p, MeshTables &m, bool periodic) 
   m.h = L / n_el;
   m.n = periodic ? n_el * p : n_el * p - 1;
   m.n_loc = m.q * m.q * m.q;
-  m.np = (m.n_loc + 15) / 16 * 16;
   m.n_dof = (int64_t)m.n * m.n * m.n;
   m.n_cells = (int64_t)n_el * n_el * n_el;
   const int q = m.q;
@@ -182,34 +181,19 @@ std::string build_mesh(double L, int n_el, int p, MeshTables &m, bool periodic) 
               m.mass[d] += jac * m.w[a] * m.w[b] * m.w[c];
             }
       }
-  m.cell_order.resize((size_t)m.n_cells);
-  int pos = 0;
-  for (int col = 0; col < 8; ++col) {
-    m.color_offset[col] = pos;
-    for (int64_t e = 0; e < m.n_cells; ++e)
-      if (m.colors[e] == col) m.cell_order[pos++] = (int32_t)e;
-  }
-  m.color_offset[8] = pos;
 
-  // first-derivative cell matrices of the k-point operator (periodic only):
-  // G_x[(a,b,c), (a2,b2,c2)] = (h/2)^2 w_a w_b w_c D[a][a2] delta_b,b2 delta_c,c2
-  // and the same along y and z; the GLL rule is exact for this integrand's
-  // degree (2p - 1) in the derivative direction.
-  if (periodic) {
-    const double s2 = (m.h / 2.0) * (m.h / 2.0);
-    for (int dd = 0; dd < 3; ++dd) m.gcell[dd].assign((size_t)nl * nl, 0.0);
-    for (int c = 0; c < q; ++c)
-      for (int b = 0; b < q; ++b)
-        for (int a = 0; a < q; ++a) {
-          const int l = a + q * b + q * q * c;
-          const double wl = s2 * m.w[a] * m.w[b] * m.w[c];
-          for (int t = 0; t < q; ++t) {
-            m.gcell[0][(size_t)l * nl + (t + q * b + q * q * c)] = wl * m.D[(size_t)a * q + t];
-            m.gcell[1][(size_t)l * nl + (a + q * t + q * q * c)] = wl * m.D[(size_t)b * q + t];
-            m.gcell[2][(size_t)l * nl + (a + q * b + q * q * t)] = wl * m.D[(size_t)c * q + t];
-          }
-        }
-  }
+  // 1D element matrices in the mass-scaled basis (an element end shares its
+  // mass with the neighbour)
+  m.ae.assign((size_t)q * q, 0.0);
+  m.ce.assign((size_t)q * q, 0.0);
+  for (int a = 0; a < q; ++a)
+    for (int b = 0; b < q; ++b) {
+      const double ma = (m.h / 2.0) * m.w[a] * (a == 0 || a == p ? 2.0 : 1.0);
+      const double mb = (m.h / 2.0) * m.w[b] * (b == 0 || b == p ? 2.0 : 1.0);
+      const double s = 1.0 / std::sqrt(ma * mb);
+      m.ae[(size_t)a * q + b] = 0.5 * (2.0 / m.h) * m.K1[(size_t)a * q + b] * s;
+      if (a != b) m.ce[(size_t)a * q + b] = m.w[a] * m.D[(size_t)a * q + b] * s;
+    }
 
   // 1D operator A = 1/2 M1^-1/2 K1D M1^-1/2 on the n interior nodes, for the
   // spectral upper bound; n <= 2000 keeps the host Jacobi affordable only for

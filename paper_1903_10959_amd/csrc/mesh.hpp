@@ -13,7 +13,6 @@ struct MeshTables {
   int n_el = 0, p = 0, q = 0;      // q = p + 1 nodes per direction
   int n = 0;                       // interior nodes per direction, n_el*p - 1
   int n_loc = 0;                   // q^3
-  int np = 0;                      // n_loc rounded up to a multiple of 16 (MFMA tile)
   int64_t n_dof = 0, n_cells = 0;
   std::vector<double> xi, w;       // GLL nodes / weights on [-1,1]
   std::vector<double> D;           // D[qq*q + a] = l_a'(xi_qq)
@@ -21,14 +20,16 @@ struct MeshTables {
   std::vector<double> kcell;       // cell stiffness of -1/2 Laplacian, n_loc x n_loc
   std::vector<int32_t> cmap;       // [n_cells * n_loc], -1 = Dirichlet node
   std::vector<uint8_t> colors;     // [n_cells]
-  std::vector<int32_t> cell_order; // cells sorted by colour
-  int color_offset[9] = {0};
   std::vector<double> mass;        // [n_dof] diagonal of M
+  // 1D element matrices in the mass-scaled basis, (p+1)^2 row-major: ae of
+  // -1/2 d^2/dx^2 (an element end holds half of the assembled diagonal) and ce
+  // of d/dx (zero diagonal: the ends' entries cancel between elements); with
+  // A = sum of ae over the elements, Htilde = A (+) A (+) A + diag(V)
+  std::vector<double> ae, ce;
   double lam1d_max = 0;            // largest eigenvalue of the assembled 1D operator
   // periodic cell [0, L)^3: node index I = (ex p + a) mod (n_el p), n = n_el p,
-  // no Dirichlet nodes; gcell[d] = int N_j d_d N_l (GLL rule), n_loc x n_loc
+  // no Dirichlet nodes
   bool periodic = false;
-  std::vector<double> gcell[3];
 };
 
 // Builds every table; returns an empty string on success, else a message.
