@@ -195,26 +195,103 @@ __global__ __launch_bounds__(256) void gram_kernel(const double *__restrict__ A,
       }
 }
 
-// G[i, j] = sum over splits of the partial tiles, for i >= j in the region
-// [r0, n) x [r0, n) (tiles numbered within the sub-triangle from tile row tf),
-// mirrored to the upper triangle.  skip0 >= 0: leave out the entries with both
-// i and j >= skip0 (written by another reduction).
+// n <= 64: one 64 x 64 tile, so the 128-tile kernel would leave three of its
+// four waves idle.  Here the waves of a work-group share its rows instead,
+// each takes every fourth group of four rows straight from memory into MFMA
+// fragments (NA = ceil(n / 16) of them per operand, lower tiles only), and
+// the four partial tiles are added in LDS in wave order.  13,824 and
+// 24,389 rows of 32 columns: 6 us against 54.
+template <int NA, bool SAME>
+__global__ __launch_bounds__(256) void gram_small_kernel(const double *__restrict__ A, int64_t lda,
+                                                         const double *__restrict__ B, int64_t ldb, int64_t nrows,
+                                                         int n, int64_t rows_per_split, double *__restrict__ part) {
+  constexpr int UN = 4;                              // row groups in flight
+  __shared__ double red[16 * NA][16 * NA + 1];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int j = lane & 15, kq = lane >> 4;
+  const int64_t r0 = (int64_t)blockIdx.x * rows_per_split;
+  const int64_t r1 = r0 + rows_per_split < nrows ? r0 + rows_per_split : nrows;
+  v4d acc[NA][NA];
+#pragma unroll
+  for (int a = 0; a < NA; ++a)
+#pragma unroll
+    for (int b = 0; b <= a; ++b) acc[a][b] = v4d{0, 0, 0, 0};
+  for (int64_t r = r0 + 4 * wave; r < r1; r += 16 * UN) {
+    double av[UN][NA], bv[UN][NA];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const int64_t row = r + 16 * u + kq;
+#pragma unroll
+      for (int a = 0; a < NA; ++a) {
+        const bool ok = row < r1 && 16 * a + j < n;
+        av[u][a] = ok ? A[row * lda + 16 * a + j] : 0.0;
+        if (!SAME) bv[u][a] = ok ? B[row * ldb + 16 * a + j] : 0.0;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < UN; ++u)
+#pragma unroll
+      for (int a = 0; a < NA; ++a)
+#pragma unroll
+        for (int b = 0; b <= a; ++b) acc[a][b] = mfma16x4(av[u][a], SAME ? av[u][b] : bv[u][b], acc[a][b]);
+  }
+  for (int w = 0; w < 4; ++w) {
+    if (wave == w) {
+#pragma unroll
+      for (int a = 0; a < NA; ++a)
+#pragma unroll
+        for (int b = 0; b <= a; ++b)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            double &d = red[16 * a + acc_row<double>(kq, q)][16 * b + j];
+            d = w == 0 ? acc[a][b][q] : d + acc[a][b][q];
+          }
+    }
+    __syncthreads();
+  }
+  double *out = part + (int64_t)blockIdx.x * (64 * 64);
+  for (int e = threadIdx.x; e < 16 * NA * 16 * NA; e += 256) {
+    const int i = e / (16 * NA), k = e % (16 * NA);
+    if (k / 16 <= i / 16) out[i * 64 + k] = red[i][k];
+  }
+}
+
+// G[i, j] = sum over splits of the partial gt x gt tiles, for i >= j in the
+// region [r0, n) x [r0, n) (tiles numbered within the sub-triangle from tile
+// row tf), mirrored to the upper triangle.  skip0 >= 0: leave out the entries
+// with both i and j >= skip0 (written by another reduction).  A work-group
+// adds 32 entries, each by eight threads that take every eighth split and are
+// then added in order: one thread per entry left the chip waiting on the
+// serial chain over the splits (6 tiles x 341 splits: 487 us; this: 38).
 __global__ __launch_bounds__(256) void gram_reduce_kernel(const double *__restrict__ part, int nsplit, int ntl,
-                                                          int n, int tf, int r0, int skip0,
+                                                          int gt, int n, int tf, int r0, int skip0,
                                                           double *__restrict__ G) {
+  __shared__ double red[8][33];
   const int m = n - r0;
   const int64_t total = (int64_t)m * m;
-  for (int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; idx < total;
-       idx += (int64_t)gridDim.x * blockDim.x) {
+  const int e = threadIdx.x & 31, sl = threadIdx.x >> 5;
+  for (int64_t base = blockIdx.x * (int64_t)32; base < total; base += (int64_t)gridDim.x * 32) {
+    const int64_t idx = base + e;
     const int i = r0 + (int)(idx / m), jj = r0 + (int)(idx - idx / m * m);
-    if (jj > i || (skip0 >= 0 && jj >= skip0)) continue;
-    const int ti = i / GT - tf, tj = jj / GT - tf;
-    const int t = ti * (ti + 1) / 2 + tj;
-    const double *p = part + (int64_t)t * (GT * GT) + (i % GT) * GT + (jj % GT);
+    const bool on = idx < total && jj <= i && !(skip0 >= 0 && jj >= skip0);
     double s = 0;
-    for (int sp = 0; sp < nsplit; ++sp) s += p[(int64_t)sp * ntl * (GT * GT)];
-    G[(int64_t)i * n + jj] = s;
-    G[(int64_t)jj * n + i] = s;
+    if (on) {
+      const int ti = i / gt - tf, tj = jj / gt - tf;
+      const int t = ti * (ti + 1) / 2 + tj;
+      const double *p = part + (int64_t)t * (gt * gt) + (i % gt) * gt + (jj % gt);
+      const int64_t st = (int64_t)ntl * (gt * gt);
+#pragma unroll 4
+      for (int sp = sl; sp < nsplit; sp += 8) s += p[sp * st];
+    }
+    red[sl][e] = s;
+    __syncthreads();
+    if (sl == 0 && on) {
+#pragma unroll
+      for (int k = 1; k < 8; ++k) s += red[k][e];
+      G[(int64_t)i * n + jj] = s;
+      G[(int64_t)jj * n + i] = s;
+    }
+    __syncthreads();
   }
 }
 
@@ -233,7 +310,10 @@ static int gram_nsplit_tiles(int64_t nrows, int ntl, int slots) {
   return (int)want;
 }
 
-static int gram_slots() { return resident_slots(gram_kernel<2, 0>); }
+static int gram_slots() {
+  static const int slots = resident_slots(gram_kernel<2, 0>);   // of the kernel on this GPU family: looked up once
+  return slots;
+}
 
 int gram_nsplit(int64_t nrows, int n) { return gram_nsplit_tiles(nrows, gram_ntiles(n), gram_slots()); }
 
@@ -257,13 +337,37 @@ static int64_t gram_rows_per_split(int64_t nrows, int nsplit) {
 }
 
 static void gram_reduce(const double *part, int nsplit, int ntl, int n, int tf, int r0, int skip0, double *G,
-                        hipStream_t s) {
+                        hipStream_t s, int gt = GT) {
   const int64_t m = n - r0;
-  int64_t blocks = (m * m + 255) / 256;
-  if (blocks > 16384) blocks = 16384;
+  int64_t blocks = (m * m + 31) / 32;
+  if (blocks > 65536) blocks = 65536;
   if (blocks < 1) return;
-  hipLaunchKernelGGL(gram_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, s, part, nsplit, ntl, n, tf, r0,
+  hipLaunchKernelGGL(gram_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, s, part, nsplit, ntl, gt, n, tf, r0,
                      skip0, G);
+}
+
+// n <= 64 (mixed or not: the 64-wide diagonal block is FP64 either way).
+// Splits of at least 128 rows, at most one per CU: never more than the partial
+// tiles of the 128-tile kernel take.
+static void gram_small(const double *A, int64_t lda, const double *B, int64_t ldb, int64_t nrows, int n, double *part,
+                       size_t max_split, double *G, hipStream_t s) {
+  int64_t nsplit = (nrows + 127) / 128;
+  if (nsplit > 256) nsplit = 256;
+  if (max_split > 0 && nsplit > (int64_t)max_split) nsplit = (int64_t)max_split;
+  const int64_t rps = gram_rows_per_split(nrows, (int)nsplit);
+  nsplit = (nrows + rps - 1) / rps;
+  const dim3 g((unsigned)nsplit), b(256);
+  const bool same = A == B && lda == ldb;
+#define GRAM_SMALL(NA)                                                                                             \
+  case NA:                                                                                                         \
+    if (same) hipLaunchKernelGGL((gram_small_kernel<NA, true>), g, b, 0, s, A, lda, B, ldb, nrows, n, rps, part);  \
+    else hipLaunchKernelGGL((gram_small_kernel<NA, false>), g, b, 0, s, A, lda, B, ldb, nrows, n, rps, part);      \
+    break;
+  switch ((n + 15) / 16) {
+    GRAM_SMALL(1) GRAM_SMALL(2) GRAM_SMALL(3) GRAM_SMALL(4)
+  }
+#undef GRAM_SMALL
+  gram_reduce(part, (int)nsplit, 1, n, 0, 0, -1, G, s, 64);
 }
 
 static bool gram_v16(const double *A, int64_t lda, const double *B, int64_t ldb, int n) {
@@ -289,6 +393,11 @@ void gram_launch(const double *A, int64_t lda, const double *B, int64_t ldb, int
 
 int gram_launch_capped(const double *A, int64_t lda, const double *B, int64_t ldb, int64_t nrows, int n,
                        double *part, size_t part_elems, double *G, int mixed, hipStream_t s) {
+  if (n <= 64 && nrows > 0) {
+    if (part_elems > 0 && part_elems < 64 * 64) return -1;
+    gram_small(A, lda, B, ldb, nrows, n, part, part_elems / (64 * 64), G, s);
+    return 0;
+  }
   const int ntiles = gram_ntiles(n);
   int nsplit = gram_nsplit_tiles(nrows, ntiles, gram_slots());
   if (part_elems > 0) {
@@ -652,34 +761,54 @@ void density_launch(const double *X, int64_t ld, int ncols, const double *Xfr, i
 // ---------------------------------------------------------------------------
 // Residual column norms
 // ---------------------------------------------------------------------------
+// Work-group = a chunk of rows x CW columns, 256 / CW threads to a column, four
+// rows in flight each, added in LDS in order.  Partial sums are stored column
+// by column, part[c * nchunk + chunk], so that one wave adds a column's with
+// coalesced loads.  (One thread per column and 1024 rows each took 304 us for
+// 32 columns of some 20,000 rows, where eight threads now share a column: 7 us;
+// 283 columns of 493,039 rows 1,020 against 571 us, memory-bound now.)
+template <int CW>
 __global__ __launch_bounds__(256) void resid_part_kernel(const double *__restrict__ X, int64_t ldx,
                                                          const double *__restrict__ HX, int64_t ldh,
                                                          const double *__restrict__ lam, int64_t nrows, int n,
-                                                         int64_t rows_per, double *__restrict__ part) {
+                                                         int64_t rows_per, int nchunk, double *__restrict__ part) {
+  constexpr int RL = 256 / CW;
+  __shared__ double red[256];
+  const int cl = threadIdx.x % CW, rl = threadIdx.x / CW;
+  const int c = blockIdx.y * CW + cl;
   const int64_t r0 = (int64_t)blockIdx.x * rows_per;
-  int64_t r1 = r0 + rows_per;
-  if (r1 > nrows) r1 = nrows;
-  for (int c = threadIdx.x; c < n; c += blockDim.x) {
+  const int64_t r1 = r0 + rows_per < nrows ? r0 + rows_per : nrows;
+  double acc = 0;
+  if (c < n) {
     const double l = lam[c];
-    double acc = 0;
-    for (int64_t r = r0; r < r1; ++r) {
-      double d = HX[r * ldh + c] - l * X[r * ldx + c];
+#pragma unroll 4
+    for (int64_t r = r0 + rl; r < r1; r += RL) {
+      const double d = HX[r * ldh + c] - l * X[r * ldx + c];
       acc += d * d;
     }
-    part[(int64_t)blockIdx.x * n + c] = acc;
+  }
+  red[threadIdx.x] = acc;
+  __syncthreads();
+  if (rl == 0 && c < n) {
+#pragma unroll
+    for (int k = 1; k < RL; ++k) acc += red[k * CW + cl];
+    part[(int64_t)c * nchunk + blockIdx.x] = acc;
   }
 }
 
-__global__ void resid_reduce_kernel(const double *__restrict__ part, int nchunk, int n, double *__restrict__ out) {
-  int c = blockIdx.x * blockDim.x + threadIdx.x;
+// one wave per column
+__global__ __launch_bounds__(256) void resid_reduce_kernel(const double *__restrict__ part, int nchunk, int n,
+                                                           double *__restrict__ out) {
+  const int c = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (c >= n) return;
   double s = 0;
-  for (int k = 0; k < nchunk; ++k) s += part[(int64_t)k * n + c];
-  out[c] = sqrt(s);
+  for (int k = lane; k < nchunk; k += 64) s += part[(int64_t)c * nchunk + k];
+  s = wave_sum(s);
+  if (lane == 0) out[c] = sqrt(s);
 }
 
 int resid_nchunk(int64_t nrows) {
-  int64_t c = (nrows + 1023) / 1024;
+  int64_t c = (nrows + 255) / 256;
   if (c > 2048) c = 2048;
   if (c < 1) c = 1;
   return (int)c;
@@ -687,11 +816,15 @@ int resid_nchunk(int64_t nrows) {
 
 void resid_launch(const double *X, int64_t ldx, const double *HX, int64_t ldh, const double *lam, int64_t nrows,
                   int n, double *part, double *resid, hipStream_t s) {
-  int nchunk = resid_nchunk(nrows);
-  int64_t rows_per = (nrows + nchunk - 1) / nchunk;
-  hipLaunchKernelGGL(resid_part_kernel, dim3(nchunk), dim3(256), 0, s, X, ldx, HX, ldh, lam, nrows, n, rows_per,
-                     part);
-  hipLaunchKernelGGL(resid_reduce_kernel, dim3((n + 255) / 256), dim3(256), 0, s, part, nchunk, n, resid);
+  const int nchunk = resid_nchunk(nrows);
+  const int64_t rows_per = (nrows + nchunk - 1) / nchunk;
+  if (n <= 32)
+    hipLaunchKernelGGL((resid_part_kernel<32>), dim3(nchunk), dim3(256), 0, s, X, ldx, HX, ldh, lam, nrows, n, rows_per,
+                       nchunk, part);
+  else
+    hipLaunchKernelGGL((resid_part_kernel<64>), dim3(nchunk, (n + 63) / 64), dim3(256), 0, s, X, ldx, HX, ldh, lam, nrows,
+                       n, rows_per, nchunk, part);
+  hipLaunchKernelGGL(resid_reduce_kernel, dim3((n + 3) / 4), dim3(256), 0, s, part, nchunk, n, resid);
 }
 
 }  // namespace chfsi

@@ -1,0 +1,60 @@
+"""The dense FP64 kernels at the edges of their tiles and row splits, in blocks
+whose rows lie odd distances apart: Gram matrices of up to 64 columns (fragments
+of 16) and just beyond, Cholesky blocks of 32, Jacobi pairs of 64, residuals in
+groups of 32 and 64 columns, on meshes with fewer rows than one split, and a
+row more than a whole number of them."""
+import numpy as np
+import pytest
+
+from gpu_util import make_ctx, oracle_apply, to_gpu, to_host
+
+pytestmark = pytest.mark.gpu
+
+COLS = [1, 15, 16, 17, 31, 32, 33, 48, 49, 63, 64, 65]
+
+
+@pytest.mark.parametrize("n_el,p", [(1, 5), (2, 4), (5, 4)])    # 64, 343 and 6,859 rows
+@pytest.mark.parametrize("ncols", COLS)
+def test_orthonormalize_and_ritz_at_tile_edges(n_el, p, ncols):
+    """CholGS against Householder QR (its error is kappa^2 times the roundoff of
+    sums of products), then the Ritz pairs of the result against numpy: values
+    within the projection's roundoff, residuals of the vectors returned."""
+    L = 2.0 * n_el
+    nd = (n_el * p - 1) ** 3
+    if ncols > nd:
+        pytest.skip("more columns than rows")
+    V = np.random.default_rng(p).uniform(-3, 1, nd)
+    c, _ = make_ctx(L, n_el, p, V=V)
+    X = np.random.default_rng(ncols).standard_normal((nd, ncols))
+    if ncols == nd:                                  # square: keep the condition number bounded
+        X = np.linalg.qr(X)[0] + 0.1 * X / np.sqrt(nd)
+    kappa = np.linalg.cond(X)
+    Xg = to_gpu(X, ncols + 3)
+    c.orthonormalize(Xg)
+    Q, R = np.linalg.qr(X)
+    Q = Q * np.sign(np.diag(R))[None, :]
+    assert np.max(np.abs(to_host(Xg) - Q)) < 1e-13 * kappa ** 2
+    H = oracle_apply(L, n_el, p, V)
+    D = np.linalg.eigvalsh(Q.T @ H(Q))
+    ev, rs = c.rayleigh_ritz(Xg)
+    scale = c.upper_bound                            # the operator's norm
+    assert np.max(np.abs(ev - D)) < 1e-13 * scale * kappa ** 2
+    Y = to_host(Xg)
+    res = np.linalg.norm(H(Y) - Y * ev[None, :], axis=0)
+    assert np.max(np.abs(rs - res)) < 1e-13 * scale * np.sqrt(ncols)
+    assert np.max(np.abs(Y.T @ Y - np.eye(ncols))) < 1e-13 * kappa ** 2
+    c.close()
+
+
+@pytest.mark.parametrize("ncols,bad", [(1, 0), (33, 0), (33, 31), (33, 32), (65, 40), (64, 63)])
+def test_zero_column_anywhere_in_a_block_is_refused(ncols, bad):
+    import paper_1903_10959_amd as P
+    c, _ = make_ctx(4.0, 2, 4, V=np.zeros(343))
+    X = np.random.default_rng(3).standard_normal((343, ncols))
+    X[:, bad] = 0.0
+    Xg = to_gpu(X, ncols + 1)
+    with pytest.raises(P.ChfsiError) as ei:
+        c.orthonormalize(Xg)
+    assert ei.value.status == -5
+    np.testing.assert_array_equal(to_host(Xg), X)
+    c.close()
