@@ -27,6 +27,14 @@ static constexpr int NB = 32;
 // Relative pivot below which the overlap counts as numerically singular.
 static constexpr double PIVOT_FLOOR = 1e-14;
 
+// 1 / sqrt(x) to about an ulp (x normal and positive): the hardware estimate
+// (about 24 bits) and one third-order step.
+__device__ __forceinline__ double rsqrt_full(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = __builtin_fma(-x * y, y, 1.0);
+  return __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
+}
+
 // Before the factorisation: diag0 = diag(S) (after an optional shift of
 // shift_rel * max diag(S) added to the diagonal, the shifted Cholesky remedy).
 __global__ __launch_bounds__(1024) void potrf_prep_kernel(double *S, int n, double shift_rel, double *diag0) {
@@ -47,61 +55,79 @@ __global__ __launch_bounds__(1024) void potrf_prep_kernel(double *S, int n, doub
   }
 }
 
-// Factor one 32x32 diagonal block in LDS.  Pivot j is accepted when
+// Factor one 32x32 diagonal block.  Pivot j is accepted when
 // d_j > PIVOT_FLOOR * diag0_j; minratio[block] = min_j d_j / diag0_j
 // (d_j / S_jj is the squared sine of the angle between column j and the span
 // of the columns before it, the loss-of-orthogonality indicator).
-__global__ __launch_bounds__(256) void potrf_diag_kernel(double *S, int n, int k0, double *dinv, int *flag,
-                                                         const double *diag0, double *minratio) {
-  __shared__ double a[NB][NB + 1];
-  __shared__ double z[NB][NB + 1];
+// One wave, no barriers: lane i holds row i of the trailing block in registers,
+// its first column always in a[0]: a pivot's update moves every entry one
+// register down, so that the loop over the pivots is one short body (unrolled
+// it is 100 KB of code, fetched for one use).  The finished columns go through
+// LDS, from where the update and the inverse (lane c: column c, shifted the
+// same way) read them as broadcasts.  The chain of 32 pivots bounds it, so
+// a pivot is one reciprocal square root and no division: 38 us per block with
+// 256 threads, three barriers, a root and a division per pivot; 27 us so.
+__device__ __forceinline__ double lane_of(double x, int l) {
+  const long long b = __builtin_bit_cast(long long, x);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)b, l);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(b >> 32), l);
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+__global__ __launch_bounds__(64) void potrf_diag_kernel(double *S, int n, int k0, double *dinv, int *flag,
+                                                        const double *diag0, double *minratio) {
+  __shared__ double L[NB][2 * NB];                   // L[c][r]: column c of the factor; r >= NB stays zero
+  __shared__ double ri[NB];                          // 1 / L[c][c]
   const int kw = min(NB, n - k0);
-  const int tid = threadIdx.x;
-  for (int idx = tid; idx < NB * NB; idx += blockDim.x) {
-    int i = idx / NB, jj = idx % NB;
-    a[i][jj] = (i < kw && jj < kw && jj <= i) ? S[(int64_t)(k0 + i) * n + k0 + jj] : 0.0;
-    z[i][jj] = 0.0;
+  const int lane = threadIdx.x, i = lane & (NB - 1); // the upper half repeats the lower
+  for (int e = lane; e < NB * 2 * NB; e += 64) (&L[0][0])[e] = 0.0;
+  double a[NB];
+#pragma unroll
+  for (int c = 0; c < NB; ++c) {
+    const bool in = i < kw && c <= i;                // padding rows: the identity
+    const double v = S[(int64_t)(k0 + (in ? i : 0)) * n + k0 + (in ? c : 0)];
+    a[c] = in ? v : (i == c ? 1.0 : 0.0);
   }
-  __syncthreads();
-  double rmin = 1.0;
-  for (int jj = 0; jj < kw; ++jj) {
-    double d = a[jj][jj];
-    __syncthreads();
-    const double ref = diag0[k0 + jj];
-    const double ratio = ref > 0.0 ? d / ref : -1.0;
-    rmin = fmin(rmin, ratio);
-    double ljj = sqrt(d);
-    if (!(ratio > PIVOT_FLOOR) || !(ljj - ljj == 0.0)) {
-      if (tid == 0 && *flag == 0) *flag = k0 + jj + 1;
-      ljj = __builtin_nan("");
-    }
-    if (tid == 0) a[jj][jj] = ljj;
-    for (int i = jj + 1 + tid; i < kw; i += blockDim.x) a[i][jj] /= ljj;
-    __syncthreads();
-    const int m = kw - jj - 1;  // trailing size
-    for (int idx = tid; idx < m * m; idx += blockDim.x) {
-      int i = jj + 1 + idx / m, k = jj + 1 + idx % m;
-      if (k <= i) a[i][k] -= a[i][jj] * a[k][jj];
-    }
-    __syncthreads();
+  const double ref_i = i < kw ? diag0[k0 + i] : 1.0;
+  double d_i = 1.0;                                  // pivot i
+#pragma unroll 1
+  for (int jj = 0; jj < NB; ++jj) {
+    const double d = lane_of(a[0], jj), ref = lane_of(ref_i, jj);
+    double inv = rsqrt_full(d);
+    if (!(d > PIVOT_FLOOR * ref) || !(ref > 0.0) || !(inv - inv == 0.0)) inv = __builtin_nan("");
+    if (i == jj) d_i = d;
+    const double l = i < jj ? 0.0 : i == jj ? d * inv : a[0] * inv;
+    if (lane < NB) L[jj][i] = l;
+    if (lane == 0) ri[jj] = inv;
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int c = 0; c + 1 < NB; ++c) a[c] = __builtin_fma(-l, L[jj][jj + 1 + c], a[c + 1]);
+    a[NB - 1] = 0.0;
   }
-  if (tid == 0) minratio[k0 / NB] = rmin;
-  // inverse of the lower-triangular diagonal block, one column per thread
-  if (tid < kw) {
-    const int c = tid;
-    z[c][c] = 1.0 / a[c][c];
-    for (int i = c + 1; i < kw; ++i) {
-      double s = 0;
-      for (int m = c; m < i; ++m) s += a[i][m] * z[m][c];
-      z[i][c] = -s / a[i][i];
-    }
+  // the ratios, all pivots at once; the first failing one is reported
+  double ratio = i < kw ? (ref_i > 0.0 ? d_i / ref_i : -1.0) : 1.0;
+  const bool fails = i < kw && !(L[i][i] - L[i][i] == 0.0);
+  const unsigned bad = (unsigned)__ballot(fails);
+#pragma unroll
+  for (int o = 16; o > 0; o >>= 1) ratio = fmin(ratio, __shfl_xor(ratio, o, 64));
+  if (lane == 0) {
+    if (bad && *flag == 0) *flag = k0 + __ffs((int)bad);
+    minratio[k0 / NB] = fmin(1.0, ratio);
   }
-  __syncthreads();
+  for (int e = lane; e < NB * NB; e += 64) {
+    const int r = e / NB, c = e % NB;
+    if (r < kw && c <= r) S[(int64_t)(k0 + r) * n + k0 + c] = L[c][r];
+  }
+  // inverse: column i of it solves L z = e_i
+#pragma unroll
+  for (int r = 0; r < NB; ++r) a[r] = r == i ? 1.0 : 0.0;
   double *dz = dinv + (int64_t)(k0 / NB) * NB * NB;
-  for (int idx = tid; idx < NB * NB; idx += blockDim.x) {
-    int i = idx / NB, jj = idx % NB;
-    if (i < kw && jj < kw && jj <= i) S[(int64_t)(k0 + i) * n + k0 + jj] = a[i][jj];
-    dz[idx] = (i < kw && jj < kw) ? z[i][jj] : 0.0;
+#pragma unroll 1
+  for (int r = 0; r < NB; ++r) {
+    const double z = a[0] * ri[r];
+    if (lane < NB) dz[r * NB + i] = (r < kw && i <= r) ? z : 0.0;
+#pragma unroll
+    for (int q = 0; q + 1 < NB; ++q) a[q] = __builtin_fma(-L[r][r + 1 + q], z, a[q + 1]);
+    a[NB - 1] = 0.0;
   }
 }
 
@@ -164,7 +190,7 @@ void potrf_launch(double *S, int n, double *dinv, int *flag, double *diag0, doub
                   hipStream_t s) {
   hipLaunchKernelGGL(potrf_prep_kernel, dim3(1), dim3(1024), 0, s, S, n, shift_rel, diag0);
   for (int k0 = 0; k0 < n; k0 += NB) {
-    hipLaunchKernelGGL(potrf_diag_kernel, dim3(1), dim3(256), 0, s, S, n, k0, dinv, flag, diag0, minratio);
+    hipLaunchKernelGGL(potrf_diag_kernel, dim3(1), dim3(64), 0, s, S, n, k0, dinv, flag, diag0, minratio);
     const int k1 = k0 + NB;
     if (k1 >= n) break;
     const int rest = n - k1;
@@ -266,21 +292,6 @@ __device__ __forceinline__ int rr_index(int pos, int r, int np) {
   return pos == 0 ? 0 : 1 + (pos - 1 + r) % (np - 1);
 }
 
-// Rotation (c, s) that zeroes A_pq: J = [[c, s], [-s, c]] on the (p, q) plane.
-__device__ __forceinline__ void jrot(const double *A, int n, int p, int q, double &c, double &s, double &t) {
-  c = 1.0;
-  s = 0.0;
-  t = 0.0;
-  if (p >= n || q >= n) return;
-  const double apq = A[(int64_t)p * n + q];
-  if (fabs(apq) < 1e-300) return;
-  const double app = A[(int64_t)p * n + p], aqq = A[(int64_t)q * n + q];
-  const double tau = (aqq - app) / (2.0 * apq);
-  t = (tau >= 0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-  c = 1.0 / sqrt(1.0 + t * t);
-  s = t * c;
-}
-
 // Block-cyclic Jacobi.  The indices are grouped in blocks of JB = 32; a
 // block round pairs the blocks in round-robin order (as the scalar method
 // pairs indices), and for every pair (I, J) of blocks
@@ -311,12 +322,12 @@ struct JacProb {
   int64_t first_inner, first_tile, first_panel;
 };
 
-__device__ __forceinline__ int jac_find(const JacProb *__restrict__ probs, int nprob, int which) {
+__device__ __forceinline__ int jac_find(const JacProb *__restrict__ probs, int nprob, int which, int idx) {
   int lo = 0, hi = nprob - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
     const int64_t f = which == 0 ? probs[mid].first_inner : which == 1 ? probs[mid].first_tile : probs[mid].first_panel;
-    if (f <= (int64_t)blockIdx.x) lo = mid;
+    if (f <= (int64_t)idx) lo = mid;
     else hi = mid - 1;
   }
   return lo;
@@ -338,95 +349,156 @@ __device__ __forceinline__ void jac_pair(int t, int ir, bool within, int &p, int
   }
 }
 
+// Rotation (c, s), t = s / c, that zeroes apq, |angle| <= 45 degrees.  With
+// d = aqq - app, h = 2 apq, r = sqrt(d^2 + h^2): c^2 = (1 + |d|/r) / 2, s =
+// |h| / (2 r c), signs those of d/h (+ for d = 0).  Two reciprocal square roots
+// on one chain instead of two divisions and two roots; d and h are scaled by a
+// power of two so that the squares neither over- nor underflow.
+__device__ __forceinline__ void jac_angle(double app, double aqq, double apq, double &c, double &s, double &t) {
+  c = 1.0;
+  s = 0.0;
+  t = 0.0;
+  double d = aqq - app, h = 2.0 * apq;
+  const bool neg = d != 0.0 && ((d < 0.0) != (h < 0.0));
+  d = fabs(d);
+  h = fabs(h);
+  const int e = __builtin_amdgcn_frexp_exp(fmax(d, h));
+  d = ldexp(d, -e);
+  h = ldexp(h, -e);
+  const double y = rsqrt_full(__builtin_fma(d, d, h * h));
+  const double u = __builtin_fma(0.5 * d, y, 0.5);
+  const double yc = rsqrt_full(u);
+  const double sa = 0.5 * h * y * yc, ta = sa * yc;
+  if (fabs(apq) >= 1e-300) {
+    c = u * yc;
+    s = neg ? -sa : sa;
+    t = neg ? -ta : ta;
+  }
+}
+
 // 1. one sweep of the 64-index pair submatrix in LDS; R out
 // g: block round of the sweep (0: pairs inside the blocks, pairing 0;
 // g >= 1: pairs across the blocks, pairing g - 1).
-__global__ __launch_bounds__(1024) void jacobi_inner_kernel(const JacProb *__restrict__ probs, int nprob, int g) {
+// Four waves rotate S: thread (a0, b) = (t / 32, t % 32) updates the 2 x 2
+// blocks (pair a0 + 8 k rows, pair b columns).  Each of them computes all 32
+// rotations for itself (lane b: pair b), so that a round has one barrier after
+// its reads and one after its writes and no rotation waits for another wave.
+// Four more waves accumulate R, one round behind, off that chain.  A round is
+// bound by its chain of latencies: 47 us per 32 rounds with sixteen waves that
+// wait for one wave's rotations (two divisions, two roots); across two blocks
+// 28-31 us so, inside them (33 rounds over 64 indices) 42 us.
+template <bool within>
+__global__ __launch_bounds__(512) void jacobi_inner_kernel(const JacProb *__restrict__ probs, int nprob, int g) {
   __shared__ double S[J2][J2 + 1];
-  __shared__ double Rs[J2][J2 + 1];
-  __shared__ double cs[J2 / 2], sn[J2 / 2], tn[J2 / 2];
-  const JacProb &P = probs[jac_find(probs, nprob, 0)];
+  __shared__ double Rs[within ? J2 : 1][J2 + 1];
+  __shared__ double cs[4][J2 / 2], sn[4][J2 / 2];    // a wave's own rotations
+  __shared__ double cr[2][J2 / 2], sr[2][J2 / 2];    // ... of a round, for R
+  const JacProb &P = probs[jac_find(probs, nprob, 0, blockIdx.x)];
   if (g >= P.nbp) return;                          // this problem's sweep is complete
-  const int r = g == 0 ? 0 : g - 1;
-  const bool within = g == 0;
+  const int r = within ? 0 : g - 1;                // (within: g = 0)
   const int k = (int)(blockIdx.x - P.first_inner);
   const int n = P.n;
   const int I = rr_index(k, r, P.nbp), J = rr_index(P.nbp - 1 - k, r, P.nbp);
   const double *A = P.A[(P.par0 + g) & 1];
-  const int t = threadIdx.x;
-  for (int e = t; e < J2 * J2; e += 1024) {
-    const int i = e / J2, j = e % J2;
-    const int gi = jac_gidx(i, I, J), gj = jac_gidx(j, I, J);
-    S[i][j] = (gi < n && gj < n) ? A[(int64_t)gi * n + gj] : 0.0;
-    Rs[i][j] = i == j ? 1.0 : 0.0;
+  {
+    double v[8];
+    const int j = threadIdx.x % J2, i0 = threadIdx.x / J2, gj = jac_gidx(j, I, J);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int gi = jac_gidx(i0 + 8 * q, I, J);
+      v[q] = (gi < n && gj < n) ? A[(int64_t)gi * n + gj] : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      S[i0 + 8 * q][j] = v[q];
+      if (within) Rs[i0 + 8 * q][j] = i0 + 8 * q == j ? 1.0 : 0.0;
+    }
   }
   __syncthreads();
   const int nround = within ? JB - 1 : JB;
-  // Across the blocks pair b is (b, JB + (b + ir) % JB): column b of R stays
-  // with the threads of pair b, and the second column passes each round to
-  // the lane of pair b - 1 in the same 32-lane half.  So R lives in
-  // registers there (rows 2 a, 2 a + 1 of both columns), with one lane shift
-  // per round; inside the blocks the pairing has no such shape and R stays
-  // in LDS.
-  const int a = t / (J2 / 2), b = t % (J2 / 2);
-  const int src = (t & 32) | ((b + 1) & 31);         // lane holding pair b + 1
-  double rP[2], rQ[2];
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    rP[h] = 2 * a + h == b ? 1.0 : 0.0;
-    rQ[h] = 2 * a + h == JB + b ? 1.0 : 0.0;
-  }
-  for (int ir = 0; ir < nround; ++ir) {
-    if (t < J2 / 2) {
-      int p, q;
-      jac_pair(t, ir, within, p, q);
-      double c = 1.0, s = 0.0, tt = 0.0;
-      const double apq = S[p][q];
-      if (fabs(apq) >= 1e-300) {
-        const double tau = (S[q][q] - S[p][p]) / (2.0 * apq);
-        tt = (tau >= 0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-        c = 1.0 / sqrt(1.0 + tt * tt);
-        s = tt * c;
+  const bool on_s = threadIdx.x < 256;
+  const int t = threadIdx.x & 255;
+  const int w = t >> 6, a0 = t / (J2 / 2), b = t % (J2 / 2);
+  double *Rg = P.R + (int64_t)k * J2 * J2;
+  if (on_s) {
+#pragma unroll 1
+    for (int ir = 0; ir <= nround; ++ir) {
+      if (ir == nround) {                            // (R's last round)
+        __syncthreads();
+        __syncthreads();
+        break;
       }
-      cs[t] = c;
-      sn[t] = s;
-      tn[t] = tt;
-    }
-    __syncthreads();
-    {
-      // 2x2 block (pair a rows, pair b columns), one per thread, in place
-      int pa, qa, pb, qb;
-      jac_pair(a, ir, within, pa, qa);
+      int pb, qb, pa[4], qa[4];
       jac_pair(b, ir, within, pb, qb);
-      if (a == b) {
-        const double apq = S[pa][qa];
-        S[pa][pa] -= tn[a] * apq;
-        S[qa][qa] += tn[a] * apq;
-        S[pa][qa] = 0.0;
-        S[qa][pa] = 0.0;
-      } else {
-        const double ca = cs[a], sa = sn[a], cb = cs[b], sb = sn[b];
-        const double b00 = S[pa][pb], b01 = S[pa][qb], b10 = S[qa][pb], b11 = S[qa][qb];
-        const double r00 = ca * b00 - sa * b10, r01 = ca * b01 - sa * b11;
-        const double r10 = sa * b00 + ca * b10, r11 = sa * b01 + ca * b11;
-        S[pa][pb] = cb * r00 - sb * r01;
-        S[pa][qb] = sb * r00 + cb * r01;
-        S[qa][pb] = cb * r10 - sb * r11;
-        S[qa][qb] = sb * r10 + cb * r11;
-      }
-      // R <- R J: rows 2 per thread, pair b
-      if (within) {
+      const double app = S[pb][pb], aqq = S[qb][qb], apq = S[pb][qb];
+      double b00[4], b01[4], b10[4], b11[4];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int row = 2 * a + h;
+      for (int u = 0; u < 4; ++u) {
+        jac_pair(a0 + 8 * u, ir, within, pa[u], qa[u]);
+        b00[u] = S[pa[u]][pb];
+        b01[u] = S[pa[u]][qb];
+        b10[u] = S[qa[u]][pb];
+        b11[u] = S[qa[u]][qb];
+      }
+      __syncthreads();                               // every wave has read the pairs' entries
+      double cb, sb, tb;
+      jac_angle(app, aqq, apq, cb, sb, tb);
+      if ((t & 32) == 0) {
+        cs[w][b] = cb;
+        sn[w][b] = sb;
+        if (w == 0) {
+          cr[ir & 1][b] = cb;
+          sr[ir & 1][b] = sb;
+        }
+      }
+      __builtin_amdgcn_wave_barrier();               // (cs, sn are read back by this wave only)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int a = a0 + 8 * u;
+        const double ca = cs[w][a], sa = sn[w][a];
+        const double r00 = ca * b00[u] - sa * b10[u], r01 = ca * b01[u] - sa * b11[u];
+        const double r10 = sa * b00[u] + ca * b10[u], r11 = sa * b01[u] + ca * b11[u];
+        const bool dia = a == b;
+        S[pa[u]][pb] = dia ? b00[u] - tb * apq : cb * r00 - sb * r01;
+        S[pa[u]][qb] = dia ? 0.0 : sb * r00 + cb * r01;
+        S[qa[u]][pb] = dia ? 0.0 : cb * r10 - sb * r11;
+        S[qa[u]][qb] = dia ? b11[u] + tb * apq : sb * r10 + cb * r11;
+      }
+      __syncthreads();
+    }
+    return;
+  }
+  // R <- R J, rows a0 + 8 h of pair b.  Across the blocks pair b is
+  // (b, JB + (b + ir) % JB): column b of R stays with the threads of pair b,
+  // and the second column passes each round to the lane of pair b - 1 in the
+  // same 32-lane half.  So R lives in registers there, with one lane shift per
+  // round; inside the blocks the pairing has no such shape and R stays in LDS
+  // (each thread's entries are its own within a round).
+  const int src = (t & 32) | ((b + 1) & 31);         // lane holding pair b + 1
+  double rP[8], rQ[8];
+#pragma unroll
+  for (int h = 0; h < 8; ++h) {
+    rP[h] = a0 + 8 * h == b ? 1.0 : 0.0;
+    rQ[h] = a0 + 8 * h == JB + b ? 1.0 : 0.0;
+  }
+#pragma unroll 1
+  for (int ir = 0; ir <= nround; ++ir) {
+    __syncthreads();
+    if (ir > 0) {
+      const double cb = cr[(ir - 1) & 1][b], sb = sr[(ir - 1) & 1][b];
+      if (within) {
+        int pb, qb;
+        jac_pair(b, ir - 1, within, pb, qb);
+#pragma unroll
+        for (int h = 0; h < 8; ++h) {
+          const int row = a0 + 8 * h;
           const double rp = Rs[row][pb], rq = Rs[row][qb];
-          Rs[row][pb] = cs[b] * rp - sn[b] * rq;
-          Rs[row][qb] = sn[b] * rp + cs[b] * rq;
+          Rs[row][pb] = cb * rp - sb * rq;
+          Rs[row][qb] = sb * rp + cb * rq;
         }
       } else {
-        const double cb = cs[b], sb = sn[b];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
+        for (int h = 0; h < 8; ++h) {
           const double rp = rP[h], rq = rQ[h];
           rP[h] = cb * rp - sb * rq;
           rQ[h] = sb * rp + cb * rq;
@@ -436,16 +508,15 @@ __global__ __launch_bounds__(1024) void jacobi_inner_kernel(const JacProb *__res
     }
     __syncthreads();
   }
-  double *Rg = P.R + (int64_t)k * J2 * J2;
   if (within) {
-    for (int e = t; e < J2 * J2; e += 1024) Rg[e] = Rs[e / J2][e % J2];
+    for (int e = t; e < J2 * J2; e += 256) Rg[e] = Rs[e / J2][e % J2];
   } else {
     // after the shift of the last round this thread holds column JB + (b + nround) % JB
     const int qcol = JB + (b + nround) % JB;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      Rg[(2 * a + h) * J2 + b] = rP[h];
-      Rg[(2 * a + h) * J2 + qcol] = rQ[h];
+    for (int h = 0; h < 8; ++h) {
+      Rg[(a0 + 8 * h) * J2 + b] = rP[h];
+      Rg[(a0 + 8 * h) * J2 + qcol] = rQ[h];
     }
   }
 }
@@ -471,15 +542,23 @@ __device__ __forceinline__ void jac_mm64(const double (*X)[J2 + 1], const double
 
 // 2. A_next[P1 rows, P2 cols] = R_P1^T A[P1, P2] R_P2 for every pair of pairs
 //    k1 <= k2, with the mirror tile A_next[P2, P1] its transpose
-__global__ __launch_bounds__(256) void jacobi_apply_a_kernel(const JacProb *__restrict__ probs, int nprob, int g) {
-  __shared__ double T[J2][J2 + 1], R1[J2][J2 + 1], R2[J2][J2 + 1];
-  const JacProb &P = probs[jac_find(probs, nprob, 1)];
-  if (g >= P.nbp) return;
+// Tiles are loaded whole into registers before the first LDS store (one
+// latency instead of sixteen), and the eigenvectors' rotation shares the
+// launch: n = 360 takes 12 us where two kernels took 22 + 14.
+typedef double (*jac_mat)[J2 + 1];
+__device__ __forceinline__ void jac_load_r(const double *__restrict__ Rg, double (&v)[16], int t) {
+#pragma unroll
+  for (int q = 0; q < 16; ++q) v[q] = Rg[t + 256 * q];
+}
+__device__ __forceinline__ void jac_put(jac_mat M, const double (&v)[16], int t) {
+#pragma unroll
+  for (int q = 0; q < 16; ++q) M[t / J2 + 4 * q][t % J2] = v[q];
+}
+__device__ __forceinline__ void jacobi_apply_a(const JacProb &P, int tile, int g, jac_mat T, jac_mat R1, jac_mat R2) {
   const int r = g == 0 ? 0 : g - 1;
   // A is symmetric, so the tile of pairs (k2, k1) is the transpose of that of
   // (k1, k2): only k1 <= k2 are computed, each written with its mirror
   // (tile = k2 (k2 + 1) / 2 + k1)
-  const int tile = (int)(blockIdx.x - P.first_tile);
   int k2 = (int)((sqrtf(8.0f * tile + 1.0f) - 1.0f) * 0.5f);
   while (k2 * (k2 + 1) / 2 > tile) --k2;
   while ((k2 + 1) * (k2 + 2) / 2 <= tile) ++k2;
@@ -489,14 +568,20 @@ __global__ __launch_bounds__(256) void jacobi_apply_a_kernel(const JacProb *__re
   const int I2 = rr_index(k2, r, P.nbp), J2b = rr_index(P.nbp - 1 - k2, r, P.nbp);
   const double *A = P.A[(P.par0 + g) & 1];
   double *An = P.A[(P.par0 + g + 1) & 1];
-  const double *Rg1 = P.R + (int64_t)k1 * J2 * J2, *Rg2 = P.R + (int64_t)k2 * J2 * J2;
   const int t = threadIdx.x;
-  for (int e = t; e < J2 * J2; e += 256) {
-    const int i = e / J2, j = e % J2;
-    const int gi = jac_gidx(i, I1, J1), gj = jac_gidx(j, I2, J2b);
-    T[i][j] = (gi < n && gj < n) ? A[(int64_t)gi * n + gj] : 0.0;
-    R1[i][j] = Rg1[e];
-    R2[i][j] = Rg2[e];
+  {
+    double v[16], v1[16], v2[16];
+    const int gj = jac_gidx(t % J2, I2, J2b);
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const int gi = jac_gidx(t / J2 + 4 * q, I1, J1);
+      v[q] = (gi < n && gj < n) ? A[(int64_t)gi * n + gj] : 0.0;
+    }
+    jac_load_r(P.R + (int64_t)k1 * J2 * J2, v1, t);
+    jac_load_r(P.R + (int64_t)k2 * J2 * J2, v2, t);
+    jac_put(T, v, t);
+    jac_put(R1, v1, t);
+    jac_put(R2, v2, t);
   }
   __syncthreads();
   const int wv = t >> 6, lane = t & 63, jl = lane & 15, kq = lane >> 4;
@@ -528,24 +613,25 @@ __global__ __launch_bounds__(256) void jacobi_apply_a_kernel(const JacProb *__re
 }
 
 // 3. V[panel rows, P cols] <- V[panel rows, P cols] R_P, in place
-__global__ __launch_bounds__(256) void jacobi_apply_v_kernel(const JacProb *__restrict__ probs, int nprob, int g) {
-  __shared__ double T[J2][J2 + 1], Rl[J2][J2 + 1];
-  const JacProb &P = probs[jac_find(probs, nprob, 2)];
-  if (g >= P.nbp) return;
+__device__ __forceinline__ void jacobi_apply_v(const JacProb &P, int w, int g, jac_mat T, jac_mat Rl) {
   const int r = g == 0 ? 0 : g - 1;
   const int np2 = P.nbp / 2;
-  const int w = (int)(blockIdx.x - P.first_panel);
   const int panel = w / np2, k = w % np2;
   const int n = P.n;
   const int I = rr_index(k, r, P.nbp), J = rr_index(P.nbp - 1 - k, r, P.nbp);
-  const double *Rg = P.R + (int64_t)k * J2 * J2;
   const int t = threadIdx.x;
   const int row0 = panel * J2;
-  for (int e = t; e < J2 * J2; e += 256) {
-    const int i = e / J2, j = e % J2;
-    const int gr = row0 + i, gj = jac_gidx(j, I, J);
-    T[i][j] = (gr < n && gj < n) ? P.V[(int64_t)gr * n + gj] : 0.0;
-    Rl[i][j] = Rg[e];
+  {
+    double v[16], vr[16];
+    const int gj = jac_gidx(t % J2, I, J);
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const int gr = row0 + t / J2 + 4 * q;
+      v[q] = (gr < n && gj < n) ? P.V[(int64_t)gr * n + gj] : 0.0;
+    }
+    jac_load_r(P.R + (int64_t)k * J2 * J2, vr, t);
+    jac_put(T, v, t);
+    jac_put(Rl, vr, t);
   }
   __syncthreads();
   const int wv = t >> 6, lane = t & 63, jl = lane & 15, kq = lane >> 4;
@@ -558,6 +644,19 @@ __global__ __launch_bounds__(256) void jacobi_apply_v_kernel(const JacProb *__re
       const int gr = row0 + 16 * wv + acc_row<double>(kq, q), gj = jac_gidx(16 * b + jl, I, J);
       if (gr < n && gj < n) P.V[(int64_t)gr * n + gj] = c[b][q];
     }
+}
+
+// Steps 2 and 3 do not depend on each other: one launch, the first n_tile
+// work-groups update A, the others V.
+__global__ __launch_bounds__(256) void jacobi_apply_kernel(const JacProb *__restrict__ probs, int nprob, int g,
+                                                           int n_tile) {
+  __shared__ double T[J2][J2 + 1], R1[J2][J2 + 1], R2[J2][J2 + 1];
+  const bool on_a = (int)blockIdx.x < n_tile;
+  const int idx = on_a ? (int)blockIdx.x : (int)blockIdx.x - n_tile;
+  const JacProb &P = probs[jac_find(probs, nprob, on_a ? 1 : 2, idx)];
+  if (g >= P.nbp) return;
+  if (on_a) jacobi_apply_a(P, idx - (int)P.first_tile, g, T, R1, R2);
+  else jacobi_apply_v(P, idx - (int)P.first_panel, g, T, R1);
 }
 
 // Squared off-diagonal and diagonal Frobenius norms of each problem's A, as
@@ -602,19 +701,30 @@ __global__ __launch_bounds__(256) void eye_kernel(double *V, int n) {
     V[idx] = (idx / n == idx % n) ? 1.0 : 0.0;
 }
 
-// evals ascending; Q[:, rank(i)] = V[:, i]; ties broken by index
+// evals ascending; Q[:, rank(i)] = V[:, i]; ties broken by index.  Work-group =
+// 256 columns x SORT_ROWS rows; each ranks its columns itself (the diagonal
+// through LDS, 256 values at a time).
+static constexpr int SORT_ROWS = 32;
 __global__ __launch_bounds__(256) void jacobi_sort_kernel(const double *A, const double *V, int n, double *evals,
                                                           double *Q) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const double di = A[(int64_t)i * n + i];
+  __shared__ double d[256];
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  const double di = i < n ? A[(int64_t)i * n + i] : 0.0;
   int rank = 0;
-  for (int k = 0; k < n; ++k) {
-    double dk = A[(int64_t)k * n + k];
-    if (dk < di || (dk == di && k < i)) ++rank;
+  for (int k0 = 0; k0 < n; k0 += 256) {
+    __syncthreads();
+    const int kk = k0 + threadIdx.x;
+    if (kk < n) d[threadIdx.x] = A[(int64_t)kk * n + kk];
+    __syncthreads();
+    const int m = n - k0 < 256 ? n - k0 : 256;
+    for (int k = 0; k < m; ++k)
+      if (d[k] < di || (d[k] == di && k0 + k < i)) ++rank;
   }
-  evals[rank] = di;
-  for (int row = 0; row < n; ++row) Q[(int64_t)row * n + rank] = V[(int64_t)row * n + i];
+  if (i >= n) return;
+  const int r0 = blockIdx.y * SORT_ROWS, r1 = r0 + SORT_ROWS < n ? r0 + SORT_ROWS : n;
+  if (blockIdx.y == 0) evals[rank] = di;
+#pragma unroll 4
+  for (int row = r0; row < r1; ++row) Q[(int64_t)row * n + rank] = V[(int64_t)row * n + i];
 }
 
 static int jac_nbp(int n) {
@@ -648,35 +758,54 @@ int jacobi_eigh_batch(const JacobiJob *jobs, int njobs, double tol, int max_swee
     J.R = jb.work + (size_t)2 * n * n;
     J.n = n;
     J.nbp = jac_nbp(n);
-    J.par0 = 0;
+    J.par0 = 0;                                    // nbp is even: each sweep ends in the buffer it started in
     J.first_inner = J.first_tile = J.first_panel = 0;
     hipLaunchKernelGGL(eye_kernel, dim3(grid_for((int64_t)n * n)), dim3(256), 0, s, J.V, n);
     if (n <= 1) active[k] = 0;
   }
   JacProb *dtab = static_cast<JacProb *>(table);
   int sweep = 0;
-  for (;; ++sweep) {
+  // the problems still iterating, as the table on the device lists them; it is
+  // written again only when one of them is done (an even number of block
+  // rounds leaves A in the buffer it started in)
+  std::vector<JacProb> run;
+  std::vector<int> ids;
+  int rmax = 0;
+  int64_t n_inner = 0, n_tile = 0, n_panel = 0;
+  auto set_table = [&]() {
+    run.clear();
+    ids.clear();
+    rmax = 0;
+    n_inner = n_tile = n_panel = 0;
+    for (int k = 0; k < njobs; ++k) {
+      if (!active[k]) continue;
+      JacProb &J = all[k];
+      const int np2 = J.nbp / 2;
+      J.first_inner = n_inner;
+      J.first_tile = n_tile;
+      J.first_panel = n_panel;
+      n_inner += np2;
+      n_tile += (int64_t)np2 * (np2 + 1) / 2;
+      n_panel += (int64_t)((J.n + J2 - 1) / J2) * np2;
+      rmax = std::max(rmax, J.nbp);                // block rounds g = 0 .. nbp - 1
+      run.push_back(J);
+      ids.push_back(k);
+    }
+    if (run.empty()) return true;
+    return hipMemcpyAsync(dtab, run.data(), run.size() * sizeof(JacProb), hipMemcpyHostToDevice, s) == hipSuccess;
+  };
+  if (!set_table()) return -1;
+  for (; !run.empty(); ++sweep) {
     // convergence of every active problem, one host synchronisation (also
     // after the last allowed sweep, so that its result is judged)
-    std::vector<JacProb> act;
-    std::vector<int> ids;
-    for (int k = 0; k < njobs; ++k)
-      if (active[k]) {
-        act.push_back(all[k]);
-        ids.push_back(k);
-      }
-    if (act.empty()) break;
-    if (hipMemcpyAsync(dtab, act.data(), act.size() * sizeof(JacProb), hipMemcpyHostToDevice, s) != hipSuccess)
-      return -1;
-    hipLaunchKernelGGL(offnorm_kernel, dim3((unsigned)(act.size() * OFFP)), dim3(256), 0, s, dtab, norms);
-    if (hipMemcpyAsync(host_norms, norms, 2 * OFFP * act.size() * sizeof(double), hipMemcpyDeviceToHost, s) !=
+    const int nr = (int)run.size();
+    hipLaunchKernelGGL(offnorm_kernel, dim3((unsigned)(nr * OFFP)), dim3(256), 0, s, dtab, norms);
+    if (hipMemcpyAsync(host_norms, norms, (size_t)2 * OFFP * nr * sizeof(double), hipMemcpyDeviceToHost, s) !=
         hipSuccess)
       return -1;
     if (hipStreamSynchronize(s) != hipSuccess) return -1;
-    std::vector<JacProb> run;
-    int rmax = 0;
-    int64_t n_inner = 0, n_tile = 0, n_panel = 0;
-    for (size_t a = 0; a < act.size(); ++a) {
+    bool changed = false;
+    for (int a = 0; a < nr; ++a) {
       const int k = ids[a];
       double off = 0, dg = 0;
       for (int q = 0; q < OFFP; ++q) {
@@ -689,37 +818,24 @@ int jacobi_eigh_batch(const JacobiJob *jobs, int njobs, double tol, int max_swee
       prev_off[k] = off;
       if (done) {
         active[k] = 0;
-        continue;
+        changed = true;
       }
-      if (sweep >= max_sweeps) continue;           // out of sweeps: stays unconverged
-      JacProb &J = all[k];
-      const int np2 = J.nbp / 2;
-      J.first_inner = n_inner;
-      J.first_tile = n_tile;
-      J.first_panel = n_panel;
-      n_inner += np2;
-      n_tile += (int64_t)np2 * (np2 + 1) / 2;
-      n_panel += (int64_t)((J.n + J2 - 1) / J2) * np2;
-      rmax = std::max(rmax, J.nbp);                // block rounds g = 0 .. nbp - 1
-      run.push_back(J);
-      J.par0 ^= J.nbp & 1;                         // buffer holding A after this sweep (nbp is even)
     }
-    if (run.empty()) break;
-    if (hipMemcpyAsync(dtab, run.data(), run.size() * sizeof(JacProb), hipMemcpyHostToDevice, s) != hipSuccess)
-      return -1;
-    const int nr = (int)run.size();
+    if (changed && !set_table()) return -1;
+    if (run.empty() || sweep >= max_sweeps) break;  // (out of sweeps: the rest stay unconverged)
     for (int g = 0; g < rmax; ++g) {
-      hipLaunchKernelGGL(jacobi_inner_kernel, dim3((unsigned)n_inner), dim3(1024), 0, s, dtab, nr, g);
-      hipLaunchKernelGGL(jacobi_apply_a_kernel, dim3((unsigned)n_tile), dim3(256), 0, s, dtab, nr, g);
-      hipLaunchKernelGGL(jacobi_apply_v_kernel, dim3((unsigned)n_panel), dim3(256), 0, s, dtab, nr, g);
+      if (g == 0)
+        hipLaunchKernelGGL((jacobi_inner_kernel<true>), dim3((unsigned)n_inner), dim3(512), 0, s, dtab, (int)run.size(), g);
+      else
+        hipLaunchKernelGGL((jacobi_inner_kernel<false>), dim3((unsigned)n_inner), dim3(512), 0, s, dtab, (int)run.size(), g);
+      hipLaunchKernelGGL(jacobi_apply_kernel, dim3((unsigned)(n_tile + n_panel)), dim3(256), 0, s, dtab,
+                         (int)run.size(), g, (int)n_tile);
     }
-    // the table is rewritten next sweep: this sweep's launches must have read it
-    if (hipStreamSynchronize(s) != hipSuccess) return -1;
   }
   for (int k = 0; k < njobs; ++k) {
     const JacProb &J = all[k];
-    hipLaunchKernelGGL(jacobi_sort_kernel, dim3((J.n + 255) / 256), dim3(256), 0, s, J.A[J.par0], J.V, J.n,
-                       jobs[k].evals, jobs[k].Q);
+    hipLaunchKernelGGL(jacobi_sort_kernel, dim3((J.n + 255) / 256, (J.n + SORT_ROWS - 1) / SORT_ROWS), dim3(256), 0, s,
+                       J.A[J.par0], J.V, J.n, jobs[k].evals, jobs[k].Q);
   }
   if (sweeps_done) *sweeps_done = sweep;
   int unconv = 0;
