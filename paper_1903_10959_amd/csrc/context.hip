@@ -1,6 +1,6 @@
 // C ABI of the library: context, tables, and the host orchestration of the
 // ChFSI steps (filter, CholGS, Rayleigh-Ritz, solve loop).  Every numerical
-// step runs in the device kernels of hx.hip, dense.hip and small.hip; the host
+// step runs in the device kernels of kron.hip, dense.hip and small.hip; the host
 // only computes scalars (recursion coefficients, bounds) and control flow.
 #include <hip/hip_runtime.h>
 
@@ -287,26 +287,32 @@ extern "C" int chfsi_set_potential(chfsi_ctx *c, const double *v, int64_t n_dof,
   if (c->device < 0 && v_on_device) return fail(c, CHFSI_ERR_ARG, "host-only context takes a host potential");
   if (c->device >= 0)
     if (int r = set_dev(c)) return r;
-  std::vector<double> hv(n_dof);
-  if (v_on_device) {
-    HIPCHK(c, hipMemcpyAsync(hv.data(), v, n_dof * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-  }
-  else std::memcpy(hv.data(), v, n_dof * sizeof(double));
   double vmax = -INFINITY;
-  for (int64_t i = 0; i < n_dof; ++i) {
-    if (!std::isfinite(hv[i])) return fail(c, CHFSI_ERR_ARG, "set_potential: non-finite value");
-    vmax = std::max(vmax, hv[i]);
+  if (v_on_device) {
+    // maximum and finiteness on the device (NaN in a partial maximum: a
+    // non-finite value), the values stay there
+    constexpr int NPART = 256;
+    HIPCHK(c, c->vpart.ensure(NPART * sizeof(double)));
+    double part[NPART];
+    max_finite_launch(v, n_dof, c->vpart.as<double>(), NPART, c->stream);
+    HIPCHK(c, hipMemcpyAsync(part, c->vpart.p, sizeof part, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    for (double x : part) {
+      if (std::isnan(x)) return fail(c, CHFSI_ERR_ARG, "set_potential: non-finite value");
+      vmax = std::max(vmax, x);
+    }
+  } else {
+    for (int64_t i = 0; i < n_dof; ++i) {
+      if (!std::isfinite(v[i])) return fail(c, CHFSI_ERR_ARG, "set_potential: non-finite value");
+      vmax = std::max(vmax, v[i]);
+    }
   }
-  c->vmax = vmax;
-  c->ub = 3.0 * c->mesh.lam1d_max + vmax;
-  if (c->device < 0) {
-    c->has_pot = true;
-    return 0;
+  if (c->device >= 0) {
+    HIPCHK(c, c->V64.ensure(n_dof * sizeof(double)));
+    HIPCHK(c, hipMemcpyAsync(c->V64.p, v, n_dof * sizeof(double),
+                             v_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));      // the caller may change v after the return
   }
-  HIPCHK(c, c->V64.ensure(n_dof * sizeof(double)));
-  HIPCHK(c, hipMemcpyAsync(c->V64.p, hv.data(), n_dof * sizeof(double), hipMemcpyHostToDevice, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
   c->vmax = vmax;
   c->ub = 3.0 * c->mesh.lam1d_max + vmax;
   c->has_pot = true;

@@ -50,6 +50,7 @@ struct chfsi_ctx {
   double vmax = 0, ub = 0;
   // device tables
   chfsi::DevBuf minv64, V64;
+  chfsi::DevBuf vpart; // partial maxima of a potential given on the device
   chfsi::DevBuf ae64;  // 1D element matrices Ae and C of the Chebyshev step, (p+1)^2 each
   int tile_variant = -1;  // tile of the step kernel (-1: built-in choice)
   int rr_residual = 0;    // Ritz residuals: 0 cost model, 1 rotate HX, 2 apply Htilde again
@@ -79,7 +80,7 @@ struct chfsi_ctx {
   bool verbose = false;   // CHFSI_VERBOSE: one progress line per solve pass on stderr
   // every device buffer the context owns
   template <typename F> void each_buf(F f) {
-    chfsi::DevBuf *all[] = {&minv64, &V64, &ae64, &fbuf[0],
+    chfsi::DevBuf *all[] = {&minv64, &V64, &vpart, &ae64, &fbuf[0],
                             &fbuf[1], &fbuf[2], &gram_part, &Smat, &dinv, &Zmat, &Wmat, &jac_work, &evals_d,
                             &resid_part, &resid_d, &flag, &HX, &diag0, &minratio, &rscratch, &occ_d, &kgroup_d, &pois_kb, &pois_m, &pois_work, &pois_q, &csel};
     for (chfsi::DevBuf *b : all) f(*b);

@@ -185,6 +185,9 @@ void herm_embed_launch(const double *G, int n2, double *E, hipStream_t s);
 void herm_select_launch(const double *V, const double *ev, int n2, double *Q, double *evals, double *lam2,
                         int *status, hipStream_t s);
 
+// part[k], k < npart: maxima of v over npart interleaved parts (-inf for an empty
+// one, NaN where a value is not finite).
+void max_finite_launch(const double *v, int64_t n, double *part, int npart, hipStream_t s);
 // Zero the strictly upper triangle, helpers.
 void fill_launch(double *X, int64_t n, double v, hipStream_t s);
 void zero_int_launch(int *p, int n, hipStream_t s);

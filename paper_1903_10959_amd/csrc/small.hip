@@ -857,6 +857,28 @@ int jacobi_eigh(double *A, int n, double *work, double *evals, double *Q, double
   return jacobi_eigh_batch(&job, 1, tol, max_sweeps, tail, tail + 16, host_scratch, s, sweeps_done, nullptr);
 }
 
+__global__ __launch_bounds__(256) void max_finite_kernel(const double *__restrict__ v, int64_t n,
+                                                         double *__restrict__ part) {
+  __shared__ double red[256];
+  double m = -__builtin_inf();
+  bool bad = false;
+  for (int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+    const double x = v[i];
+    bad |= !(x - x == 0.0);
+    m = fmax(m, x);
+  }
+  red[threadIdx.x] = bad ? __builtin_inf() : m;     // (every kept value is finite: +inf stands for "not finite")
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if ((int)threadIdx.x < w) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + w]);
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) part[blockIdx.x] = red[0] == __builtin_inf() ? __builtin_nan("") : red[0];
+}
+void max_finite_launch(const double *v, int64_t n, double *part, int npart, hipStream_t s) {
+  hipLaunchKernelGGL(max_finite_kernel, dim3((unsigned)npart), dim3(256), 0, s, v, n, part);
+}
+
 __global__ void fill_kernel(double *X, int64_t n, double v) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     X[i] = v;

@@ -2,11 +2,12 @@
 whose rows lie odd distances apart: Gram matrices of up to 64 columns (fragments
 of 16) and just beyond, Cholesky blocks of 32, Jacobi pairs of 64, residuals in
 groups of 32 and 64 columns, on meshes with fewer rows than one split, and a
-row more than a whole number of them."""
+row more than a whole number of them.  And the potential given on the device."""
 import numpy as np
 import pytest
 
-from gpu_util import make_ctx, oracle_apply, to_gpu, to_host
+import workload
+from gpu_util import make_ctx, oracle_apply, to_gpu, to_host, torch_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -57,4 +58,32 @@ def test_zero_column_anywhere_in_a_block_is_refused(ncols, bad):
         c.orthonormalize(Xg)
     assert ei.value.status == -5
     np.testing.assert_array_equal(to_host(Xg), X)
+    c.close()
+
+
+@pytest.mark.parametrize("n_el,p", [(1, 2), (2, 4), (8, 5)])    # 1, 343 and 59,319 values
+def test_potential_on_the_device_equals_the_host_one(n_el, p):
+    """Same bound and same operator from either; a non-finite value anywhere is
+    refused and the potential before it stays."""
+    import paper_1903_10959_amd as P
+    torch, dev = torch_dev()
+    nd = (n_el * p - 1) ** 3
+    V = np.random.default_rng(7).uniform(-9, -1, nd)
+    c, _ = make_ctx(3.0, n_el, p, V=V)
+    X = workload.start_block(nd, 3, 11)
+    ub, Y = c.upper_bound, to_host(c.apply(to_gpu(X)))
+    c.set_potential(np.zeros(nd))
+    Vg = torch.from_numpy(V).to(dev)
+    c.set_potential(Vg)
+    Vg.zero_()                                       # the caller's after the return
+    assert c.upper_bound == ub
+    np.testing.assert_array_equal(to_host(c.apply(to_gpu(X))), Y)
+    for at in sorted({0, nd // 2, nd - 1}):
+        for x in (np.nan, np.inf, -np.inf):
+            W = torch.zeros(nd, dtype=torch.float64, device=dev)
+            W[at] = x
+            with pytest.raises(P.ChfsiError):
+                c.set_potential(W)
+    assert c.upper_bound == ub
+    np.testing.assert_array_equal(to_host(c.apply(to_gpu(X))), Y)
     c.close()
