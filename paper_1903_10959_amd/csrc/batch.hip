@@ -575,7 +575,7 @@ extern "C" size_t chfsi_batch_footprint_bytes(int n_el, int p, int nblock) {
   b += 3 * nb * nb * 8 + nb32 * 32 * 32 * 8 + jacobi_work_elems(nblock) * 8 + 3 * nb * 8 + 4 * sizeof(int) +
        nb32 * 8;
   b += rmul_scratch_elems((int64_t)nd, nblock) * 8;
-  b += gram_part_elems_slots((int64_t)nd, nblock, 512) * 8;       // 256 CUs x 2 resident gram work-groups
+  b += gram_part_elems((int64_t)nd, nblock) * 8;
   b += (size_t)resid_nchunk((int64_t)nd) * nb * 8;
   // the session's three recursion buffers (FP64-sized for either rung, columns
   // in whole groups) and HX

@@ -1015,7 +1015,7 @@ extern "C" size_t chfsi_footprint_bytes(int n_el, int p, int nblock, int block_w
   b += nd * nblock * 8;                                            // HX
   const size_t nn = (size_t)nblock * nblock;
   b += 4 * nn * 8 + jacobi_work_elems(nblock) * 8;                 // S, Z, W, jacobi
-  b += gram_part_elems_slots((int64_t)nd, nblock, 512) * 8;       // 256 CUs x 2 resident gram work-groups
+  b += gram_part_elems((int64_t)nd, nblock) * 8;
   b += rmul_scratch_elems((int64_t)nd, nblock) * 8;
   b += (size_t)resid_nchunk((int64_t)nd) * nblock * 8;
   return b;

@@ -25,8 +25,6 @@
 
 namespace chfsi {
 
-static constexpr int GT = 128;  // gram output tile (4 waves x 64x64)
-
 // Resident work-groups of `kern` (256 threads) on the current device.
 template <typename K>
 static int resident_slots(K kern) {
@@ -55,147 +53,141 @@ __device__ __forceinline__ void tri_tile(int t, int &ti, int &tj) {
   tj = t - i * (i + 1) / 2;
 }
 
-// One (split, lower tile) work-group: partial G tile over rows [r0, r1).  The
-// contraction runs over chunks of 16 rows: the chunk's 128 columns of A and
-// of B are loaded into registers one chunk ahead (16-byte loads when the
-// leading dimensions are even), written to the other half of a
-// double-buffered LDS area after the chunk's MFMAs, and published by one
-// barrier per chunk.  Wave (wi, wj) owns the 64 x 64 quarter (wi, wj); on a
-// diagonal tile the strictly upper quarter is never read and is skipped.
-// FP32 modes stage the chunk in LDS already rounded to FP32 (half the LDS
-// bytes, so more resident work-groups).
-// mode 0: every lower tile, FP64.  Mixed overlap: mode 1 computes every
-// quarter except the 64 x 64 diagonal blocks with FP32 inputs and products,
-// mode 2 (diagonal tiles only) the diagonal blocks in FP64.  Split projected
-// Hamiltonian: mode 3 computes every quarter outside the trailing block
-// (rows and columns >= fr0, fr0 a multiple of 64) with FP32 inputs and
-// products, mode 4 the quarters inside it in FP64.
-// Grid: nsplit x ngrid work-groups.  Modes 0, 1, 3: ngrid = ntl = all lower
-// tiles.  Mode 2: ngrid = the diagonal tiles, part indexed by the full
-// triangle (ntl tiles).  Mode 4: ngrid = ntl = the lower tiles of the trailing
-// sub-triangle starting at tile row/column tf, part indexed within it.
-template <int VEC, int MODE>
-__global__ __launch_bounds__(256) void gram_kernel(const double *__restrict__ A, int64_t lda,
-                                                   const double *__restrict__ B, int64_t ldb, int64_t nrows, int n,
-                                                   int ngrid, int ntl, int tf, int64_t rows_per_split, int fr0,
-                                                   double *__restrict__ part) {
-  typedef double vec_t __attribute__((ext_vector_type(VEC)));
-  typedef typename std::conditional<MODE == 1 || MODE == 3, float, double>::type CT;   // product type
-  typedef typename acc4<CT>::type acc_t;
-  typedef CT lds_vec_t __attribute__((ext_vector_type(VEC)));
-  constexpr int KR = sizeof(CT) == 4 ? 32 : 16;   // rows per chunk (FP32 chunks: same LDS bytes)
-  constexpr int PT = KR * GT / (256 * VEC);       // vectors per thread per operand
-  // staged in the product type: FP32 modes round once, at the LDS store
-  __shared__ __align__(16) CT As[2][KR][GT];
-  __shared__ __align__(16) CT Bs[2][KR][GT];
-  const int lid = xcd_grouped_block();
-  const int split = lid / ngrid;
-  int t = lid - split * ngrid;                    // part tile index
-  int ti, tj;
-  if (MODE == 2) {
-    ti = tj = t;                                  // diagonal tile t
-    t = ti * (ti + 1) / 2 + ti;
-  } else {
-    tri_tile(t, ti, tj);
-    ti += tf;
-    tj += tf;
-  }
-  const int tid = threadIdx.x;
-  const int wave = tid >> 6, lane = tid & 63;
-  const int wi = wave >> 1, wj = wave & 1;
-  const int j = lane & 15, kq = lane >> 4;
-  auto quarter_active = [&](int qi, int qj) {
-    // strictly upper quarters and quarters wholly past the last column are never read
-    const bool inside = ti * GT + qi * 64 < n && tj * GT + qj * 64 < n;
-    const bool lower = !(ti == tj && qi < qj);
-    const bool in_fr = ti * GT + qi * 64 >= fr0 && tj * GT + qj * 64 >= fr0;
-    return inside && (MODE == 0 ? lower : MODE == 1 ? !(ti == tj && qi <= qj) : MODE == 2 ? qi == qj
-                      : MODE == 3 ? lower && !in_fr : lower && in_fr);
-  };
-  if (!(quarter_active(0, 0) || quarter_active(1, 0) || quarter_active(0, 1) || quarter_active(1, 1)))
-    return;                                        // whole work-group idle in this mode
-  const bool active = quarter_active(wi, wj);
-  const int64_t r0 = (int64_t)split * rows_per_split;
-  int64_t r1 = r0 + rows_per_split;
-  if (r1 > nrows) r1 = nrows;
-  const int ib = ti * GT, jb = tj * GT;           // tile origin
-
-  vec_t areg[PT], breg[PT];
-  // slot v -> (row v / (GT/VEC), column vector v % (GT/VEC)); out-of-range
-  // slots load a clamped in-bounds address and store zero
-  auto load_chunk = [&](int64_t k0) {
+// acc += A[r0 : r1, ib + ...]^T B[r0 : r1, jb + ...], one wave's tile of F x F
+// fragments, with products in CT.  Fragments are read straight from memory (16
+// consecutive columns of four rows each), UN groups of four rows ahead in
+// registers.  frag: the fragments to multiply (ALL: every one).  The last row of
+// the matrix is read with its columns clamped to n; in the rows before it a
+// fragment may run on into the next row, whose values only reach entries
+// beyond n.
+template <typename CT, int F, bool ALL, typename ACC>
+__device__ __forceinline__ void gram_tile(const double *__restrict__ A, int64_t lda, const double *__restrict__ B,
+                                          int64_t ldb, int64_t r0, int64_t r1, int64_t nrows, int n, int ib, int jb,
+                                          unsigned frag, ACC (&acc)[F][F]) {
+  constexpr int UN = F < 4 ? 4 : 2;
+  const int lane = threadIdx.x & 63, j = lane & 15, kq = lane >> 4;
+  auto multiply = [&](const double (&av)[F], const double (&bv)[F]) {
 #pragma unroll
-    for (int i = 0; i < PT; ++i) {
-      const int v = tid + 256 * i;
-      const int64_t row = min(k0 + v / (GT / VEC), r1 - 1);
-      const int cv = (v % (GT / VEC)) * VEC;
-      areg[i] = *reinterpret_cast<const vec_t *>(A + row * lda + min(ib + cv, n - VEC));
-      breg[i] = *reinterpret_cast<const vec_t *>(B + row * ldb + min(jb + cv, n - VEC));
+    for (int a = 0; a < F; ++a)
+#pragma unroll
+      for (int b = 0; b < F; ++b)
+        if (ALL || (frag >> (a * F + b) & 1)) acc[a][b] = mfma16x4((CT)av[a], (CT)bv[b], acc[a][b]);
+  };
+  const int64_t rfast = r1 < nrows ? r1 : nrows - 1;
+  const int nfast = rfast > r0 ? (int)((rfast - r0) / (4 * UN)) : 0;   // groups of 4 UN rows
+  const double *pa = A + (r0 + kq) * lda + ib + j, *pb = B + (r0 + kq) * ldb + jb + j;
+  if (nfast > 0) {
+    double av[UN][F], bv[UN][F];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+#pragma unroll
+      for (int a = 0; a < F; ++a) av[u][a] = pa[16 * a];
+#pragma unroll
+      for (int b = 0; b < F; ++b) bv[u][b] = pb[16 * b];
+      pa += 4 * lda;
+      pb += 4 * ldb;
     }
-  };
-  auto store_chunk = [&](int buf, int64_t k0) {
-#pragma unroll
-    for (int i = 0; i < PT; ++i) {
-      const int v = tid + 256 * i;
-      const int kr = v / (GT / VEC), cv = (v % (GT / VEC)) * VEC;
-      const bool rok = k0 + kr < r1;
-      lds_vec_t a, b;
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) {
-        a[e] = (rok && ib + cv + e < n) ? (CT)areg[i][e] : (CT)0;
-        b[e] = (rok && jb + cv + e < n) ? (CT)breg[i][e] : (CT)0;
-      }
-      *reinterpret_cast<lds_vec_t *>(&As[buf][kr][cv]) = a;
-      *reinterpret_cast<lds_vec_t *>(&Bs[buf][kr][cv]) = b;
-    }
-  };
-
-  acc_t acc[4][4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = acc_t{0, 0, 0, 0};
-  const int64_t nk = (r1 - r0 + KR - 1) / KR;
-  if (nk > 0) {
-    load_chunk(r0);
-    store_chunk(0, r0);
-  }
-  __syncthreads();
 #pragma unroll 1
-  for (int64_t kc = 0; kc < nk; ++kc) {
-    const int buf = (int)(kc & 1);
-    if (kc + 1 < nk) load_chunk(r0 + (kc + 1) * KR);
-    if (active) {
+    for (int g = 1; g < nfast; ++g) {
+      // keeps the work-group's waves, which share columns, within a few rows of
+      // each other (every wave of it makes the same turns, or has ended)
+      __builtin_amdgcn_s_barrier();
 #pragma unroll
-      for (int ks = 0; ks < KR; ks += 4) {
-        const int kk = ks + kq;
-        CT av[4], bv[4];
+      for (int u = 0; u < UN; ++u) {
+        multiply(av[u], bv[u]);
 #pragma unroll
-        for (int a = 0; a < 4; ++a) av[a] = As[buf][kk][wi * 64 + a * 16 + j];
+        for (int a = 0; a < F; ++a) av[u][a] = pa[16 * a];
 #pragma unroll
-        for (int b = 0; b < 4; ++b) bv[b] = Bs[buf][kk][wj * 64 + b * 16 + j];
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-          for (int b = 0; b < 4; ++b) acc[a][b] = mfma16x4(av[a], bv[b], acc[a][b]);
+        for (int b = 0; b < F; ++b) bv[u][b] = pb[16 * b];
+        pa += 4 * lda;
+        pb += 4 * ldb;
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
-    if (kc + 1 < nk) store_chunk(buf ^ 1, r0 + (kc + 1) * KR);
-    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < UN; ++u) multiply(av[u], bv[u]);
   }
-  if (!active) return;
-  double *out = part + ((int64_t)split * ntl + t) * (GT * GT) + (wi * 64) * GT + wj * 64;
+#pragma unroll 1
+  for (int64_t r = r0 + (int64_t)nfast * (4 * UN); r < r1; r += 4) {
+    const bool rok = r + kq < r1;
+    const int64_t row = rok ? r + kq : r1 - 1;
+    double av[F], bv[F];
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < F; ++a) {
+      const int c = ib + 16 * a + j;
+      const double v = A[row * lda + min(c, n - 1)];
+      av[a] = rok ? v : 0.0;
+    }
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        out[(a * 16 + acc_row<CT>(kq, q)) * GT + b * 16 + j] = (double)acc[a][b][q];
-      }
+    for (int b = 0; b < F; ++b) {
+      const int c = jb + 16 * b + j;
+      const double v = B[row * ldb + min(c, n - 1)];
+      bv[b] = rok ? v : 0.0;
+    }
+    multiply(av, bv);
+  }
 }
 
-// n <= 64: one 64 x 64 tile, so the 128-tile kernel would leave three of its
+// G = A^T B over a split of the rows, lower triangle: one wave per 16F x 16F
+// lower tile, four tiles of one tile row (they share the columns of A in the
+// CU's cache) to a work-group, no LDS and no barriers.  The matrix cores bound
+// it: 64 clocks per FP64 fragment product against 2 / F loads, so that a small
+// tile costs no more than a large one and little is computed beyond the
+// triangle and the last column.
+// MODE 0: FP64.  MODE 1, mixed overlap: FP64 in the diagonal tiles, FP32
+// inputs and products in the rest.  MODE 2, split projected Hamiltonian: FP64
+// in the trailing block (rows and columns >= fr0), FP32 in the rest.
+// Grid: nsplit x ceil(ntl / NW) work-groups, ntl lower tiles.  FP32 products
+// take half the time, so those modes are bound by the columns: eight tiles to a
+// work-group (split, 970,299 x 360: 2.75 against 2.87 ms with four).
+template <int MODE, int F, int NW>
+__global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : F == 3 ? 3 : 2) void gram_kernel(const double *__restrict__ A, int64_t lda,
+                                                   const double *__restrict__ B, int64_t ldb, int64_t nrows, int n,
+                                                   int ntl, int64_t rows_per_split, int fr0,
+                                                   double *__restrict__ part) {
+  constexpr int T = 16 * F;
+  const int lane = threadIdx.x & 63, j = lane & 15, kq = lane >> 4;
+  const int ngrid = (ntl + NW - 1) / NW;
+  const int lid = xcd_grouped_block();
+  const int split = lid / ngrid;
+  const int t = __builtin_amdgcn_readfirstlane(NW * (lid - split * ngrid) + (int)(threadIdx.x >> 6));
+  if (t >= ntl) return;
+  int ti, tj;
+  tri_tile(t, ti, tj);
+  const int ib = ti * T, jb = tj * T;
+  const int64_t r0 = (int64_t)split * rows_per_split;
+  const int64_t r1 = r0 + rows_per_split < nrows ? r0 + rows_per_split : nrows;
+  // the fragments with an entry that is read
+  constexpr unsigned ALLF = (1u << (F * F)) - 1;
+  unsigned frag = 0;
+#pragma unroll
+  for (int a = 0; a < F; ++a)
+#pragma unroll
+    for (int b = 0; b < F; ++b)
+      if (ib + 16 * a < n && jb + 16 * b < n && ib + 16 * a >= jb + 16 * b) frag |= 1u << (a * F + b);
+  frag = __builtin_amdgcn_readfirstlane(frag);
+  double *out = part + ((int64_t)split * ntl + t) * (T * T);
+  auto run = [&](auto ct) {
+    typedef decltype(ct) CT;
+    typename acc4<CT>::type acc[F][F];
+#pragma unroll
+    for (int a = 0; a < F; ++a)
+#pragma unroll
+      for (int b = 0; b < F; ++b) acc[a][b] = typename acc4<CT>::type{0, 0, 0, 0};
+    if (frag == ALLF) gram_tile<CT, F, true>(A, lda, B, ldb, r0, r1, nrows, n, ib, jb, frag, acc);
+    else gram_tile<CT, F, false>(A, lda, B, ldb, r0, r1, nrows, n, ib, jb, frag, acc);
+#pragma unroll
+    for (int a = 0; a < F; ++a)
+#pragma unroll
+      for (int b = 0; b < F; ++b)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) out[(a * 16 + acc_row<CT>(kq, q)) * T + b * 16 + j] = (double)acc[a][b][q];
+  };
+  if (MODE == 0 || (MODE == 1 ? ti == tj : jb >= fr0)) run(double{});
+  else run(float{});
+}
+
+// n <= 64: one 64 x 64 tile, so the tile kernel would leave three of its
 // four waves idle.  Here the waves of a work-group share its rows instead,
 // each takes every fourth group of four rows straight from memory into MFMA
 // fragments (NA = ceil(n / 16) of them per operand, lower tiles only), and
@@ -256,27 +248,23 @@ __global__ __launch_bounds__(256) void gram_small_kernel(const double *__restric
   }
 }
 
-// G[i, j] = sum over splits of the partial gt x gt tiles, for i >= j in the
-// region [r0, n) x [r0, n) (tiles numbered within the sub-triangle from tile
-// row tf), mirrored to the upper triangle.  skip0 >= 0: leave out the entries
-// with both i and j >= skip0 (written by another reduction).  A work-group
-// adds 32 entries, each by eight threads that take every eighth split and are
-// then added in order: one thread per entry left the chip waiting on the
-// serial chain over the splits (6 tiles x 341 splits: 487 us; this: 38).
+// G[i, j] = sum over splits of the partial gt x gt tiles, mirrored to the upper
+// triangle.  A work-group adds 32 entries, each by eight threads that take
+// every eighth split and are then added in order: one thread per entry left
+// the chip waiting on the serial chain over the splits (6 tiles x 341 splits:
+// 487 us; this: 38).
 __global__ __launch_bounds__(256) void gram_reduce_kernel(const double *__restrict__ part, int nsplit, int ntl,
-                                                          int gt, int n, int tf, int r0, int skip0,
-                                                          double *__restrict__ G) {
+                                                          int gt, int n, double *__restrict__ G) {
   __shared__ double red[8][33];
-  const int m = n - r0;
-  const int64_t total = (int64_t)m * m;
+  const int64_t total = (int64_t)n * n;
   const int e = threadIdx.x & 31, sl = threadIdx.x >> 5;
   for (int64_t base = blockIdx.x * (int64_t)32; base < total; base += (int64_t)gridDim.x * 32) {
     const int64_t idx = base + e;
-    const int i = r0 + (int)(idx / m), jj = r0 + (int)(idx - idx / m * m);
-    const bool on = idx < total && jj <= i && !(skip0 >= 0 && jj >= skip0);
+    const int i = (int)(idx / n), jj = (int)(idx - idx / n * n);
+    const bool on = idx < total && jj <= i;
     double s = 0;
     if (on) {
-      const int ti = i / gt - tf, tj = jj / gt - tf;
+      const int ti = i / gt, tj = jj / gt;
       const int t = ti * (ti + 1) / 2 + tj;
       const double *p = part + (int64_t)t * (gt * gt) + (i % gt) * gt + (jj % gt);
       const int64_t st = (int64_t)ntl * (gt * gt);
@@ -295,55 +283,35 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(const double *__restri
   }
 }
 
-static int gram_ntiles(int n) {
-  int nt = (n + GT - 1) / GT;
-  return nt * (nt + 1) / 2;
-}
-
-// Row splits for a launch of ntl tiles: the largest count whose grid fits in
-// four rounds of `slots` resident work-groups, with at least 256 rows per split.
-static int gram_nsplit_tiles(int64_t nrows, int ntl, int slots) {
-  int64_t want = 4 * (int64_t)slots / ntl;
+// Row splits: as many as fill four rounds of 512 work-groups with 128 x 128
+// tiles, at least 256 rows each.  The count is that of 128-wide tiles whatever
+// the kernel's are, so that the sums and the partial buffer do not depend on
+// the tile chosen (48-wide tiles: 2.7 to 4 rounds of 768 work-groups).
+static int gram_nsplit(int64_t nrows, int n) {
+  const int64_t nt = (n + 127) / 128, ntl = nt * (nt + 1) / 2;
+  int64_t want = 2048 / ntl;
   const int64_t maxs = (nrows + 255) / 256;
   if (want > maxs) want = maxs;
   if (want < 1) want = 1;
   return (int)want;
 }
 
-static int gram_slots() {
-  static const int slots = resident_slots(gram_kernel<2, 0>);   // of the kernel on this GPU family: looked up once
-  return slots;
+size_t gram_part_elems(int64_t nrows, int n) {
+  const int64_t nt = (n + 127) / 128, ntl = nt * (nt + 1) / 2;
+  return (size_t)gram_nsplit(nrows, n) * ntl * 128 * 128;
 }
-
-int gram_nsplit(int64_t nrows, int n) { return gram_nsplit_tiles(nrows, gram_ntiles(n), gram_slots()); }
-
-// Enough for a launch over the full triangle or over any trailing sub-triangle.
-size_t gram_part_elems_slots(int64_t nrows, int n, int slots) {
-  const int nt = (n + GT - 1) / GT;
-  size_t best = 0;
-  for (int m = 1; m <= nt; ++m) {
-    const int ntl = m * (m + 1) / 2;
-    const size_t e = (size_t)gram_nsplit_tiles(nrows, ntl, slots) * ntl;
-    if (e > best) best = e;
-  }
-  return best * GT * GT;
-}
-
-size_t gram_part_elems(int64_t nrows, int n) { return gram_part_elems_slots(nrows, n, gram_slots()); }
 
 static int64_t gram_rows_per_split(int64_t nrows, int nsplit) {
   int64_t rps = (nrows + nsplit - 1) / nsplit;
   return (rps + 15) / 16 * 16;
 }
 
-static void gram_reduce(const double *part, int nsplit, int ntl, int n, int tf, int r0, int skip0, double *G,
-                        hipStream_t s, int gt = GT) {
-  const int64_t m = n - r0;
+static void gram_reduce(const double *part, int nsplit, int ntl, int n, double *G, hipStream_t s, int gt) {
+  const int64_t m = n;
   int64_t blocks = (m * m + 31) / 32;
   if (blocks > 65536) blocks = 65536;
   if (blocks < 1) return;
-  hipLaunchKernelGGL(gram_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, s, part, nsplit, ntl, gt, n, tf, r0,
-                     skip0, G);
+  hipLaunchKernelGGL(gram_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, s, part, nsplit, ntl, gt, n, G);
 }
 
 // n <= 64 (mixed or not: the 64-wide diagonal block is FP64 either way).
@@ -353,6 +321,7 @@ static void gram_small(const double *A, int64_t lda, const double *B, int64_t ld
                        size_t max_split, double *G, hipStream_t s) {
   int64_t nsplit = (nrows + 127) / 128;
   if (nsplit > 256) nsplit = 256;
+  if (nsplit < 1) nsplit = 1;
   if (max_split > 0 && nsplit > (int64_t)max_split) nsplit = (int64_t)max_split;
   const int64_t rps = gram_rows_per_split(nrows, (int)nsplit);
   nsplit = (nrows + rps - 1) / rps;
@@ -367,23 +336,24 @@ static void gram_small(const double *A, int64_t lda, const double *B, int64_t ld
     GRAM_SMALL(1) GRAM_SMALL(2) GRAM_SMALL(3) GRAM_SMALL(4)
   }
 #undef GRAM_SMALL
-  gram_reduce(part, (int)nsplit, 1, n, 0, 0, -1, G, s, 64);
+  gram_reduce(part, (int)nsplit, 1, n, G, s, 64);
 }
 
-static bool gram_v16(const double *A, int64_t lda, const double *B, int64_t ldb, int n) {
-  return lda % 2 == 0 && ldb % 2 == 0 && n % 2 == 0 && ((uintptr_t)A % 16) == 0 && ((uintptr_t)B % 16) == 0;
-}
-
-template <int MODE>
-static void gram_mode(bool v16, dim3 grid, const double *A, int64_t lda, const double *B, int64_t ldb,
-                      int64_t nrows, int n, int ngrid, int ntl, int tf, int64_t rps, int fr0, double *part,
-                      hipStream_t s) {
-  if (v16)
-    hipLaunchKernelGGL((gram_kernel<2, MODE>), grid, dim3(256), 0, s, A, lda, B, ldb, nrows, n, ngrid, ntl, tf, rps,
-                       fr0, part);
-  else
-    hipLaunchKernelGGL((gram_kernel<1, MODE>), grid, dim3(256), 0, s, A, lda, B, ldb, nrows, n, ngrid, ntl, tf, rps,
-                       fr0, part);
+template <int MODE, int F, int NW>
+static int gram_tiles(const double *A, int64_t lda, const double *B, int64_t ldb, int64_t nrows, int n, int fr0,
+                      double *part, size_t part_elems, double *G, hipStream_t s) {
+  constexpr int T = 16 * F;
+  const int nt = (n + T - 1) / T, ntl = nt * (nt + 1) / 2, nwg = (ntl + NW - 1) / NW;
+  int64_t nsplit = gram_nsplit(nrows, n);
+  const int64_t fit = (int64_t)((part_elems > 0 ? part_elems : gram_part_elems(nrows, n)) / ((size_t)ntl * T * T));
+  if (fit < 1) return -1;
+  if (nsplit > fit) nsplit = fit;
+  const int64_t rps = gram_rows_per_split(nrows, (int)nsplit);
+  nsplit = (nrows + rps - 1) / rps;
+  hipLaunchKernelGGL((gram_kernel<MODE, F, NW>), dim3((unsigned)(nsplit * nwg)), dim3(64 * NW), 0, s, A, lda, B, ldb, nrows, n,
+                     ntl, rps, fr0, part);
+  gram_reduce(part, (int)nsplit, ntl, n, G, s, T);
+  return 0;
 }
 
 void gram_launch(const double *A, int64_t lda, const double *B, int64_t ldb, int64_t nrows, int n, double *part,
@@ -393,52 +363,26 @@ void gram_launch(const double *A, int64_t lda, const double *B, int64_t ldb, int
 
 int gram_launch_capped(const double *A, int64_t lda, const double *B, int64_t ldb, int64_t nrows, int n,
                        double *part, size_t part_elems, double *G, int mixed, hipStream_t s) {
-  if (n <= 64 && nrows > 0) {
+  if (n <= 64) {
     if (part_elems > 0 && part_elems < 64 * 64) return -1;
     gram_small(A, lda, B, ldb, nrows, n, part, part_elems / (64 * 64), G, s);
     return 0;
   }
-  const int ntiles = gram_ntiles(n);
-  int nsplit = gram_nsplit_tiles(nrows, ntiles, gram_slots());
-  if (part_elems > 0) {
-    const size_t fit = part_elems / ((size_t)ntiles * GT * GT);
-    if (fit < 1) return -1;
-    if ((size_t)nsplit > fit) nsplit = (int)fit;
-  }
-  const int64_t rps = gram_rows_per_split(nrows, nsplit);
-  const bool v16 = gram_v16(A, lda, B, ldb, n);
-  const int nt = (n + GT - 1) / GT;
-  const dim3 all((unsigned)(nsplit * ntiles)), diag((unsigned)(nsplit * nt));
-  if (!mixed) {
-    gram_mode<0>(v16, all, A, lda, B, ldb, nrows, n, ntiles, ntiles, 0, rps, 0, part, s);
-  } else {
-    gram_mode<1>(v16, all, A, lda, B, ldb, nrows, n, ntiles, ntiles, 0, rps, 0, part, s);
-    gram_mode<2>(v16, diag, A, lda, B, ldb, nrows, n, nt, ntiles, 0, rps, 0, part, s);
-  }
-  gram_reduce(part, nsplit, ntiles, n, 0, 0, -1, G, s);
-  return 0;
+  if (mixed) return gram_tiles<1, 4, 8>(A, lda, B, ldb, nrows, n, 0, part, part_elems, G, s);
+  // 48- or 64-wide tiles, by the fragments they cover the lower triangle with
+  // (857,375 rows: n = 283, 378 fragments against 480, 1.5 against 1.7 ms; n =
+  // 640, 1,890 against 1,760, 7.2 against 6.5 ms)
+  const int nt3 = (n + 47) / 48, nt4 = (n + 63) / 64;
+  if (9 * nt3 * (nt3 + 1) <= 16 * nt4 * (nt4 + 1))
+    return gram_tiles<0, 3, 4>(A, lda, B, ldb, nrows, n, 0, part, part_elems, G, s);
+  return gram_tiles<0, 4, 4>(A, lda, B, ldb, nrows, n, 0, part, part_elems, G, s);
 }
 
 void gram_split_launch(const double *A, int64_t lda, const double *B, int64_t ldb, int64_t nrows, int n, double *part,
                        double *G, int fr0, hipStream_t s) {
   fr0 = fr0 / 64 * 64;
-  const bool v16 = gram_v16(A, lda, B, ldb, n);
-  // the trailing block in FP64, on a grid over its own sub-triangle of tiles
-  // (so that the few tiles it touches get every row split), reduced first
-  const int nt = (n + GT - 1) / GT, tf = fr0 / GT, m = nt - tf;
-  const int ntl4 = m * (m + 1) / 2;
-  const int slots = gram_slots();
-  const int nsplit4 = gram_nsplit_tiles(nrows, ntl4, slots);
-  gram_mode<4>(v16, dim3((unsigned)(nsplit4 * ntl4)), A, lda, B, ldb, nrows, n, ntl4, ntl4, tf,
-               gram_rows_per_split(nrows, nsplit4), fr0, part, s);
-  gram_reduce(part, nsplit4, ntl4, n, tf, fr0, -1, G, s);
-  if (fr0 == 0) return;
-  // everything else with FP32 inputs and products; part is reused in order
-  const int ntiles = gram_ntiles(n);
-  const int nsplit = gram_nsplit_tiles(nrows, ntiles, slots);
-  gram_mode<3>(v16, dim3((unsigned)(nsplit * ntiles)), A, lda, B, ldb, nrows, n, ntiles, ntiles, 0,
-               gram_rows_per_split(nrows, nsplit), fr0, part, s);
-  gram_reduce(part, nsplit, ntiles, n, 0, 0, fr0, G, s);
+  if (fr0 == 0) gram_launch(A, lda, B, ldb, nrows, n, part, G, 0, s);
+  else gram_tiles<2, 4, 8>(A, lda, B, ldb, nrows, n, fr0, part, 0, G, s);
 }
 
 // ---------------------------------------------------------------------------

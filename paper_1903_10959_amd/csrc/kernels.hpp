@@ -82,16 +82,12 @@ template <typename T>
 void nonfinite_launch(const T *X, int64_t ld, int64_t nrows, int ncols, int *flag, hipStream_t s);
 
 // ---- tall-skinny products (dense.hip) ---------------------------------------
-// G = A^T B over nrows rows, lower-triangular 128x128 tiles, split over rows;
-// partial tiles go to `part` ([nsplit x ntiles x 128 x 128]) and are summed in
-// a fixed order into G (n x n, row-major, lower triangle mirrored to upper).
-// mixed: 64x64 diagonal blocks in FP64, the rest with FP32 inputs/products.
-// nsplit is sized from the device's resident work-groups; gram_part_elems is
-// the partial buffer for any gram launch on the current device, and
-// gram_part_elems_slots the same for a given resident count (no device query).
-int gram_nsplit(int64_t nrows, int n);
+// G = A^T B over nrows rows, lower-triangular tiles, split over rows; partial
+// tiles go to `part` and are summed in a fixed order into G (n x n, row-major,
+// lower triangle mirrored to upper).  mixed: 64x64 diagonal blocks in FP64, the
+// rest with FP32 inputs/products.  The number of splits follows the device's
+// resident work-groups; gram_part_elems bounds the partial buffer of any launch.
 size_t gram_part_elems(int64_t nrows, int n);
-size_t gram_part_elems_slots(int64_t nrows, int n, int slots);
 void gram_launch(const double *A, int64_t lda, const double *B, int64_t ldb, int64_t nrows, int n, double *part,
                  double *G, int mixed, hipStream_t s);
 // As gram_launch with a partial buffer of part_elems doubles (0: sized by
