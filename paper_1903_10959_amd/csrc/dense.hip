@@ -6,8 +6,9 @@
 //    the 64x64 diagonal blocks, FP32 inputs/products on the rest.
 //  * rmul: X <- X W in place by row panels (Sec. 3.4 step 4, X L^-T; Sec. 3.5
 //    subspace rotation X Q).  The paper's outer blocking over rows (B^d) keeps
-//    only a panel of the output in extra memory: here a chunk of rows is
-//    multiplied into a scratch panel and copied back.
+//    only a panel of the output in extra memory: here the rows of a work-group
+//    in LDS, or beyond 624 columns a chunk of rows multiplied into a scratch
+//    panel and copied back.
 //  * resid: column norms ||HX_j - lam_j X_j||.
 //
 // Launch shapes are sized from the device's resident work-group count (CUs x
@@ -538,6 +539,124 @@ __global__ __launch_bounds__(256) void rmul_gemm_kernel(const double *__restrict
       }
 }
 
+// X <- X W by whole rows, without the panel: a work-group copies RB rows into LDS
+// (18 loads in flight per thread), and its waves then take blocks of 16 NA rows
+// x 16 columns of the result, the longest sums first when W is triangular, and
+// write them over the rows just read, which no other work-group needs.  X
+// fragments come from LDS; W, which all work-groups share in the L2, is read
+// straight into fragments 16 rows ahead.  The waves draw the next block from a
+// counter, so that SIMDs with the shorter ones do more of them.  A triangular
+// product computes no more than it needs but for 16 columns, and the panel's
+// write, read and copy are gone: 857,375 rows, n = 32, 223 -> 152 us; n = 283,
+// 3.77 -> 2.27 ms (full W 4.74 -> 3.60); n = 568, 8.92 -> 6.64 ms.  Bound by the
+// matrix cores at n > 100 (two thirds busy), by the rows' traffic below.  64
+// rows to a block (NA = 4, half the reads of W): 2 to 10 % slower.
+// CAP: doubles of LDS; S = ceil16(n) + 2 is the row stride there (2 mod 4: the
+// 32 lanes of half a fragment read different banks).
+template <bool MIXED, int CAP, int NW, int NA>
+__global__ __launch_bounds__(64 * NW, NW == 16 ? 4 : 2) void rmul_rows_kernel(double *X, int64_t ld, int64_t nrows, int n,
+                                                                               const double *__restrict__ W,
+                                                                               int64_t ldw, int upper, int RB) {
+  constexpr int UN = 4, RU = 16 * NA;
+  __shared__ double Xs[CAP];
+  __shared__ int next;
+  if (threadIdx.x == 0) next = NW;
+  const int n16 = (n + 15) / 16 * 16, S = n16 + 2;
+  const int lane = threadIdx.x & 63, j = lane & 15, kq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t row0 = (int64_t)blockIdx.x * RB;
+  // rows r = wave, wave + NW, ... in chunks of 64 columns, LB chunks in flight
+  constexpr int LB = 18;
+  const int nch = (n16 + 63) / 64, items = RB / NW * nch;
+  for (int i0 = 0; i0 < items; i0 += LB) {
+    double v[LB];
+#pragma unroll
+    for (int u = 0; u < LB; ++u) {
+      const int i = min(i0 + u, items - 1), r = wave + i / nch * NW, k = i % nch * 64 + lane;
+      v[u] = X[(row0 + r < nrows ? row0 + r : nrows - 1) * ld + min(k, n - 1)];
+    }
+#pragma unroll
+    for (int u = 0; u < LB; ++u) {
+      const int i = i0 + u, r = wave + i / nch * NW, k = i % nch * 64 + lane;
+      if (i < items && k < n16) Xs[r * S + k] = row0 + r < nrows && k < n ? v[u] : 0.0;
+    }
+  }
+  __syncthreads();
+  const int ncb = (n + 15) / 16, units = ncb * (RB / RU);
+  for (int o = wave; o < units;) {
+    const int rg = o % (RB / RU), cb = ncb - 1 - o / (RB / RU);
+    int taken = 0;                                 // the unit after this one
+    if (lane == 0) taken = atomicAdd(&next, 1);
+    o = __builtin_amdgcn_readfirstlane(taken);
+    if (row0 + RU * rg >= nrows) continue;
+    const int c0 = 16 * cb;
+    const int kend = upper ? min(n, c0 + 16) : n, ngr = (kend + 15) / 16;
+    const double *xs = Xs + (RU * rg + j) * S + kq;
+    const int col = min(c0 + j, n - 1);
+    double w[UN];
+    auto load = [&](int g, int u) {                // rows of group g, all below n
+      const double *p = W + (int64_t)(16 * g + 4 * u + kq) * ldw;
+      w[u] = p[col];
+    };
+    auto load_last = [&](int g, int u) {
+      const double *p = W + (int64_t)min(16 * g + 4 * u + kq, n - 1) * ldw;
+      w[u] = p[col];
+    };
+    auto multiply = [&](int g, int u, auto &acc) {
+      const int k = 16 * g + 4 * u;
+#pragma unroll
+      for (int a = 0; a < NA; ++a) {
+        const double x = xs[16 * a * S + k];
+        if constexpr (sizeof(acc[0]) == sizeof(v4f)) acc[a] = mfma16x4((float)x, (float)w[u], acc[a]);
+        else acc[a] = mfma16x4(x, w[u], acc[a]);
+      }
+    };
+    // groups [g0, g1), the rows of group g0 in w; afterwards those of g1 if g1 < ngr
+    auto groups = [&](int g0, int g1, auto &acc) {
+      int g = g0;
+#pragma unroll 1
+      for (; g < g1 && g + 2 < ngr; ++g)
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+          multiply(g, u, acc);
+          load(g + 1, u);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll 1
+      for (; g < g1; ++g)
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+          multiply(g, u, acc);
+          if (g + 1 < ngr) load_last(g + 1, u);
+        }
+    };
+#pragma unroll
+    for (int u = 0; u < UN; ++u) load_last(0, u);
+    v4d acc[NA];
+#pragma unroll
+    for (int a = 0; a < NA; ++a) acc[a] = v4d{0, 0, 0, 0};
+    int g0 = 0;
+    if constexpr (MIXED) {
+      g0 = min(c0 / 64 * 4, ngr);
+      v4f acc32[NA];
+#pragma unroll
+      for (int a = 0; a < NA; ++a) acc32[a] = v4f{0, 0, 0, 0};
+      groups(0, g0, acc32);
+#pragma unroll
+      for (int a = 0; a < NA; ++a) acc[a] = f32acc_to_f64_layout(acc32[a], lane);
+    }
+    groups(g0, ngr, acc);
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int64_t row = row0 + RU * rg + 16 * a + acc_row<double>(kq, q);
+        const int c = c0 + j;
+        if (row < nrows && c < n) X[row * ld + c] = acc[a][q];
+      }
+  }
+}
+
 __global__ __launch_bounds__(256) void copy_back_kernel(const double *__restrict__ C, int64_t ldc, double *X,
                                                         int64_t ld, int64_t row0, int64_t nrows, int n,
                                                         int col0) {
@@ -559,12 +678,39 @@ size_t rmul_scratch_elems(int64_t nrows, int n) {
   return (size_t)e;
 }
 
+// Columns up to which 32 rows fit in LDS.
+static constexpr int ROWS_MAXN = 624;
+
+template <bool MIXED>
+static void rmul_rows_launch(double *X, int64_t ld, int64_t nrows, int n, const double *W, int64_t ldw, int upper,
+                             hipStream_t s) {
+  const int S = (n + 15) / 16 * 16 + 2;
+  auto go = [&](auto kern, int threads, int RB) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)((nrows + RB - 1) / RB)), dim3(threads), 0, s, X, ld, nrows, n, W, ldw, upper,
+                       RB);
+  };
+  // four work-groups to a CU up to 144 columns, two up to 304, then one
+  if (S <= 34) go(rmul_rows_kernel<MIXED, 5100, 4, 2>, 256, 128);
+  else if (S <= 78) go(rmul_rows_kernel<MIXED, 5100, 4, 2>, 256, 64);
+  else if (S <= 158) go(rmul_rows_kernel<MIXED, 5100, 4, 2>, 256, 32);
+  else if (S <= 316) go(rmul_rows_kernel<MIXED, 10200, 8, 2>, 512, 32);
+  else go(rmul_rows_kernel<MIXED, 20400, 16, 2>, 1024, 32);
+}
+
 int rmul_cols_launch(double *X, int64_t ld, int64_t nrows, int n, const double *W, int64_t ldw, int nout,
                      int out_col0, int upper, int mixed, double *scratch, size_t scratch_elems, hipStream_t s) {
   if (mixed && !upper) return -1;
   if (upper && (nout != n || ldw != n)) return -1;
   if (n <= 0 || nout <= 0 || nrows <= 0) return 0;
   if (scratch_elems < (size_t)MT * nout) return -1;
+  // whole rows in LDS while they fit; a product of fewer columns than X has
+  // too few blocks for a work-group's waves there (857,375 x 283 -> 35 columns:
+  // 1.65 ms against 1.05 in tiles)
+  if (n <= ROWS_MAXN && nout == n && out_col0 == 0) {
+    if (mixed) rmul_rows_launch<true>(X, ld, nrows, n, W, ldw, upper, s);
+    else rmul_rows_launch<false>(X, ld, nrows, n, W, ldw, upper, s);
+    return 0;
+  }
   const int nt = (nout + NTL - 1) / NTL;
   // row tiles per launch: as many as the scratch panel holds, rounded down to
   // whole rounds of resident work-groups when there is more than one round

@@ -100,7 +100,8 @@ int gram_launch_capped(const double *A, int64_t lda, const double *B, int64_t ld
 // products: the split projected Hamiltonian.
 void gram_split_launch(const double *A, int64_t lda, const double *B, int64_t ldb, int64_t nrows, int n, double *part,
                        double *G, int fr0, hipStream_t s);
-// X[r, 0:n] <- X[r, 0:n] W for all rows, chunk by chunk through `scratch`
+// X[r, 0:n] <- X[r, 0:n] W for all rows, in LDS up to 624 columns, beyond that
+// chunk by chunk through `scratch`
 // (scratch_elems doubles, at least 128 x n; rmul_scratch_elems gives the size
 // used by the library).  W: n x n row-major.  upper: W upper triangular (zero
 // blocks skipped).  mixed (requires upper): the 64-wide diagonal blocks of W in
