@@ -10,14 +10,13 @@
 //   (A x)(I,J,K) = s [ m_J m_K sum_I' k(I,I') x(I',J,K) + m_I m_K sum_J' k(J,J') x(I,J',K)
 //                    + m_I m_J sum_K' k(K,K') x(I,J,K') ],   s = 1/(4 pi),
 // k the assembled 1D Laplacian stiffness (band half-width p), m the 1D GLL
-// mass.  This is the matrix-free operator in its assembled form, applied as a
-// blocked stencil that reads x about once from HBM and writes y once (16 bytes
-// per DoF).
+// mass.  This is the matrix-free operator in its assembled form, applied cell by
+// cell in one pass over x and y (16 bytes per DoF).
 //
 // One CG iteration is three launches: the product fused with the partial
-// p.q; r -= alpha q with the partials of r.z and r.r; x += alpha p and the new
-// direction p = z + beta p.  The two global sums each iteration needs are
-// formed where they are used: every work-group of the update sums the
+// p.q; z -= alpha q / diag(A) with the partials of r.z and r.r; x += alpha p and
+// the new direction p = z + beta p.  The two global sums each iteration needs
+// are formed where they are used: every work-group of the update sums the
 // product's partials (alpha = r.z / p.q), every work-group of the direction
 // pass sums the update's (beta = r.z' / r.z and the stop test r.r <=
 // tol^2 f.f), each in the same fixed order, so all work-groups hold the same
@@ -25,10 +24,13 @@
 // between two slots by iteration parity, so no work-group reads the slot its
 // own launch writes; the stop count, which every work-group of the same
 // launch also reads, can only change from "never" to this iteration's number
-// plus one, and both values let iteration it run.  Neither z nor diag(A)^-1
-// is stored: diag(A) at a node is a sum of three products of 1D values, so
-// both vector passes recompute z = r / diag(A), and an iteration moves eight
-// arrays of n_dof values.  The
+// plus one, and both values let iteration it run.  The residual is kept as z =
+// r / diag(A), which the direction pass reads as it is; diag(A) itself is
+// recomputed in the update, from 1D values, and an iteration moves ten arrays
+// of n_dof values (24^3 cells of degree 6, which the last-level cache holds:
+// 20 + 15 + 19 us and 8 us between launches; 32 + 19 + 27 before, with the band
+// stencil, a third of the lanes idle in rows of 143, and r / diag(A) formed in
+// both vector passes).  The
 // iteration that meets the tolerance records its number; launches of later
 // iterations return at once, so the host launches iterations in groups and
 // reads that number between groups.  (Forming p inside the product, where
@@ -72,180 +74,253 @@ __device__ __forceinline__ double block_sum(double v, double *sh) {
   return s;
 }
 
-// y = A x with 2.5D blocking.  Work-group = 4 waves; wave w covers 64
-// consecutive I (one lane each) and the RY rows J0 + w RY + [0, RY); the
-// work-group marches over KB planes K.  Per plane it stages the plane's
-// (64 + 2P) x (4 RY + 2P) halo tile of x in LDS (the x- and y-direction
-// neighbours); each lane keeps, per row, its z-window of 2P + 1 values in
-// registers.  The lane's x-direction band coefficients sit in registers, the
-// wave's y- and z-direction ones are wave-uniform (scalar loads), and the
-// y-direction sums of a lane's RY rows share one LDS column read of RY + 2P
-// values.  The plane tiles are fetched PD planes ahead.  DOT: part[work-group]
-// = its share of x . y.
-// Grid: ceil(n/64) ceil(n/(4 RY)) ceil(n/KB) work-groups (1D, XCD-grouped).
-constexpr int TX = 64;
-template <int P, int RY, int KB, int PD, bool DOT>
-__global__ __launch_bounds__(PB) void poisson_stencil_kernel(const double *__restrict__ x, double *__restrict__ y,
-                                                             const double *__restrict__ kb,
-                                                             const double *__restrict__ m, int n, double s,
-                                                             const double *__restrict__ scal, int it,
-                                                             double *__restrict__ part) {
-  constexpr int BW = 2 * P + 1, TY = 4 * RY, WX = TX + 2 * P, WY = TY + 2 * P;
-  constexpr int NTL = (WY * WX + PB - 1) / PB;    // tile values per thread
-  __shared__ double sh[PB];
-  __shared__ double xs[WY][WX];
-  if (DOT && it >= scal[S_STOPAT]) return;
+// The symmetric, centrosymmetric table T(k, l) = (2 / h) K1(k, l) / m(k) of a
+// cell, m the assembled 1D mass (a vertex's on both ends): row k of A's 1D part
+// divided by the mass, so that a node's sum over the three directions is
+// multiplied by s m_I m_J m_K once.
+template <int P> struct CellTable {
+  static constexpr int N = ((P + 1) * (P + 1) + 1) / 2;
+  double t[N];
+  __device__ __forceinline__ double operator()(int k, int l) const {
+    const int i = k * (P + 1) + l, r = (P + 1) * (P + 1) - 1 - i;
+    return t[i < r ? i : r];
+  }
+};
+
+// y = A x by cells.  A wave takes 64 consecutive I and half of the P rows J of
+// one cell (all of them up to P = 3), and marches over the planes K of its cell
+// layers.  The y- and z-direction sums of a cell are its small dense table times
+// the values in registers (8 products per node where a band row has 2 P + 1),
+// the sums of a layer's P + 1 planes are held until the layer is complete, and
+// what they owe the next layer's first plane is carried on.  The x-direction
+// band goes through LDS, a strip per wave: no barriers.  Planes are loaded one
+// ahead, as buffers whose range ends with the plane: what lies outside the mesh
+// reads as zero (no branch, no address arithmetic per plane) and is not written.
+// It is bound by instructions, not by memory: 24^3 cells of degree 6, 32 -> 20
+// us per product (a whole cell per wave: 26, too few waves to hide the chains).  DOT: part[work-group] = its share of x . y.
+// Grid: ceil(n / 64) ceil(n_el / cells per work-group) ceil(n_el / zl)
+// work-groups (1D, XCD-grouped).
+static constexpr unsigned OFF_OUT = 0x80000000u;   // beyond any plane
+template <int P> struct StencilSplit {
+  static constexpr int H = P < 4 ? 1 : 2;          // waves per cell
+  static constexpr int RM = (P + H - 1) / H;       // rows of the first
+  static constexpr int CELLS = 4 / H;              // cells per work-group, along y
+};
+
+// the wave's rows [R0, R1) of cell cy, layers [L0, L1); returns its share of x . y
+template <int P, int R0, int R1, bool DOT>
+__device__ __forceinline__ double stencil_march(const double *__restrict__ x, double *__restrict__ y,
+                                                const double *__restrict__ kbs, const double *__restrict__ m,
+                                                const CellTable<P> &T, int n, int n_el, double s, int I0, int cy, int L0,
+                                                int L1, double *st) {
+  constexpr int R = R1 - R0, BW = 2 * P + 1, WX = 64 + 2 * P, HL = (2 * P * R + 63) / 64;
+  constexpr bool LOW = R0 == 0;                    // the vertex row also belongs to the cell before
+  typedef unsigned u2_t __attribute__((ext_vector_type(2)));
   const int lane = threadIdx.x & 63;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // XCD-grouped block order: the hardware deals consecutive work-groups to the
-  // 8 XCDs in turn; the logical index below is contiguous per XCD, and tiles
-  // adjacent in J (which share their halo rows) get consecutive logical
-  // indices, so their shared rows are fetched into one L2
-  const int g = (int)gridDim.x, b = (int)blockIdx.x;
-  const int lid = (b & 7) * (g >> 3) + min(b & 7, g & 7) + (b >> 3);
-  const int gx = (n + TX - 1) / TX, gy = (n + TY - 1) / TY;
-  const int bx = lid % gx, by = (lid / gx) % gy, bz = lid / (gx * gy);
-  const int I0 = bx * TX, J0 = by * TY, K0 = bz * KB;
   const int I = I0 + lane;
-  const int64_t n2 = (int64_t)n * n;
-  const bool ilive = I < n;
+  const bool ilive = I < n, live = cy < n_el;
+  const unsigned pbytes = (unsigned)n * (unsigned)n * 8u;
+  // offsets in a plane: the cell's rows, the rows of the cell before
+  auto row_off = [&](int i, int node) {
+    return live && i >= 0 && i < n && node >= 1 && node <= n ? (unsigned)(i + n * (node - 1)) * 8u : OFF_OUT;
+  };
+  unsigned oo[P + 1], ol[P], ox[HL];
+  int ex[HL];                                      // strip slots of the x-direction halo (-1: none)
+#pragma unroll
+  for (int r = 0; r <= P; ++r) oo[r] = row_off(I, cy * P + r);
+#pragma unroll
+  for (int r = 0; r < P; ++r) ol[r] = row_off(I, (cy - 1) * P + r);
+#pragma unroll
+  for (int u = 0; u < HL; ++u) {
+    const int e = lane + 64 * u, r = e / (2 * P), c = e % (2 * P);
+    const int slot = c < P ? c : 64 + c;
+    ex[u] = e < 2 * P * R ? r * WX + slot : -1;
+    ox[u] = e < 2 * P * R ? row_off(I0 - P + slot, cy * P + R0 + r) : OFF_OUT;
+  }
   double kx[BW];
 #pragma unroll
-  for (int d = 0; d < BW; ++d) kx[d] = ilive ? kb[(int64_t)I * BW + d] : 0.0;
-  const double mI = ilive ? m[I] : 0.0;
-  // this wave's rows (wave-uniform)
-  int Jr[RY];
-  bool live[RY];
-  double mJ[RY];
-#pragma unroll
-  for (int r = 0; r < RY; ++r) {
-    Jr[r] = J0 + w * RY + r;
-    live[r] = ilive && Jr[r] < n;
-    mJ[r] = Jr[r] < n ? m[Jr[r]] : 0.0;
-  }
-  // z-windows: x(I, J_r, K - P .. K + P), zero outside the mesh (Dirichlet)
-  double win[RY][BW];
-#pragma unroll
-  for (int r = 0; r < RY; ++r) {
-    const int64_t col = (int64_t)I + (int64_t)n * Jr[r];
-#pragma unroll
-    for (int d = 0; d < BW; ++d) {
-      const int k = K0 - P + d - 1;                // shifted in at the first plane
-      win[r][d] = (live[r] && k >= 0 && k < n) ? x[col + k * n2] : 0.0;
-    }
-  }
-  // the plane tiles are loaded into registers PD planes ahead, in PD sets
-  // used in turn (their latency hides behind PD planes of sums), then stored
-  // to LDS
-  double treg[PD][NTL];
-  double wnext[PD][RY];
-  auto load_plane = [&](int K, double(&tr)[NTL], double(&wn)[RY]) {
-#pragma unroll
-    for (int u = 0; u < NTL; ++u) {
-      const int e = threadIdx.x + u * PB;
-      const int rr = e / WX, cc = e - rr * WX;
-      const int i = I0 - P + cc, j = J0 - P + rr;
-      tr[u] = (e < WY * WX && i >= 0 && i < n && j >= 0 && j < n) ? x[(int64_t)i + (int64_t)n * j + K * n2] : 0.0;
-    }
-    const int k = K + P;
-#pragma unroll
-    for (int r = 0; r < RY; ++r)
-      wn[r] = (live[r] && k < n) ? x[(int64_t)I + (int64_t)n * Jr[r] + k * n2] : 0.0;
+  for (int d = 0; d < BW; ++d) kx[d] = ilive ? kbs[(int64_t)I * BW + d] : 0.0;
+  const double wI = ilive ? s * m[I] : 0.0;
+  auto plane_of = [&](const double *v, int node) {  // the plane of a node, empty outside the mesh
+    const bool in = node >= 1 && node <= n;
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<double *>(v + (int64_t)(in ? node - 1 : 0) * n * n), 0,
+                                             in ? (int)pbytes : 0, 0x00020000);
   };
+  auto ld = [&](__amdgpu_buffer_rsrc_t r, unsigned off) {
+    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
+  };
+  double acc[P + 1][R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) acc[P][r] = 0;
+  double vn[P + 1], ln[P], xn[HL];                 // the plane ahead
+  auto fetch = [&](int node) {
+    const auto rp = plane_of(x, node);
+#pragma unroll
+    for (int r = 0; r <= P; ++r) vn[r] = ld(rp, oo[r]);
+    if constexpr (LOW) {
+#pragma unroll
+      for (int r = 0; r < P; ++r) ln[r] = ld(rp, ol[r]);
+    }
+#pragma unroll
+    for (int u = 0; u < HL; ++u) xn[u] = ld(rp, ox[u]);
+  };
+  fetch(L0 * P);
+  // what the layer before owes the first plane
+  if (L0 > 0) {
+    double pv[P][R];
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+      const auto rp = plane_of(x, (L0 - 1) * P + k);
+#pragma unroll
+      for (int r = 0; r < R; ++r) pv[k][r] = ld(rp, oo[R0 + r]);
+    }
+#pragma unroll
+    for (int k = 0; k < P; ++k)
+#pragma unroll
+      for (int r = 0; r < R; ++r) acc[P][r] = __builtin_fma(T(P, k), pv[k][r], acc[P][r]);
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) asm volatile("" : "+v"(acc[P][r]));
   double dot = 0;
-  const int K1 = min(K0 + KB, n);
-  // plane K from the set (tr, wn), which then receives plane K + PD
-  auto plane = [&](int K, double(&tr)[NTL], double(&wn)[RY]) {
-    __syncthreads();                               // previous plane's tile consumed
+#pragma unroll 1
+  for (int L = L0; L < L1; ++L) {
 #pragma unroll
-    for (int u = 0; u < NTL; ++u) {
-      const int e = threadIdx.x + u * PB;
-      if (e < WY * WX) xs[e / WX][e % WX] = tr[u];
-    }
+    for (int k = 0; k < P; ++k) {
+      double v[P + 1], ty[R];
 #pragma unroll
-    for (int r = 0; r < RY; ++r) {
+      for (int r = 0; r <= P; ++r) v[r] = vn[r];
 #pragma unroll
-      for (int d = 0; d < BW - 1; ++d) win[r][d] = win[r][d + 1];
-      win[r][BW - 1] = wn[r];
-    }
-    __syncthreads();
-    if (K + PD < K1) load_plane(K + PD, tr, wn);
-    const double *kz = kb + (int64_t)K * BW;
-    const double mK = m[K];
-    double colv[RY + 2 * P];
+      for (int r = 0; r < R; ++r) st[r * WX + P + lane] = v[R0 + r];
+      if constexpr (LOW) {
+        ty[0] = T(0, 0) * v[0];                    // the cell before: its last row is this vertex row
 #pragma unroll
-    for (int i = 0; i < RY + 2 * P; ++i) colv[i] = xs[w * RY + i][lane + P];
-#pragma unroll
-    for (int r = 0; r < RY; ++r) {
-      if (!live[r]) continue;
-      const double *ky = kb + (int64_t)Jr[r] * BW;
-      double sx = 0, sy = 0, sz = 0;
-#pragma unroll
-      for (int d = 0; d < BW; ++d) {
-        sx += kx[d] * xs[w * RY + r + P][lane + d];
-        sy += ky[d] * colv[r + d];
-        sz += kz[d] * win[r][d];
+        for (int d = 0; d < P; ++d) ty[0] = __builtin_fma(T(P, d), ln[d], ty[0]);
       }
-      const double v = s * (mJ[r] * mK * sx + mI * mK * sy + mI * mJ[r] * sz);
-      y[(int64_t)I + (int64_t)n * Jr[r] + K * n2] = v;
-      if constexpr (DOT) dot += win[r][P] * v;
-    }
-  };
 #pragma unroll
-  for (int d = 0; d < PD; ++d)
-    if (K0 + d < K1) load_plane(K0 + d, treg[d], wnext[d]);
-  int K = K0;
-  if constexpr (PD == 2) {
-    // pairs in the loop (no branch between the halves), an odd last plane after it
-    for (; K + 1 < K1; K += 2) {
-      plane(K, treg[0], wnext[0]);
-      plane(K + 1, treg[1], wnext[1]);
+      for (int u = 0; u < HL; ++u)
+        if (ex[u] >= 0) st[ex[u]] = xn[u];
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      fetch(L * P + k + 1);
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int d = 0; d <= P; ++d)
+          ty[r] = d == 0 && !(LOW && r == 0) ? T(R0 + r, d) * v[d] : __builtin_fma(T(R0 + r, d), v[d], ty[r]);
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        double tx = kx[P] * v[R0 + r];
+#pragma unroll
+        for (int d = 0; d < BW; ++d)
+          if (d != P) tx = __builtin_fma(kx[d], st[r * WX + lane + d], tx);
+        const double t = tx + ty[r], vr = v[R0 + r];
+        if (k == 0) {
+          acc[0][r] = __builtin_fma(2.0 * T(0, 0), vr, acc[P][r] + t);
+#pragma unroll
+          for (int l = 1; l <= P; ++l) acc[l][r] = T(l, 0) * vr;
+        } else {
+#pragma unroll
+          for (int l = 0; l <= P; ++l) acc[l][r] = __builtin_fma(T(l, k), vr, l == k ? acc[l][r] + t : acc[l][r]);
+        }
+      }
+      // the sums are formed here, not put off to their use at the layer's end
+      // (which would keep every operand until then)
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int l = 0; l <= P; ++l) asm volatile("" : "+v"(acc[l][r]));
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_sched_barrier(0);
     }
-    if (K < K1) plane(K, treg[0], wnext[0]);
-  } else {
-    for (; K < K1; ++K) plane(K, treg[0], wnext[0]);
+    // the layer's planes are complete with the first plane of the next, in vn
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+      const int node = L * P + k;
+      const auto ry = plane_of(y, node), rp = plane_of(x, node);
+      const double wK = node >= 1 ? wI * m[node - 1] : 0.0;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int jn = cy * P + R0 + r;
+        const double wJ = live && jn >= 1 ? m[jn - 1] : 0.0;
+        const double q = wK * wJ * __builtin_fma(T(k, P), vn[R0 + r], acc[k][r]);
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2_t, q), ry, (int)oo[R0 + r], 0, 0);
+        if constexpr (DOT) dot = __builtin_fma(ld(rp, oo[R0 + r]), q, dot);
+      }
+    }
   }
+  return dot;
+}
+
+template <int P, bool DOT>
+__global__ __launch_bounds__(PB, 2) void poisson_stencil_kernel(const double *__restrict__ x, double *__restrict__ y,
+                                                                const double *__restrict__ kbs,
+                                                                const double *__restrict__ m, CellTable<P> T, int n,
+                                                                int n_el, int zl, double s,
+                                                                const double *__restrict__ scal, int it,
+                                                                double *__restrict__ part) {
+  typedef StencilSplit<P> SP;
+  __shared__ double sh[PB / 64];
+  __shared__ double strip[4][SP::RM][64 + 2 * P];
+  if (DOT && it >= scal[S_STOPAT]) return;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // XCD-grouped block order: the hardware deals consecutive work-groups to the
+  // 8 XCDs in turn; the logical index below is contiguous per XCD
+  const int g = (int)gridDim.x, b = (int)blockIdx.x;
+  const int lid = (b & 7) * (g >> 3) + min(b & 7, g & 7) + (b >> 3);
+  const int gx = (n + 63) / 64, gy = (n_el + SP::CELLS - 1) / SP::CELLS;
+  const int I0 = lid % gx * 64, cy = lid / gx % gy * SP::CELLS + w / SP::H, L0 = lid / (gx * gy) * zl;
+  const int L1 = min(L0 + zl, n_el);
+  double dot;
+  if (SP::H == 1 || (w & 1) == 0)
+    dot = stencil_march<P, 0, SP::RM, DOT>(x, y, kbs, m, T, n, n_el, s, I0, cy, L0, L1, &strip[w][0][0]);
+  else
+    dot = stencil_march<P, SP::RM % P, P, DOT>(x, y, kbs, m, T, n, n_el, s, I0, cy, L0, L1, &strip[w][0][0]);
   if constexpr (DOT) {
     const double bsum = block_sum(dot, sh);
     if (threadIdx.x == 0) part[blockIdx.x] = bsum;
   }
 }
 
-// The two vector passes run by rows of the mesh: wave w of work-group b
-// takes the 64 consecutive I of its I-chunk in VR consecutive rows (J, K), so
-// the J- and K-dependent factors of diag(A) are wave-uniform and each lane
-// keeps its I-dependent ones.  The loads of the partials a pass sums are
-// issued first, then all of the rows' loads, so the global sum is formed
-// while the rows are in flight.
-constexpr int VR = 16;
+// The two vector passes run over the values in memory order, VU per thread 256
+// apart: every lane works whatever n is.  The loads of the partials a pass sums
+// are issued first, then all of its values', so the global sum is formed while
+// they are in flight.
+constexpr int VU = 8;
 constexpr int PU = 4;   // partials per thread loaded ahead (the rest, if any, after)
-static dim3 vec_grid(int n) {
-  const int64_t rows = (int64_t)n * n;
-  return dim3((unsigned)(((n + 63) / 64) * ((rows + 4 * VR - 1) / (4 * VR))));
-}
-struct VecPos {
-  int I;           // this lane's node index along x
-  int row0;        // first row of the wave's run (row = J + n K < n^2 < 2^31)
-  int J0, K0;      // its J and K (wave-uniform)
-  bool ilive;
+static dim3 vec_grid(int64_t nd) { return dim3((unsigned)((nd + PB * VU - 1) / (PB * VU))); }
+// (I, J, K) of a value, and of the one 256 further on
+struct NodePos {
+  int I, J, K;
+  __device__ __forceinline__ NodePos(int64_t base, int off, int n) {
+    const int64_t row = base / n;                  // wave-uniform
+    const int i = (int)(base - row * n) + off, j = i / n;
+    I = i - j * n;
+    K = (int)(row / n);
+    J = (int)(row - (int64_t)K * n) + j;
+    wrap(n);
+  }
+  __device__ __forceinline__ void wrap(int n) {
+    if (J >= n) {
+      const int k = J / n;
+      K += k;
+      J -= k * n;
+    }
+  }
+  __device__ __forceinline__ void advance(int n, int dI, int dJ) {
+    I += dI;
+    J += dJ;
+    if (I >= n) {
+      I -= n;
+      ++J;
+    }
+    wrap(n);
+  }
 };
-__device__ __forceinline__ VecPos vec_pos(int n) {
-  const int gx = (n + 63) / 64;
-  const int b = (int)blockIdx.x;
-  const int bx = b % gx, br = b / gx;
-  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  VecPos v;
-  v.I = bx * 64 + ((int)threadIdx.x & 63);
-  v.row0 = (br * 4 + w) * VR;
-  v.K0 = v.row0 / n;
-  v.J0 = v.row0 - v.K0 * n;
-  v.ilive = v.I < n;
-  return v;
-}
-// z = r / diag(A) at (I, J, K): the lane's I factors and the row's J, K ones
-__device__ __forceinline__ double jacobi_z(double rv, double kdI, double mI, double kdJ, double mJ, double kdK,
-                                           double mK, double s) {
-  return __dmul_rn(rv, 1.0 / (s * (kdI * mJ * mK + mI * kdJ * mK + mI * mJ * kdK)));
+// diag(A) at (I, J, K): s m_I m_J m_K (a_I + a_J + a_K), a = k_II / m_I after m
+__device__ __forceinline__ double diag_at(const double *m, int n, double s, int I, int J, int K) {
+  const double *a = m + n;
+  return s * m[I] * m[J] * m[K] * (a[I] + a[J] + a[K]);
 }
 // Sum of a[0 .. na) in a fixed order, in two steps: parts_load issues the
 // thread's first PU loads, parts_sum adds them, then the rest, then sums over
@@ -267,53 +342,51 @@ __device__ __forceinline__ double parts_sum(const double *__restrict__ a, int na
 }
 
 // Iteration it: alpha = r.z / p.q from the product's partials (work-group 0
-// keeps it for the direction pass); r -= alpha q; partials of r.z
-// (z = r / diag(A)) and r.r.
-__global__ __launch_bounds__(PB) void poisson_update_kernel(double *__restrict__ r, const double *__restrict__ q,
-                                                            const double *__restrict__ kb,
-                                                            const double *__restrict__ m, int n, int p, double s,
+// keeps it for the direction pass); z -= alpha q / diag(A), the residual r =
+// diag(A) z not being stored; partials of r.z and r.r.
+__global__ __launch_bounds__(PB) void poisson_update_kernel(double *__restrict__ z, const double *__restrict__ q,
+                                                            const double *__restrict__ m, int n, int64_t nd, double s,
                                                             double *__restrict__ scal, int it,
                                                             const double *__restrict__ part_pq, int npq,
                                                             double *__restrict__ part_rz, double *__restrict__ part_rr) {
+  extern __shared__ double mt[];                   // m and a
   __shared__ double sh[PB / 64];
   if (it >= scal[S_STOPAT]) return;
   double pp[PU];
   parts_load(part_pq, npq, pp);
-  const int bw = 2 * p + 1;
-  const int64_t rows = (int64_t)n * n;
-  const VecPos vp = vec_pos(n);
-  const double kdI = vp.ilive ? kb[(int64_t)vp.I * bw + p] : 0.0, mI = vp.ilive ? m[vp.I] : 0.0;
-  double rv[VR], qv[VR];
+  for (int i = (int)threadIdx.x; i < 2 * n; i += PB) mt[i] = m[i];
+  const int64_t base = (int64_t)blockIdx.x * (PB * VU);
+  const int left = nd - base < PB * VU ? (int)(nd - base) : PB * VU;
+  double *zb = z + base;
+  const double *qb = q + base;
+  double zv[VU], qv[VU];
 #pragma unroll
-  for (int u = 0; u < VR; ++u) {
-    const int64_t row = vp.row0 + u;
-    const bool ok = vp.ilive && row < rows;
-    const int64_t idx = vp.I + n * row;
-    rv[u] = ok ? r[idx] : 0.0;
-    qv[u] = ok ? q[idx] : 0.0;
+  for (int u = 0; u < VU; ++u) {
+    const int e = (int)threadIdx.x + PB * u;
+    zv[u] = e < left ? zb[e] : 0.0;
+    qv[u] = e < left ? qb[e] : 0.0;
   }
+  NodePos at(base, (int)threadIdx.x, n);
+  const int dJ = PB / n, dI = PB - dJ * n;
   const double pq = parts_sum(part_pq, npq, pp, sh);
   const double alpha = pq != 0 ? scal[S_RZ + (it & 1)] / pq : 0.0;
   if (blockIdx.x == 0 && threadIdx.x == 0) scal[S_ALPHA] = alpha;
   double rz = 0, rr = 0;
-  int J = vp.J0, K = vp.K0;
 #pragma unroll
-  for (int u = 0; u < VR; ++u, ++J) {
-    const int64_t row = vp.row0 + u;
-    if (row >= rows) break;                         // wave-uniform
-    if (J == n) {
-      J = 0;
-      ++K;
+  for (int u = 0; u < VU; ++u) {
+    const int e = (int)threadIdx.x + PB * u;
+    if (e < left) {
+      const double d = diag_at(mt, n, s, at.I, at.J, at.K);
+      // 1 / d to an ulp: the hardware estimate and two Newton steps
+      double y = __builtin_amdgcn_rcp(d);
+      y = fma(fma(-d, y, 1.0), y, y);
+      y = fma(fma(-d, y, 1.0), y, y);
+      const double v = zv[u] - alpha * (qv[u] * y), r = d * v;
+      zb[e] = v;
+      rz += r * v;
+      rr += r * r;
     }
-    const double kdJ = kb[(int64_t)J * bw + p], mJ = m[J], kdK = kb[(int64_t)K * bw + p], mK = m[K];
-    if (vp.ilive) {
-      const int64_t idx = vp.I + n * row;
-      const double v = rv[u] - alpha * qv[u];
-      r[idx] = v;
-      const double zv = jacobi_z(v, kdI, mI, kdJ, mJ, kdK, mK, s);
-      rz += v * zv;
-      rr += v * v;
-    }
+    at.advance(n, dI, dJ);
   }
   const double a = block_sum(rz, sh);
   const double b = block_sum(rr, sh);
@@ -324,13 +397,11 @@ __global__ __launch_bounds__(PB) void poisson_update_kernel(double *__restrict__
 }
 
 // Iteration it: r.z' and r.r from the update's partials; x += alpha p (the
-// update's alpha); unless r.r meets the tolerance, p = z + beta p with
-// z = r / diag(A), beta = r.z' / r.z.  Work-group 0 keeps r.z' (the other
-// parity slot), r.r, and the iteration count once the tolerance is met.
+// update's alpha); unless r.r meets the tolerance, p = z + beta p, beta = r.z' /
+// r.z.  Work-group 0 keeps r.z' (the other parity slot), r.r, and the iteration
+// count once the tolerance is met.
 __global__ __launch_bounds__(PB) void poisson_dir_kernel(double *__restrict__ x, double *__restrict__ pv,
-                                                         const double *__restrict__ r,
-                                                         const double *__restrict__ kb,
-                                                         const double *__restrict__ m, int n, int p, double s,
+                                                         const double *__restrict__ z, int64_t nd,
                                                          double *__restrict__ scal, int it,
                                                          const double *__restrict__ part_rz,
                                                          const double *__restrict__ part_rr, int nparts) {
@@ -340,26 +411,24 @@ __global__ __launch_bounds__(PB) void poisson_dir_kernel(double *__restrict__ x,
   parts_load(part_rz, nparts, pz);
   parts_load(part_rr, nparts, pr);
   const double alpha = scal[S_ALPHA], rz_old = scal[S_RZ + (it & 1)], stop = scal[S_STOP];
-  const int bw = 2 * p + 1;
-  const int64_t rows = (int64_t)n * n;
-  const VecPos vp = vec_pos(n);
-  const double kdI = vp.ilive ? kb[(int64_t)vp.I * bw + p] : 0.0, mI = vp.ilive ? m[vp.I] : 0.0;
-  double pw[VR], rw[VR];
+  const int64_t base = (int64_t)blockIdx.x * (PB * VU);
+  const int left = nd - base < PB * VU ? (int)(nd - base) : PB * VU;
+  double *xb = x + base, *pb = pv + base;
+  const double *zb = z + base;
+  double pw[VU], zw[VU];
   {
-    double xw[VR];
+    double xw[VU];
 #pragma unroll
-    for (int u = 0; u < VR; ++u) {
-      const int64_t row = vp.row0 + u;
-      const bool ok = vp.ilive && row < rows;
-      const int64_t idx = vp.I + n * row;
-      pw[u] = ok ? pv[idx] : 0.0;
-      xw[u] = ok ? x[idx] : 0.0;
-      rw[u] = ok ? r[idx] : 0.0;
+    for (int u = 0; u < VU; ++u) {
+      const int e = (int)threadIdx.x + PB * u;
+      pw[u] = e < left ? pb[e] : 0.0;
+      xw[u] = e < left ? xb[e] : 0.0;
+      zw[u] = e < left ? zb[e] : 0.0;
     }
 #pragma unroll
-    for (int u = 0; u < VR; ++u) {
-      const int64_t row = vp.row0 + u;
-      if (vp.ilive && row < rows) x[vp.I + n * row] = fma(alpha, pw[u], xw[u]);
+    for (int u = 0; u < VU; ++u) {
+      const int e = (int)threadIdx.x + PB * u;
+      if (e < left) xb[e] = fma(alpha, pw[u], xw[u]);
     }
   }
   const double rz = parts_sum(part_rz, nparts, pz, sh);
@@ -372,41 +441,29 @@ __global__ __launch_bounds__(PB) void poisson_dir_kernel(double *__restrict__ x,
   }
   if (last) return;
   const double beta = rz_old != 0 ? rz / rz_old : 0.0;
-  int J = vp.J0, K = vp.K0;
 #pragma unroll
-  for (int u = 0; u < VR; ++u, ++J) {
-    const int64_t row = vp.row0 + u;
-    if (row >= rows) break;                         // wave-uniform
-    if (J == n) {
-      J = 0;
-      ++K;
-    }
-    if (vp.ilive) {
-      const double zv = jacobi_z(rw[u], kdI, mI, kb[(int64_t)J * bw + p], m[J], kb[(int64_t)K * bw + p], m[K], s);
-      pv[vp.I + n * row] = fma(beta, pw[u], zv);
-    }
+  for (int u = 0; u < VU; ++u) {
+    const int e = (int)threadIdx.x + PB * u;
+    if (e < left) pb[e] = fma(beta, pw[u], zw[u]);
   }
 }
 
-// Setup: r = f - A x (q = A x given), p = z = r / diag(A); partials of r.z,
-// r.r and f.f.
+// Setup: r = f - A x (q = A x given), z = p = r / diag(A); partials of r.z, r.r
+// and f.f.
 __global__ __launch_bounds__(PB) void poisson_init_kernel(const double *__restrict__ f, const double *__restrict__ q,
-                                                          double *__restrict__ r, double *__restrict__ pv,
-                                                          const double *__restrict__ kb,
-                                                          const double *__restrict__ m, int n, int p, double s,
+                                                          double *__restrict__ z, double *__restrict__ pv,
+                                                          const double *__restrict__ m, int n, double s,
                                                           double *__restrict__ part_rz, double *__restrict__ part_rr,
                                                           double *__restrict__ part_ff) {
   __shared__ double sh[PB];
   const int64_t nd = (int64_t)n * n * n;
-  const int bw = 2 * p + 1;
   double rz = 0, rr = 0, ff = 0;
   for (int64_t idx = (int64_t)blockIdx.x * PB + threadIdx.x; idx < nd; idx += (int64_t)gridDim.x * PB) {
     const double fv = f[idx];
     const double rv = fv - q[idx];
     const int I = (int)(idx % n), J = (int)((idx / n) % n), K = (int)(idx / ((int64_t)n * n));
-    const double zv = jacobi_z(rv, kb[(int64_t)I * bw + p], m[I], kb[(int64_t)J * bw + p], m[J],
-                               kb[(int64_t)K * bw + p], m[K], s);
-    r[idx] = rv;
+    const double zv = rv / diag_at(m, n, s, I, J, K);
+    z[idx] = zv;
     pv[idx] = zv;
     rz += rv * zv;
     rr += rv * rv;
@@ -478,13 +535,14 @@ static void poisson_tables(const MeshTables &M, std::vector<double> &kb, std::ve
       mm[e * p + a] += (M.h / 2.0) * M.w[a];
       for (int b = 0; b < q; ++b) K[(size_t)(e * p + a) * n1 + (e * p + b)] += (2.0 / M.h) * M.K1[(size_t)a * q + b];
     }
-  kb.assign((size_t)n * bw, 0.0);
-  m1.resize(n);
+  kb.assign((size_t)n * bw, 0.0);                  // the band over the row's mass
+  m1.resize(2 * (size_t)n);                        // the mass, then the band's diagonal over it
   for (int i = 0; i < n; ++i) {
     m1[i] = mm[i + 1];
+    m1[n + i] = K[(size_t)(i + 1) * n1 + (i + 1)] / m1[i];
     for (int d = -p; d <= p; ++d) {
       const int j = i + d;
-      if (j >= 0 && j < n) kb[(size_t)i * bw + d + p] = K[(size_t)(i + 1) * n1 + (j + 1)];
+      if (j >= 0 && j < n) kb[(size_t)i * bw + d + p] = K[(size_t)(i + 1) * n1 + (j + 1)] / m1[i];
     }
   }
 }
@@ -497,14 +555,12 @@ static int poisson_ready(chfsi_ctx *c) {
     return fail(c, CHFSI_ERR_STATE, "poisson: the periodic cell needs a neutral charge (not supported)");
   if (int r = set_dev(c)) return r;
   const MeshTables &M = c->mesh;
-  const size_t bw = 2 * M.p + 1;
   if (c->pois_n != M.n || c->pois_p != M.p || c->pois_h != M.h) {
     std::vector<double> kb, m1;
     poisson_tables(M, kb, m1);
     HIPCHK(c, c->pois_kb.ensure(kb.size() * sizeof(double)));
     HIPCHK(c, c->pois_m.ensure(m1.size() * sizeof(double)));
-    HIPCHK(c, hipMemcpyAsync(c->pois_kb.p, kb.data(), (size_t)M.n * bw * sizeof(double), hipMemcpyHostToDevice,
-                             c->stream));
+    HIPCHK(c, hipMemcpyAsync(c->pois_kb.p, kb.data(), kb.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(c->pois_m.p, m1.data(), m1.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     c->pois_n = M.n;
@@ -516,33 +572,50 @@ static int poisson_ready(chfsi_ctx *c) {
 
 static const double kInv4Pi = 0.25 / 3.14159265358979323846;
 
-// stencil tile: rows per wave, planes per work-group, planes loaded ahead
-// (measured at the 143^3 and 159^3 interior meshes)
-constexpr int POIS_RY = 2, POIS_KB = 8, POIS_PD = 1;
-
-static dim3 apply_grid(int n) {
-  constexpr int TY = 4 * POIS_RY;
-  return dim3((unsigned)((n + TX - 1) / TX) * ((n + TY - 1) / TY) * ((n + POIS_KB - 1) / POIS_KB));
+// Work-groups of the stencil at zl cell layers each.  Two layers save the reads
+// of the one before (24^3 cells of degree 6: 19.6 against 21.1 us; 32^3 of degree
+// 5: 19.4 against 21.4) where that leaves 400 work-groups, the 256 CUs' worth and
+// some (20^3 of degree 7, 300: 28.3 against 27.0; 12^3 of degree 6: 12.1 against
+// 8.0).
+static int64_t stencil_groups(int n, int n_el, int p, int zl) {
+  const int cells = p < 4 ? StencilSplit<1>::CELLS : StencilSplit<4>::CELLS;
+  return (int64_t)((n + 63) / 64) * ((n_el + cells - 1) / cells) * ((n_el + zl - 1) / zl);
+}
+static int stencil_zl(int n, int n_el, int p) { return stencil_groups(n, n_el, p, 2) >= 400 ? 2 : 1; }
+static dim3 apply_grid(const MeshTables &M) {
+  return dim3((unsigned)stencil_groups(M.n, M.n_el, M.p, stencil_zl(M.n, M.n_el, M.p)));
 }
 
 // y = A x; with part (and scal, it): the partials of x . y for iteration it
 // (skipped once the solve has stopped).  -1 for an unsupported degree.
-static int poisson_stencil_launch(const MeshTables &M, const double *x, double *y, const double *kb, const double *m,
+template <int P>
+static void poisson_stencil_go(const MeshTables &M, const double *x, double *y, const double *kbs, const double *m,
+                               const double *scal, int it, double *part, hipStream_t s) {
+  CellTable<P> T;
+  for (int i = 0; i < CellTable<P>::N; ++i) {
+    const int k = i / (P + 1), l = i % (P + 1);
+    const double mass = (M.h / 2.0) * (k == 0 || k == P ? M.w[0] + M.w[P] : M.w[k]);
+    T.t[i] = (2.0 / M.h) * M.K1[(size_t)k * (P + 1) + l] / mass;
+  }
+  const dim3 g = apply_grid(M), b(PB);
+  const int zl = stencil_zl(M.n, M.n_el, M.p);
+  if (part)
+    hipLaunchKernelGGL((poisson_stencil_kernel<P, true>), g, b, 0, s, x, y, kbs, m, T, M.n, M.n_el, zl, kInv4Pi, scal,
+                       it, part);
+  else
+    hipLaunchKernelGGL((poisson_stencil_kernel<P, false>), g, b, 0, s, x, y, kbs, m, T, M.n, M.n_el, zl, kInv4Pi,
+                       nullptr, 0, nullptr);
+}
+static int poisson_stencil_launch(const MeshTables &M, const double *x, double *y, const double *kbs, const double *m,
                                   const double *scal, int it, double *part, hipStream_t s) {
-  const dim3 g = apply_grid(M.n), b(PB);
   switch (M.p) {
-#define CHFSI_POIS_P(P)                                                                                        \
-  case P:                                                                                                      \
-    if (part)                                                                                                  \
-      hipLaunchKernelGGL((poisson_stencil_kernel<P, POIS_RY, POIS_KB, POIS_PD, true>), g, b, 0, s, x, y, kb, m, M.n,       \
-                         kInv4Pi, scal, it, part);                                                                 \
-    else                                                                                                       \
-      hipLaunchKernelGGL((poisson_stencil_kernel<P, POIS_RY, POIS_KB, POIS_PD, false>), g, b, 0, s, x, y, kb, m, M.n,      \
-                         kInv4Pi, nullptr, 0, nullptr);                                                           \
-    return 0;
-    CHFSI_POIS_P(1) CHFSI_POIS_P(2) CHFSI_POIS_P(3) CHFSI_POIS_P(4) CHFSI_POIS_P(5) CHFSI_POIS_P(6)
-    CHFSI_POIS_P(7)
-#undef CHFSI_POIS_P
+    case 1: poisson_stencil_go<1>(M, x, y, kbs, m, scal, it, part, s); return 0;
+    case 2: poisson_stencil_go<2>(M, x, y, kbs, m, scal, it, part, s); return 0;
+    case 3: poisson_stencil_go<3>(M, x, y, kbs, m, scal, it, part, s); return 0;
+    case 4: poisson_stencil_go<4>(M, x, y, kbs, m, scal, it, part, s); return 0;
+    case 5: poisson_stencil_go<5>(M, x, y, kbs, m, scal, it, part, s); return 0;
+    case 6: poisson_stencil_go<6>(M, x, y, kbs, m, scal, it, part, s); return 0;
+    case 7: poisson_stencil_go<7>(M, x, y, kbs, m, scal, it, part, s); return 0;
     default: return -1;
   }
 }
@@ -578,15 +651,15 @@ extern "C" int chfsi_poisson_solve(chfsi_ctx *c, const double *rho, int ncharges
     qmap[charge_dofs[i]] += charges[i];
   }
   const int64_t nb = std::min<int64_t>((nd + PB - 1) / PB, MAXG);   // element-wise grids (grid-stride)
-  const int64_t nv = vec_grid(M.n).x;                // the two vector passes
-  const dim3 ga = apply_grid(M.n);
+  const int64_t nv = vec_grid(nd).x;                 // the two vector passes
+  const dim3 ga = apply_grid(M);
   const int64_t na = (int64_t)ga.x * ga.y * ga.z;  // product grid
   const int64_t npart = std::max(std::max(nb, na), nv);
-  // workspace: f, r, p, q (nd each), partials (3 npart), scalars
+  // workspace: f, z, p, q (nd each), partials (3 npart), scalars
   HIPCHK(c, c->pois_work.ensure((size_t)(4 * nd + 3 * npart + S_NSCAL) * sizeof(double)));
-  double *f = c->pois_work.as<double>(), *r = f + nd, *pv = r + nd, *q = pv + nd;
+  double *f = c->pois_work.as<double>(), *z = f + nd, *pv = z + nd, *q = pv + nd;
   double *pa = q + nd, *pb = pa + npart, *pc = pb + npart, *scal = pc + npart;
-  const double *kb = c->pois_kb.as<double>(), *m = c->pois_m.as<double>();
+  const double *kbs = c->pois_kb.as<double>(), *m = c->pois_m.as<double>();
   const dim3 grid((unsigned)nb), block(PB);
   hipStream_t s = c->stream;
   hipLaunchKernelGGL(poisson_rhs_kernel, grid, block, 0, s, rho, c->minv64.as<double>(), f, nd);
@@ -606,8 +679,8 @@ extern "C" int chfsi_poisson_solve(chfsi_ctx *c, const double *rho, int ncharges
                        (int)qd.size());
     HIPCHK(c, hipStreamSynchronize(s));            // the host staging vectors go out of scope
   }
-  poisson_stencil_launch(M, phi, q, kb, m, nullptr, 0, nullptr, s);
-  hipLaunchKernelGGL(poisson_init_kernel, grid, block, 0, s, f, q, r, pv, kb, m, M.n, M.p, kInv4Pi, pa, pb, pc);
+  poisson_stencil_launch(M, phi, q, kbs, m, nullptr, 0, nullptr, s);
+  hipLaunchKernelGGL(poisson_init_kernel, grid, block, 0, s, f, q, z, pv, m, M.n, kInv4Pi, pa, pb, pc);
   hipLaunchKernelGGL(poisson_setup_reduce_kernel, dim3(1), dim3(PR), 0, s, pa, pb, pc, (int)nb, tol * tol, scal);
   // iterations in groups; the device records the iteration that met the
   // tolerance, the host reads it between groups (a group started after the
@@ -618,11 +691,11 @@ extern "C" int chfsi_poisson_solve(chfsi_ctx *c, const double *rho, int ncharges
   while (launched < max_iter) {
     const int k = std::min(GROUP, max_iter - launched);
     for (int i = 0; i < k; ++i, ++launched) {
-      poisson_stencil_launch(M, pv, q, kb, m, scal, launched, pc, s);
-      hipLaunchKernelGGL(poisson_update_kernel, dim3((unsigned)nv), block, 0, s, r, q, kb, m, M.n, M.p, kInv4Pi, scal,
-                         launched, pc, (int)na, pa, pb);
-      hipLaunchKernelGGL(poisson_dir_kernel, dim3((unsigned)nv), block, 0, s, phi, pv, r, kb, m, M.n, M.p, kInv4Pi,
-                         scal, launched, pa, pb, (int)nv);
+      poisson_stencil_launch(M, pv, q, kbs, m, scal, launched, pc, s);
+      hipLaunchKernelGGL(poisson_update_kernel, dim3((unsigned)nv), block, 2 * M.n * sizeof(double), s, z, q, m, M.n, nd, kInv4Pi, scal, launched,
+                         pc, (int)na, pa, pb);
+      hipLaunchKernelGGL(poisson_dir_kernel, dim3((unsigned)nv), block, 0, s, phi, pv, z, nd, scal, launched, pa, pb,
+                         (int)nv);
     }
     HIPCHK(c, hipMemcpyAsync(hs, scal, sizeof(hs), hipMemcpyDeviceToHost, s));
     HIPCHK(c, hipStreamSynchronize(s));
@@ -632,8 +705,8 @@ extern "C" int chfsi_poisson_solve(chfsi_ctx *c, const double *rho, int ncharges
   HIPCHK(c, hipStreamSynchronize(s));
   const int it = hs[S_STOPAT] < launched ? (int)hs[S_STOPAT] : launched;
   // the true residual of the returned phi
-  poisson_stencil_launch(M, phi, q, kb, m, nullptr, 0, nullptr, s);
-  hipLaunchKernelGGL(poisson_init_kernel, grid, block, 0, s, f, q, r, pv, kb, m, M.n, M.p, kInv4Pi, pa, pb, pc);
+  poisson_stencil_launch(M, phi, q, kbs, m, nullptr, 0, nullptr, s);
+  hipLaunchKernelGGL(poisson_init_kernel, grid, block, 0, s, f, q, z, pv, m, M.n, kInv4Pi, pa, pb, pc);
   hipLaunchKernelGGL(poisson_setup_reduce_kernel, dim3(1), dim3(PR), 0, s, pa, pb, pc, (int)nb, tol * tol, scal);
   HIPCHK(c, hipMemcpyAsync(hs, scal, sizeof(hs), hipMemcpyDeviceToHost, s));
   HIPCHK(c, hipStreamSynchronize(s));
