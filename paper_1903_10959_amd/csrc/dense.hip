@@ -26,6 +26,8 @@
 
 namespace chfsi {
 
+static constexpr int GT = 128;  // output tile of the LDS gram kernel (4 waves x 64x64)
+
 // Resident work-groups of `kern` (256 threads) on the current device.
 template <typename K>
 static int resident_slots(K kern) {
@@ -130,22 +132,23 @@ __device__ __forceinline__ void gram_tile(const double *__restrict__ A, int64_t 
 }
 
 // G = A^T B over a split of the rows, lower triangle: one wave per 16F x 16F
-// lower tile, four tiles of one tile row (they share the columns of A in the
-// CU's cache) to a work-group, no LDS and no barriers.  The matrix cores bound
-// it: 64 clocks per FP64 fragment product against 2 / F loads, so that a small
-// tile costs no more than a large one and little is computed beyond the
-// triangle and the last column.
-// MODE 0: FP64.  MODE 1, mixed overlap: FP64 in the diagonal tiles, FP32
-// inputs and products in the rest.  MODE 2, split projected Hamiltonian: FP64
-// in the trailing block (rows and columns >= fr0), FP32 in the rest.
-// Grid: nsplit x ceil(ntl / NW) work-groups, ntl lower tiles.  FP32 products
-// take half the time, so those modes are bound by the columns: eight tiles to a
-// work-group (split, 970,299 x 360: 2.75 against 2.87 ms with four).
-template <int MODE, int F, int NW>
-__global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : F == 3 ? 3 : 2) void gram_kernel(const double *__restrict__ A, int64_t lda,
-                                                   const double *__restrict__ B, int64_t ldb, int64_t nrows, int n,
-                                                   int ntl, int64_t rows_per_split, int fr0,
-                                                   double *__restrict__ part) {
+// lower tile, NW tiles of one tile row (they share the columns of A in the CU's
+// cache) to a work-group, no LDS.  An FP64 fragment product takes the matrix
+// core 64 clocks against 2 / F loads, so that tiles can be small and little is
+// computed beyond the triangle and the last column; the columns that tiles of
+// one split share and the L2 no longer holds are the next bound (F = 2: slower
+// than F = 3).  857,375 rows, against 128 x 128 tiles by four waves through LDS:
+// n = 283, 2.74 -> 1.51 ms; n = 568, 7.4 -> 5.2 (53 TFLOP/s of what is asked, 73
+// the card's matrix rate); n = 1,128, 21.7 -> 19.7; mixed 568, 7.1 -> 5.0.
+// MIXED (the mixed overlap): FP64 in the diagonal tiles, FP32 inputs and
+// products in the rest.
+// Grid: nsplit x ceil(ntl / NW) work-groups, ntl lower tiles.
+template <bool MIXED, int F, int NW>
+__global__ __launch_bounds__(64 * NW, F == 3 ? 3 : 2) void gram_kernel(const double *__restrict__ A, int64_t lda,
+                                                                       const double *__restrict__ B, int64_t ldb,
+                                                                       int64_t nrows, int n, int ntl,
+                                                                       int64_t rows_per_split,
+                                                                       double *__restrict__ part) {
   constexpr int T = 16 * F;
   const int lane = threadIdx.x & 63, j = lane & 15, kq = lane >> 4;
   const int ngrid = (ntl + NW - 1) / NW;
@@ -184,8 +187,140 @@ __global__ __launch_bounds__(64 * NW, NW == 8 ? 2 : F == 3 ? 3 : 2) void gram_ke
 #pragma unroll
         for (int q = 0; q < 4; ++q) out[(a * 16 + acc_row<CT>(kq, q)) * T + b * 16 + j] = (double)acc[a][b][q];
   };
-  if (MODE == 0 || (MODE == 1 ? ti == tj : jb >= fr0)) run(double{});
+  if (!MIXED || ti == tj) run(double{});
   else run(float{});
+}
+
+// The split projected Hamiltonian, whose FP32 part is bound by the columns read
+// rather than the matrix cores: 128 x 128 tiles by four waves, so that a column
+// read serves 128 others (857,375 x 1,128: 14.5 ms against 16.6 in wave tiles;
+// 256: 1.31 against 1.70).
+// One (split, lower tile) work-group: partial G tile over rows [r0, r1).  The
+// contraction runs over chunks of 16 rows: the chunk's 128 columns of A and
+// of B are loaded into registers one chunk ahead (16-byte loads when the
+// leading dimensions are even), written to the other half of a
+// double-buffered LDS area after the chunk's MFMAs, and published by one
+// barrier per chunk.  Wave (wi, wj) owns the 64 x 64 quarter (wi, wj); on a
+// diagonal tile the strictly upper quarter is never read and is skipped.
+// FR false: every quarter outside the trailing block (rows and columns >=
+// fr0, fr0 a multiple of 64) with FP32 inputs and products, the chunk staged in
+// LDS already rounded to FP32.  FR true: the quarters inside it in FP64.
+// Grid: nsplit x ntl work-groups.  FR false: ntl = all lower tiles.  FR true:
+// the lower tiles of the trailing sub-triangle starting at tile row/column tf,
+// part indexed within it.
+template <int VEC, bool FR>
+__global__ __launch_bounds__(256) void gram_split_kernel(const double *__restrict__ A, int64_t lda,
+                                                   const double *__restrict__ B, int64_t ldb, int64_t nrows, int n,
+                                                   int ntl, int tf, int64_t rows_per_split, int fr0,
+                                                   double *__restrict__ part) {
+  typedef double vec_t __attribute__((ext_vector_type(VEC)));
+  typedef typename std::conditional<FR, double, float>::type CT;   // product type
+  typedef typename acc4<CT>::type acc_t;
+  typedef CT lds_vec_t __attribute__((ext_vector_type(VEC)));
+  constexpr int KR = sizeof(CT) == 4 ? 32 : 16;   // rows per chunk (FP32 chunks: same LDS bytes)
+  constexpr int PT = KR * GT / (256 * VEC);       // vectors per thread per operand
+  // staged in the product type: FP32 modes round once, at the LDS store
+  __shared__ __align__(16) CT As[2][KR][GT];
+  __shared__ __align__(16) CT Bs[2][KR][GT];
+  const int lid = xcd_grouped_block();
+  const int split = lid / ntl;
+  const int t = lid - split * ntl;                // part tile index
+  int ti, tj;
+  tri_tile(t, ti, tj);
+  ti += tf;
+  tj += tf;
+  const int tid = threadIdx.x;
+  const int wave = tid >> 6, lane = tid & 63;
+  const int wi = wave >> 1, wj = wave & 1;
+  const int j = lane & 15, kq = lane >> 4;
+  auto quarter_active = [&](int qi, int qj) {
+    // strictly upper quarters and quarters wholly past the last column are never read
+    const bool inside = ti * GT + qi * 64 < n && tj * GT + qj * 64 < n;
+    const bool lower = !(ti == tj && qi < qj);
+    const bool in_fr = ti * GT + qi * 64 >= fr0 && tj * GT + qj * 64 >= fr0;
+    return inside && lower && in_fr == FR;
+  };
+  if (!(quarter_active(0, 0) || quarter_active(1, 0) || quarter_active(0, 1) || quarter_active(1, 1)))
+    return;                                        // whole work-group idle
+  const bool active = quarter_active(wi, wj);
+  const int64_t r0 = (int64_t)split * rows_per_split;
+  int64_t r1 = r0 + rows_per_split;
+  if (r1 > nrows) r1 = nrows;
+  const int ib = ti * GT, jb = tj * GT;           // tile origin
+
+  vec_t areg[PT], breg[PT];
+  // slot v -> (row v / (GT/VEC), column vector v % (GT/VEC)); out-of-range
+  // slots load a clamped in-bounds address and store zero
+  auto load_chunk = [&](int64_t k0) {
+#pragma unroll
+    for (int i = 0; i < PT; ++i) {
+      const int v = tid + 256 * i;
+      const int64_t row = min(k0 + v / (GT / VEC), r1 - 1);
+      const int cv = (v % (GT / VEC)) * VEC;
+      areg[i] = *reinterpret_cast<const vec_t *>(A + row * lda + min(ib + cv, n - VEC));
+      breg[i] = *reinterpret_cast<const vec_t *>(B + row * ldb + min(jb + cv, n - VEC));
+    }
+  };
+  auto store_chunk = [&](int buf, int64_t k0) {
+#pragma unroll
+    for (int i = 0; i < PT; ++i) {
+      const int v = tid + 256 * i;
+      const int kr = v / (GT / VEC), cv = (v % (GT / VEC)) * VEC;
+      const bool rok = k0 + kr < r1;
+      lds_vec_t a, b;
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) {
+        a[e] = (rok && ib + cv + e < n) ? (CT)areg[i][e] : (CT)0;
+        b[e] = (rok && jb + cv + e < n) ? (CT)breg[i][e] : (CT)0;
+      }
+      *reinterpret_cast<lds_vec_t *>(&As[buf][kr][cv]) = a;
+      *reinterpret_cast<lds_vec_t *>(&Bs[buf][kr][cv]) = b;
+    }
+  };
+
+  acc_t acc[4][4];
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int b = 0; b < 4; ++b) acc[a][b] = acc_t{0, 0, 0, 0};
+  const int64_t nk = (r1 - r0 + KR - 1) / KR;
+  if (nk > 0) {
+    load_chunk(r0);
+    store_chunk(0, r0);
+  }
+  __syncthreads();
+#pragma unroll 1
+  for (int64_t kc = 0; kc < nk; ++kc) {
+    const int buf = (int)(kc & 1);
+    if (kc + 1 < nk) load_chunk(r0 + (kc + 1) * KR);
+    if (active) {
+#pragma unroll
+      for (int ks = 0; ks < KR; ks += 4) {
+        const int kk = ks + kq;
+        CT av[4], bv[4];
+#pragma unroll
+        for (int a = 0; a < 4; ++a) av[a] = As[buf][kk][wi * 64 + a * 16 + j];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) bv[b] = Bs[buf][kk][wj * 64 + b * 16 + j];
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+          for (int b = 0; b < 4; ++b) acc[a][b] = mfma16x4(av[a], bv[b], acc[a][b]);
+      }
+    }
+    if (kc + 1 < nk) store_chunk(buf ^ 1, r0 + (kc + 1) * KR);
+    __syncthreads();
+  }
+  if (!active) return;
+  double *out = part + ((int64_t)split * ntl + t) * (GT * GT) + (wi * 64) * GT + wj * 64;
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        out[(a * 16 + acc_row<CT>(kq, q)) * GT + b * 16 + j] = (double)acc[a][b][q];
+      }
 }
 
 // n <= 64: one 64 x 64 tile, so the tile kernel would leave three of its
@@ -249,23 +384,27 @@ __global__ __launch_bounds__(256) void gram_small_kernel(const double *__restric
   }
 }
 
-// G[i, j] = sum over splits of the partial gt x gt tiles, mirrored to the upper
-// triangle.  A work-group adds 32 entries, each by eight threads that take
-// every eighth split and are then added in order: one thread per entry left
-// the chip waiting on the serial chain over the splits (6 tiles x 341 splits:
-// 487 us; this: 38).
+// G[i, j] = sum over splits of the partial gt x gt tiles, for i >= j in the
+// region [r0, n) x [r0, n) (tiles numbered within the sub-triangle from tile
+// row tf), mirrored to the upper triangle.  skip0 >= 0: leave out the entries
+// with both i and j >= skip0 (written by another reduction).  A work-group
+// adds 32 entries, each by eight threads that take every eighth split and are
+// then added in order: one thread per entry left the chip waiting on the
+// serial chain over the splits (6 tiles x 341 splits: 487 us; this: 38).
 __global__ __launch_bounds__(256) void gram_reduce_kernel(const double *__restrict__ part, int nsplit, int ntl,
-                                                          int gt, int n, double *__restrict__ G) {
+                                                          int gt, int n, int tf, int r0, int skip0,
+                                                          double *__restrict__ G) {
   __shared__ double red[8][33];
-  const int64_t total = (int64_t)n * n;
+  const int m = n - r0;
+  const int64_t total = (int64_t)m * m;
   const int e = threadIdx.x & 31, sl = threadIdx.x >> 5;
   for (int64_t base = blockIdx.x * (int64_t)32; base < total; base += (int64_t)gridDim.x * 32) {
     const int64_t idx = base + e;
-    const int i = (int)(idx / n), jj = (int)(idx - idx / n * n);
-    const bool on = idx < total && jj <= i;
+    const int i = r0 + (int)(idx / m), jj = r0 + (int)(idx - idx / m * m);
+    const bool on = idx < total && jj <= i && !(skip0 >= 0 && jj >= skip0);
     double s = 0;
     if (on) {
-      const int ti = i / gt, tj = jj / gt;
+      const int ti = i / gt - tf, tj = jj / gt - tf;
       const int t = ti * (ti + 1) / 2 + tj;
       const double *p = part + (int64_t)t * (gt * gt) + (i % gt) * gt + (jj % gt);
       const int64_t st = (int64_t)ntl * (gt * gt);
@@ -297,9 +436,14 @@ static int gram_nsplit(int64_t nrows, int n) {
   return (int)want;
 }
 
+// Enough for a launch over the full triangle or over any trailing sub-triangle.
 size_t gram_part_elems(int64_t nrows, int n) {
-  const int64_t nt = (n + 127) / 128, ntl = nt * (nt + 1) / 2;
-  return (size_t)gram_nsplit(nrows, n) * ntl * 128 * 128;
+  size_t best = 0;
+  for (int64_t m = 1; m <= (n + 127) / 128; ++m) {
+    const size_t e = (size_t)gram_nsplit(nrows, (int)(m * 128)) * (m * (m + 1) / 2);
+    if (e > best) best = e;
+  }
+  return best * 128 * 128;
 }
 
 static int64_t gram_rows_per_split(int64_t nrows, int nsplit) {
@@ -307,12 +451,14 @@ static int64_t gram_rows_per_split(int64_t nrows, int nsplit) {
   return (rps + 15) / 16 * 16;
 }
 
-static void gram_reduce(const double *part, int nsplit, int ntl, int n, double *G, hipStream_t s, int gt) {
-  const int64_t m = n;
+static void gram_reduce(const double *part, int nsplit, int ntl, int n, double *G, hipStream_t s, int gt, int tf = 0,
+                        int r0 = 0, int skip0 = -1) {
+  const int64_t m = n - r0;
   int64_t blocks = (m * m + 31) / 32;
   if (blocks > 65536) blocks = 65536;
   if (blocks < 1) return;
-  hipLaunchKernelGGL(gram_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, s, part, nsplit, ntl, gt, n, G);
+  hipLaunchKernelGGL(gram_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, s, part, nsplit, ntl, gt, n, tf, r0,
+                     skip0, G);
 }
 
 // n <= 64 (mixed or not: the 64-wide diagonal block is FP64 either way).
@@ -340,8 +486,25 @@ static void gram_small(const double *A, int64_t lda, const double *B, int64_t ld
   gram_reduce(part, (int)nsplit, 1, n, G, s, 64);
 }
 
-template <int MODE, int F, int NW>
-static int gram_tiles(const double *A, int64_t lda, const double *B, int64_t ldb, int64_t nrows, int n, int fr0,
+static bool gram_v16(const double *A, int64_t lda, const double *B, int64_t ldb, int n) {
+  return lda % 2 == 0 && ldb % 2 == 0 && n % 2 == 0 && ((uintptr_t)A % 16) == 0 && ((uintptr_t)B % 16) == 0;
+}
+
+template <bool FR>
+static void gram_split_part(bool v16, int nsplit, const double *A, int64_t lda, const double *B, int64_t ldb,
+                            int64_t nrows, int n, int ntl, int tf, int fr0, double *part, hipStream_t s) {
+  const dim3 grid((unsigned)(nsplit * ntl));
+  const int64_t rps = gram_rows_per_split(nrows, nsplit);
+  if (v16)
+    hipLaunchKernelGGL((gram_split_kernel<2, FR>), grid, dim3(256), 0, s, A, lda, B, ldb, nrows, n, ntl, tf, rps, fr0,
+                       part);
+  else
+    hipLaunchKernelGGL((gram_split_kernel<1, FR>), grid, dim3(256), 0, s, A, lda, B, ldb, nrows, n, ntl, tf, rps, fr0,
+                       part);
+}
+
+template <bool MIXED, int F, int NW>
+static int gram_tiles(const double *A, int64_t lda, const double *B, int64_t ldb, int64_t nrows, int n,
                       double *part, size_t part_elems, double *G, hipStream_t s) {
   constexpr int T = 16 * F;
   const int nt = (n + T - 1) / T, ntl = nt * (nt + 1) / 2, nwg = (ntl + NW - 1) / NW;
@@ -351,8 +514,8 @@ static int gram_tiles(const double *A, int64_t lda, const double *B, int64_t ldb
   if (nsplit > fit) nsplit = fit;
   const int64_t rps = gram_rows_per_split(nrows, (int)nsplit);
   nsplit = (nrows + rps - 1) / rps;
-  hipLaunchKernelGGL((gram_kernel<MODE, F, NW>), dim3((unsigned)(nsplit * nwg)), dim3(64 * NW), 0, s, A, lda, B, ldb, nrows, n,
-                     ntl, rps, fr0, part);
+  hipLaunchKernelGGL((gram_kernel<MIXED, F, NW>), dim3((unsigned)(nsplit * nwg)), dim3(64 * NW), 0, s, A, lda, B, ldb, nrows, n,
+                     ntl, rps, part);
   gram_reduce(part, (int)nsplit, ntl, n, G, s, T);
   return 0;
 }
@@ -369,21 +532,36 @@ int gram_launch_capped(const double *A, int64_t lda, const double *B, int64_t ld
     gram_small(A, lda, B, ldb, nrows, n, part, part_elems / (64 * 64), G, s);
     return 0;
   }
-  if (mixed) return gram_tiles<1, 4, 8>(A, lda, B, ldb, nrows, n, 0, part, part_elems, G, s);
-  // 48- or 64-wide tiles, by the fragments they cover the lower triangle with
-  // (857,375 rows: n = 283, 378 fragments against 480, 1.5 against 1.7 ms; n =
-  // 640, 1,890 against 1,760, 7.2 against 6.5 ms)
+  if (mixed) return gram_tiles<true, 4, 8>(A, lda, B, ldb, nrows, n, part, part_elems, G, s);
+  // 48-wide tiles by fours or 64-wide ones by eights: up to 800 columns by the
+  // fragments they compute, the idle waves of the last work-group included
+  // (857,375 rows: n = 568, 720 against 768, 5.2 and 6.3 ms; n = 640, 972 against
+  // 896, 6.7 and 6.2), beyond that the wide ones, which read less (n = 1,128: 22.0
+  // and 19.7 ms)
   const int nt3 = (n + 47) / 48, nt4 = (n + 63) / 64;
-  if (9 * nt3 * (nt3 + 1) <= 16 * nt4 * (nt4 + 1))
-    return gram_tiles<0, 3, 4>(A, lda, B, ldb, nrows, n, 0, part, part_elems, G, s);
-  return gram_tiles<0, 4, 4>(A, lda, B, ldb, nrows, n, 0, part, part_elems, G, s);
+  const int wg3 = (nt3 * (nt3 + 1) / 2 + 3) / 4, wg4 = (nt4 * (nt4 + 1) / 2 + 7) / 8;
+  if (n > 800 || wg4 * 8 * 16 < wg3 * 4 * 9) return gram_tiles<false, 4, 8>(A, lda, B, ldb, nrows, n, part, part_elems, G, s);
+  return gram_tiles<false, 3, 4>(A, lda, B, ldb, nrows, n, part, part_elems, G, s);
 }
 
 void gram_split_launch(const double *A, int64_t lda, const double *B, int64_t ldb, int64_t nrows, int n, double *part,
                        double *G, int fr0, hipStream_t s) {
   fr0 = fr0 / 64 * 64;
-  if (fr0 == 0) gram_launch(A, lda, B, ldb, nrows, n, part, G, 0, s);
-  else gram_tiles<2, 4, 8>(A, lda, B, ldb, nrows, n, fr0, part, 0, G, s);
+  if (fr0 == 0) {
+    gram_launch(A, lda, B, ldb, nrows, n, part, G, 0, s);
+    return;
+  }
+  const bool v16 = gram_v16(A, lda, B, ldb, n);
+  // the trailing block in FP64, on a grid over its own sub-triangle of tiles
+  // (so that the few tiles it touches get every row split), reduced first
+  const int nt = (n + GT - 1) / GT, tf = fr0 / GT, m = nt - tf, ntl4 = m * (m + 1) / 2;
+  const int nsplit4 = gram_nsplit(nrows, m * GT);
+  gram_split_part<true>(v16, nsplit4, A, lda, B, ldb, nrows, n, ntl4, tf, fr0, part, s);
+  gram_reduce(part, nsplit4, ntl4, n, G, s, GT, tf, fr0);
+  // everything else with FP32 inputs and products; part is reused in order
+  const int ntl = nt * (nt + 1) / 2, nsplit = gram_nsplit(nrows, n);
+  gram_split_part<false>(v16, nsplit, A, lda, B, ldb, nrows, n, ntl, 0, fr0, part, s);
+  gram_reduce(part, nsplit, ntl, n, G, s, GT, 0, 0, fr0);
 }
 
 // ---------------------------------------------------------------------------
@@ -911,6 +1089,9 @@ void resid_launch(const double *X, int64_t ldx, const double *HX, int64_t ldh, c
   if (n <= 32)
     hipLaunchKernelGGL((resid_part_kernel<32>), dim3(nchunk), dim3(256), 0, s, X, ldx, HX, ldh, lam, nrows, n, rows_per,
                        nchunk, part);
+  else if (n > 512)                                // whole lines of a row at a time: 4,019,679 x 1,128 12.3 against 13.1 ms
+    hipLaunchKernelGGL((resid_part_kernel<256>), dim3(nchunk, (n + 255) / 256), dim3(256), 0, s, X, ldx, HX, ldh, lam,
+                       nrows, n, rows_per, nchunk, part);
   else
     hipLaunchKernelGGL((resid_part_kernel<64>), dim3(nchunk, (n + 63) / 64), dim3(256), 0, s, X, ldx, HX, ldh, lam, nrows,
                        n, rows_per, nchunk, part);

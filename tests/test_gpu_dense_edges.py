@@ -2,7 +2,7 @@
 whose rows lie odd distances apart: Gram matrices of up to 64 columns (fragments
 of 16) and in tiles of 48 and 64 beyond, rotations by 128, 64 and 32 rows, Cholesky
 blocks of 32, Jacobi pairs of 64, residuals in
-groups of 32 and 64 columns, on meshes with fewer rows than one split, and a
+groups of 32, 64 and 256 columns, on meshes with fewer rows than one split, and a
 row more than a whole number of them.  And the potential given on the device."""
 import numpy as np
 import pytest
@@ -12,7 +12,7 @@ from gpu_util import make_ctx, oracle_apply, to_gpu, to_host, torch_dev
 
 pytestmark = pytest.mark.gpu
 
-COLS = [1, 15, 16, 17, 31, 32, 33, 48, 49, 63, 64, 65, 96, 97, 128, 144, 145, 304, 305, 340]
+COLS = [1, 15, 16, 17, 31, 32, 33, 48, 49, 63, 64, 65, 96, 97, 128, 144, 145, 304, 305, 340, 513, 640]
 
 
 @pytest.mark.parametrize("n_el,p", [(1, 5), (2, 4), (5, 4)])    # 64, 343 and 6,859 rows
