@@ -53,7 +53,9 @@ void gll_rule(int p, std::vector<double> &xi, std::vector<double> &w) {
   }
 }
 
-void sym_eigvals(std::vector<double> a, int n, std::vector<double> &out) {
+// (aligned: its loops ran 28 % slower, 59 against 46 ms for a Bloch vector at
+// n = 72, where a change elsewhere in the library had moved them by 32 bytes)
+__attribute__((aligned(64))) void sym_eigvals(std::vector<double> a, int n, std::vector<double> &out) {
   for (int sweep = 0; sweep < 100; ++sweep) {
     double off = 0, tot = 0;
     for (int i = 0; i < n; ++i)
