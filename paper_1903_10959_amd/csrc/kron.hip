@@ -158,13 +158,15 @@ __device__ __forceinline__ int line_dof(int e, int a, int P, int n_el, bool peri
 //     coefficient.
 // The scheduling barriers keep the LDS reads of one output row from being
 // hoisted over the others': without them the register need grows past two
-// work-groups' share (measured, FP64 p = 5: 209 against 168 registers).
+// work-groups' share (measured, FP64 p = 5: 209 against 168 registers).  A
+// launch that leaves every CU at most one work-group goes without them (LONE).
 // ---------------------------------------------------------------------------
-template <typename T_, int P_, int CL_, int CX_, int CY_, int NS_, bool CPLX_ = false>
+template <typename T_, int P_, int CL_, int CX_, int CY_, int NS_, bool CPLX_ = false, bool LONE_ = false>
 struct KronTile {
   typedef T_ T;
   static constexpr int P = P_, CL = CL_, CX = CX_, CY = CY_, NS = NS_;
   static constexpr bool CPLX = CPLX_;
+  static constexpr bool LONE = LONE_;                // one work-group per CU: registers to spare
   static constexpr int NA = (P + NS - 1) / NS;       // nodes of a line per part
   static constexpr int L = CL * CX * CY;             // lanes of one wave row
   static constexpr int NT = NS * P * L;              // threads
@@ -299,6 +301,10 @@ __device__ __forceinline__ void kron_tile(const KronProb<typename C::T> &pr, int
   const unsigned nbx = nd2 * ldxb, nby = nd2 * ldyb, nbp = Xp ? nby : 0u, nbv = nd2 * 8u;
   auto plane = [&](const void *base, unsigned bytes, int kd) {
     return buf_of(reinterpret_cast<const char *>(base) + (uint64_t)bytes * (unsigned)(kd < 0 ? 0 : kd), kd < 0 ? 0u : bytes);
+  };
+
+  auto row_fence = [] {
+    if constexpr (!C::LONE) __builtin_amdgcn_sched_barrier(0);
   };
 
   // The march, for the nodes of part PART (its waves run their own copy; all
@@ -444,7 +450,7 @@ __device__ __forceinline__ void kron_tile(const KronProb<typename C::T> &pr, int
               acc[c][0] = fma_t(A(P, m), xs[m], acc[c][0]);
               if (CPLX) gx[0] = fma_t(Cc(P, m), xs[m], gx[0]);
             }
-            __builtin_amdgcn_sched_barrier(0);
+            row_fence();
           }
 #pragma unroll
           for (int m = 0; m <= P; ++m) xs[m] = lds_at(row_lds + node_at(m, 0));
@@ -459,10 +465,10 @@ __device__ __forceinline__ void kron_tile(const KronProb<typename C::T> &pr, int
             }
             if (CPLX) {
               acc[c][a] += mul_ik(0, gx[a]);
-              __builtin_amdgcn_sched_barrier(0);
+              row_fence();
             }
           }
-          __builtin_amdgcn_sched_barrier(0);
+          row_fence();
           // the diagonal, and z
           T xk[NO];
           set_xk(xs + A0, xk);
@@ -471,7 +477,7 @@ __device__ __forceinline__ void kron_tile(const KronProb<typename C::T> &pr, int
 #pragma unroll
           for (int r = 0; r <= P; ++r) zrow(r, c, xs + A0, xk);
         }
-        __builtin_amdgcn_sched_barrier(0);
+        row_fence();
         // y: this element, and for its first node the element below it
         // (Ae[P][m] = Ae[0][P - m], C[P][m] = -C[0][P - m])
 #pragma unroll
@@ -484,7 +490,7 @@ __device__ __forceinline__ void kron_tile(const KronProb<typename C::T> &pr, int
             if (CPLX) g = fma_t(yc[m], v, g);        // (C's diagonal is stored as zero)
           }
           if (CPLX) acc[c][a] += mul_ik(1, g);
-          __builtin_amdgcn_sched_barrier(0);
+          row_fence();
         }
         if (b == 0) {
 #pragma unroll
@@ -497,7 +503,7 @@ __device__ __forceinline__ void kron_tile(const KronProb<typename C::T> &pr, int
               if (CPLX) g = fma_t(-yc[P - m], v, g);
             }
             if (CPLX) acc[c][a] += mul_ik(1, g);
-            __builtin_amdgcn_sched_barrier(0);
+            row_fence();
           }
         }
         lds_barrier();
@@ -679,6 +685,15 @@ struct TileOf {
   static constexpr int WAVES = !f64 ? 4 : CPLX ? (P == 7 ? 2 : 3) : P <= 3 ? 4 : P == 4 ? (CX == 4 ? 3 : 4)
                                : P == 5 ? 3 : P == 6 ? 4 : 2;
   typedef KronTile<T, P, CL, CX, 2, NS, CPLX> type;
+  // The same tile for launches of at most one work-group per CU, whose time is
+  // its waves' chains: no scheduling barriers, and in FP64 the nodes of a line in
+  // two parts, twice the waves.  us per step, lone against not: FP64 p = 4, 4^3
+  // cells x 24 columns 8.25, 9.05; p = 5, 5^3 x 32 13.95, 15.3; FP32 p = 4 8.04,
+  // 8.79; p = 6, 5^3 x 32 19.9, 21.0.  (FP64 p = 6, already in two parts, 21.7
+  // against 21.3, p = 7 53 against 36: spills.)
+  static constexpr bool HAS_LONE = !CPLX && CX == 2 && P >= 3 && P <= (f64 ? 5 : 6);
+  typedef typename std::conditional<HAS_LONE, KronTile<T, P, CL, 2, 2, f64 ? 2 : 1, false, true>, type>::type lone;
+  static constexpr int LONE_WAVES = (lone::NT + 255) / 256;
 };
 // (a mesh whose 4 x 2 tiles, one cell deep, do not fill the CUs takes 2 x 2:
 // p = 4, 4^3 cells x 24 columns 9.1 against 12.1 us)
@@ -780,6 +795,12 @@ struct LaunchOp {
       status = -1;
       return;
     }
+    if constexpr (TO::HAS_LONE)
+      if (nwg <= CUS) {
+        typedef typename TO::lone L;
+        hipLaunchKernelGGL((kron_kernel<L, TO::LONE_WAVES>), dim3((unsigned)nwg), dim3(L::NT), 0, s, pr, g);
+        return;
+      }
     hipLaunchKernelGGL((kron_kernel<C, TO::WAVES>), dim3((unsigned)nwg), dim3(C::NT), 0, s, pr, g);
   }
 };
@@ -892,6 +913,13 @@ struct BatchLaunchOp {
   int nwork, step;
   hipStream_t s;
   template <typename TO> void run() {
+    if constexpr (TO::HAS_LONE)
+      if (nwork <= CUS) {
+        typedef typename TO::lone L;
+        hipLaunchKernelGGL((kron_batch_kernel<L, TO::LONE_WAVES>), dim3((unsigned)nwork), dim3(L::NT), 0, s, probs, work,
+                           step);
+        return;
+      }
     hipLaunchKernelGGL((kron_batch_kernel<typename TO::type, TO::WAVES>), dim3((unsigned)nwork), dim3(TO::type::NT), 0, s,
                        probs, work, step);
   }
