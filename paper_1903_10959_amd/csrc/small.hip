@@ -2,7 +2,7 @@
 //
 //  * potrf: blocked right-looking Cholesky S = L L^T (Sec. 3.4 Alg. 3 step 2;
 //    the paper uses ScaLAPACK pXpotrf).  32x32 diagonal blocks are factored
-//    in LDS by one work-group, which also inverts them for the panel solve.
+//    by one wave, which also inverts them for the panel solve.
 //  * trtri_t: W = L^-T (Alg. 3 step 3; the paper uses pXtrtri), block row by
 //    block row from the diagonal-block inverses.
 //  * jacobi: symmetric eigensolver for the projected Hamiltonian (Sec. 3.5
