@@ -28,7 +28,7 @@
 // r / diag(A), which the direction pass reads as it is; diag(A) itself is
 // recomputed in the update, from 1D values, and an iteration moves ten arrays
 // of n_dof values (24^3 cells of degree 6, which the last-level cache holds:
-// 20 + 15 + 19 us and 8 us between launches; 32 + 19 + 27 before, with the band
+// 20 + 15 + 19 us and 2 us between launches; 32 + 19 + 27 and 4 before, with the band
 // stencil, a third of the lanes idle in rows of 143, and r / diag(A) formed in
 // both vector passes).  The
 // iteration that meets the tolerance records its number; launches of later
