@@ -46,7 +46,8 @@ typedef struct chfsi_ctx chfsi_ctx;   /* opaque; owned by the library */
 
 /* Arithmetic of the filter's products.  FP64 = the paper's precision.
  * FP32: recursion state and products in FP32.  BF16: the block's values enter
- * the products rounded to BF16, FP32 accumulation, recursion state FP32.
+ * the off-diagonal products rounded to BF16; the diagonal (kinetic, potential and
+ * shift together) multiplies the FP32 value; FP32 accumulation and recursion state.
  * BF16X3: products at least as exact as a BF16 hi/lo split of both operands
  * with three products accumulated in FP32 (the library runs them in FP32). */
 typedef enum {

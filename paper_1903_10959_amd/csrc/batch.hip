@@ -217,10 +217,13 @@ int build_sweep(chfsi_batch *B, Sweep<T> &S, const std::vector<int> &ids, const 
   std::vector<int4> all;
   struct Group {
     int p, variant, first, count;
+    bool bf16;                                     // some of its problems are on a BF16 rung
   };
   std::vector<Group> groups;
   for (auto &kv : lists) {
-    groups.push_back({kv.first.first, kv.first.second, (int)all.size(), (int)kv.second.size()});
+    bool bf16 = false;
+    for (const int4 &w : kv.second) bf16 |= hp[w.x].bf16 != 0;
+    groups.push_back({kv.first.first, kv.first.second, (int)all.size(), (int)kv.second.size(), bf16});
     all.insert(all.end(), kv.second.begin(), kv.second.end());
   }
   BCHK(B, S.probs.ensure(hp.size() * sizeof(KronBatchProblem<T>)));
@@ -238,7 +241,7 @@ int build_sweep(chfsi_batch *B, Sweep<T> &S, const std::vector<int> &ids, const 
   int lerr = 0;
   for (int k = 0; k < B->degree; ++k)
     for (const Group &g : groups)
-      lerr |= kron_batch_launch<T>(g.p, g.variant, S.probs.template as<KronBatchProblem<T>>(),
+      lerr |= kron_batch_launch<T>(g.p, g.variant, g.bf16, S.probs.template as<KronBatchProblem<T>>(),
                                    S.work.template as<int4>() + g.first, g.count, k, B->stream);
   for (size_t m = 0; m < ids.size(); ++m) {
     const Prob &p = B->probs[ids[m]];

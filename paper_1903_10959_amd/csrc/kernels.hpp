@@ -36,7 +36,7 @@ struct KronArgs {
   int n_el, p, n, periodic, ncols;
   double s1, s2, shift;
   int variant = -1;    // tile: -1 built-in choice, 0 2 x 2 cells, 1 4 x 2 where available
-  int bf16 = 0;        // float: X enters the products rounded to BF16
+  int bf16 = 0;        // float: X enters the products with the 1D matrices' off-diagonal entries rounded to BF16
   double k[3] = {0, 0, 0};   // complex: Bloch vector
 };
 int kron_launch(const KronArgs<double> &a, hipStream_t s);
@@ -63,7 +63,7 @@ struct KronBatchProblem {
 // The tile variant a problem runs (its context's setting, or for -1 the
 // built-in choice); with it, its tiles (-1: no tile kernel for the degree), its
 // work items appended to `work`, and the launch of one step for a work list of
-// one degree and variant.
+// one degree and variant (bf16: some of its problems round to BF16).
 template <typename T>
 int kron_batch_variant(int p, int variant, int n_el, int ncols);
 template <typename T>
@@ -71,8 +71,8 @@ int64_t kron_batch_tiles(int p, int variant, int n_el, int ncols);
 template <typename T>
 int kron_batch_work(int p, int variant, int n_el, int ncols, int prob, int zlen, std::vector<int4> &work);
 template <typename T>
-int kron_batch_launch(int p, int variant, const KronBatchProblem<T> *probs, const int4 *work, int nwork, int step,
-                      hipStream_t s);
+int kron_batch_launch(int p, int variant, bool bf16, const KronBatchProblem<T> *probs, const int4 *work, int nwork,
+                      int step, hipStream_t s);
 // out = in, values converted; gin, gout: columns to a group of either side
 // (any value >= ncols for a row-major block).
 template <typename Tin, typename Tout>

@@ -120,7 +120,7 @@ struct KronProb {
   const double *ae;   // Ae [(P+1)^2], then the first-derivative matrix C [(P+1)^2]
   int n_el, n, periodic, ncols;
   double s1, s2, shift;
-  int bf16;           // round the values that enter the products to BF16
+  int bf16;           // (BF tiles) round the values that enter the products to BF16
   double k[3];        // complex: Bloch vector
 };
 
@@ -160,13 +160,23 @@ __device__ __forceinline__ int line_dof(int e, int a, int P, int n_el, bool peri
 // hoisted over the others': without them the register need grows past two
 // work-groups' share (measured, FP64 p = 5: 209 against 168 registers).  A
 // launch that leaves every CU at most one work-group goes without them (LONE).
+//
+// BF tiles (float) can round the values that the 1D element matrices multiply to
+// BF16.  The diagonal, where the potential and the shift are, multiplies the
+// value itself, which the thread keeps until the coefficient is known: in
+// registers, at p = 7 in LDS (16^3 cells x 128 columns 790 us per step; kept in
+// registers, 42 of which spill, 870).
 // ---------------------------------------------------------------------------
-template <typename T_, int P_, int CL_, int CX_, int CY_, int NS_, bool CPLX_ = false, bool LONE_ = false>
+template <typename T_, int P_, int CL_, int CX_, int CY_, int NS_, bool CPLX_ = false, bool LONE_ = false,
+          bool BF_ = false>
 struct KronTile {
   typedef T_ T;
   static constexpr int P = P_, CL = CL_, CX = CX_, CY = CY_, NS = NS_;
   static constexpr bool CPLX = CPLX_;
   static constexpr bool LONE = LONE_;                // one work-group per CU: registers to spare
+  static constexpr bool BF = BF_;                    // products may take their values rounded to BF16
+  static constexpr bool XD_LDS = BF && P == 7;       // (BF) the diagonal's values wait in LDS
+  static_assert(!BF || std::is_same<T, float>::value, "BF16 rounding of FP32 blocks");
   static constexpr int NA = (P + NS - 1) / NS;       // nodes of a line per part
   static constexpr int L = CL * CX * CY;             // lanes of one wave row
   static constexpr int NT = NS * P * L;              // threads
@@ -197,6 +207,7 @@ __device__ __forceinline__ void kron_tile(const KronProb<typename C::T> &pr, int
   __shared__ __align__(16) char lds[C::W * C::H * C::NODE];
   __shared__ T dlds[C::NN];          // this plane's diagonal coefficients
   __shared__ double dxy[C::NN];      // the x and y parts of the diagonal less the shift
+  __shared__ T xdl[C::XD_LDS ? NA * C::NT : 1];      // a thread's own values, NT apart
   const int t = threadIdx.x;
   const int row = __builtin_amdgcn_readfirstlane(t / C::L);    // wave row
   const int part = C::NS == 1 ? 0 : row / P, b = row - part * P;
@@ -290,7 +301,7 @@ __device__ __forceinline__ void kron_tile(const KronProb<typename C::T> &pr, int
   auto lds_at = [&](int off) -> T & { return *reinterpret_cast<T *>(lds + off); };
 
   auto rnd = [&](T x) -> T {
-    if constexpr (std::is_same<T, float>::value) return pr.bf16 ? (float)(__bf16)x : x;
+    if constexpr (C::BF) return pr.bf16 ? (float)(__bf16)x : x;
     else return x;
   };
 
@@ -394,9 +405,13 @@ __device__ __forceinline__ void kron_tile(const KronProb<typename C::T> &pr, int
 #pragma unroll
       for (int c = 0; c < P; ++c) {
         // plane c of this element to LDS
-        T x[NO], dg[NO];
+        T x[NO], dg[NO], xd[NO];                     // xd: what the diagonal multiplies
 #pragma unroll
-        for (int a = 0; a < NO; ++a) x[a] = rnd(xo[a]);
+        for (int a = 0; a < NO; ++a) {
+          if constexpr (C::XD_LDS) xdl[a * C::NT + t] = xo[a];
+          else xd[a] = xo[a];
+          x[a] = rnd(xo[a]);
+        }
 #pragma unroll
         for (int a = 0; a < NO; ++a) lds_at(row_lds + node_at(A0 + a, 0)) = x[a];
         int hl = h_lds;
@@ -473,7 +488,10 @@ __device__ __forceinline__ void kron_tile(const KronProb<typename C::T> &pr, int
           T xk[NO];
           set_xk(xs + A0, xk);
 #pragma unroll
-          for (int a = 0; a < NO; ++a) acc[c][a] = fma_t(own_d[A0 + a], xs[A0 + a], acc[c][a]);
+          for (int a = 0; a < NO; ++a) {
+            if constexpr (C::XD_LDS) xd[a] = xdl[a * C::NT + t];
+            acc[c][a] = fma_t(own_d[A0 + a], C::BF ? xd[a] : xs[A0 + a], acc[c][a]);
+          }
 #pragma unroll
           for (int r = 0; r <= P; ++r) zrow(r, c, xs + A0, xk);
         }
@@ -658,7 +676,7 @@ __global__ __launch_bounds__(256) void kron_general_kernel(KronProb<T> pr, int P
       }
       if (CPLX) y = fma_t((T)((col & 1) ? -pr.k[dir] : pr.k[dir]), g, y);
     }
-    y = fma_t((T)(pr.s1 * dg), at(d), y);
+    y = fma_t((T)(pr.s1 * dg), pr.X[d * pr.ldx + col], y);   // (the value itself, as in the tile kernel)
     if (pr.Xp) y = fma_t((T)pr.s2, pr.Xp[d * pr.ldy + col], y);
     pr.Y[d * pr.ldy + col] = y;
   }
@@ -676,7 +694,7 @@ __global__ __launch_bounds__(256) void kron_general_kernel(KronProb<T> pr, int P
 //   part 3165 (two parts spill at the 128 registers of fourteen waves);
 //   FP32, 32 columns per node: p = 6, 24^3 x 128 1090 (16 lanes of two
 //   columns each: 1270).
-template <typename T, int P, int V, bool CPLX>
+template <typename T, int P, int V, bool CPLX, bool BF = false>
 struct TileOf {
   static constexpr bool f64 = sizeof(T) == 8;
   static constexpr int CL = f64 ? 16 : 32;
@@ -684,7 +702,7 @@ struct TileOf {
   static constexpr int NS = (f64 && (CPLX ? (P == 5 || P == 6) : P == 6)) ? 2 : 1;
   static constexpr int WAVES = !f64 ? 4 : CPLX ? (P == 7 ? 2 : 3) : P <= 3 ? 4 : P == 4 ? (CX == 4 ? 3 : 4)
                                : P == 5 ? 3 : P == 6 ? 4 : 2;
-  typedef KronTile<T, P, CL, CX, 2, NS, CPLX> type;
+  typedef KronTile<T, P, CL, CX, 2, NS, CPLX, false, BF> type;
   // The same tile for launches of at most one work-group per CU, whose time is
   // its waves' chains: no scheduling barriers, and in FP64 the nodes of a line in
   // two parts, twice the waves.  us per step, lone against not: FP64 p = 4, 4^3
@@ -692,7 +710,7 @@ struct TileOf {
   // 8.79; p = 6, 5^3 x 32 19.9, 21.0.  (FP64 p = 6, already in two parts, 21.7
   // against 21.3, p = 7 53 against 36: spills.)
   static constexpr bool HAS_LONE = !CPLX && CX == 2 && P >= 3 && P <= (f64 ? 5 : 6);
-  typedef typename std::conditional<HAS_LONE, KronTile<T, P, CL, 2, 2, f64 ? 2 : 1, false, true>, type>::type lone;
+  typedef typename std::conditional<HAS_LONE, KronTile<T, P, CL, 2, 2, f64 ? 2 : 1, false, true, BF>, type>::type lone;
   static constexpr int LONE_WAVES = (lone::NT + 255) / 256;
 };
 // (a mesh whose 4 x 2 tiles, one cell deep, do not fill the CUs takes 2 x 2:
@@ -706,14 +724,14 @@ static int tile_variant(int p, bool f64, int variant, int n_el, int ncols) {
 }
 
 // Calls f.template run<TileOf<...>>() for degree p (1..7) and variant v; -1 otherwise.
-template <typename T, bool CPLX, typename F>
+template <typename T, bool CPLX, bool BF = false, typename F>
 static int with_tile(int p, int v, F &&f) {
   switch (p) {
 #define KRON_CASE(N)                                                   \
   case N:                                                              \
-    if constexpr (TileOf<T, N, 1, CPLX>::CX == 4)                      \
-      if (v != 0) return f.template run<TileOf<T, N, 1, CPLX>>(), 0;   \
-    return f.template run<TileOf<T, N, 0, CPLX>>(), 0;
+    if constexpr (TileOf<T, N, 1, CPLX, BF>::CX == 4)                  \
+      if (v != 0) return f.template run<TileOf<T, N, 1, CPLX, BF>>(), 0; \
+    return f.template run<TileOf<T, N, 0, CPLX, BF>>(), 0;
     KRON_CASE(1) KRON_CASE(2) KRON_CASE(3) KRON_CASE(4) KRON_CASE(5) KRON_CASE(6) KRON_CASE(7)
 #undef KRON_CASE
     default: return -1;
@@ -812,6 +830,8 @@ static int launch(const KronArgs<T> &a, hipStream_t s) {
   if (kron_tiled(a.p, a.n, std::max(a.X.ld, a.Y.ld), sizeof(T))) {
     LaunchOp<T> op{pr, s};
     const int v = CPLX ? 0 : tile_variant(a.p, sizeof(T) == 8, a.variant, a.n_el, a.ncols);
+    if constexpr (std::is_same<T, float>::value)
+      if (a.bf16) return with_tile<T, CPLX, true>(a.p, v, op) ? -1 : op.status;
     return with_tile<T, CPLX>(a.p, v, op) ? -1 : op.status;
   }
   // the general kernel reads row-major blocks
@@ -925,17 +945,19 @@ struct BatchLaunchOp {
   }
 };
 template <typename T>
-int kron_batch_launch(int p, int variant, const KronBatchProblem<T> *probs, const int4 *work, int nwork, int step,
-                      hipStream_t s) {
+int kron_batch_launch(int p, int variant, bool bf16, const KronBatchProblem<T> *probs, const int4 *work, int nwork,
+                      int step, hipStream_t s) {
   if (nwork <= 0) return 0;
   BatchLaunchOp<T> op{probs, work, nwork, step, s};
+  if constexpr (std::is_same<T, float>::value)
+    if (bf16) return with_tile<T, false, true>(p, variant, op);
   return with_tile<T, false>(p, variant, op);
 }
 #define KRON_BATCH(T)                                                                                        \
   template int kron_batch_variant<T>(int, int, int, int);                                                    \
   template int64_t kron_batch_tiles<T>(int, int, int, int);                                                  \
   template int kron_batch_work<T>(int, int, int, int, int, int, std::vector<int4> &);                        \
-  template int kron_batch_launch<T>(int, int, const KronBatchProblem<T> *, const int4 *, int, int, hipStream_t);
+  template int kron_batch_launch<T>(int, int, bool, const KronBatchProblem<T> *, const int4 *, int, int, hipStream_t);
 KRON_BATCH(double)
 KRON_BATCH(float)
 #undef KRON_BATCH
