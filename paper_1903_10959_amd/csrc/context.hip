@@ -434,6 +434,7 @@ static int cheb_step_t(chfsi_ctx *c, const ColBuf<const T> &X, const T *Xp, cons
 
 int chfsi::cheb_step_c(chfsi_ctx *c, const ColBuf<const double> &X, const double *Xp, const ColBuf<double> &Y,
                        int ncols, double s1, double s2, double shift) {
+  if (c->mesh.p > 7) return fail(c, CHFSI_ERR_ARG, "Htilde_k step: degree p must be in 1..7");
   KronArgs<double> a = kron_args<double>(c, 2 * ncols);
   a.X = X;
   a.Xp = Xp;
