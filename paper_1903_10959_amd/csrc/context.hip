@@ -280,6 +280,17 @@ extern "C" int chfsi_get_cell_matrix(const chfsi_ctx *c, double *k) {
   return 0;
 }
 
+// Whether v is memory of the given device, which its kernels can read (another
+// device's, or the host's, only copies reach).
+static bool on_device(int device, const void *v) {
+  hipPointerAttribute_t at;
+  if (hipPointerGetAttributes(&at, v) != hipSuccess) {
+    (void)hipGetLastError();                       // (not an error of this library's work)
+    return false;
+  }
+  return at.type == hipMemoryTypeDevice && at.device == device;
+}
+
 extern "C" int chfsi_set_potential(chfsi_ctx *c, const double *v, int64_t n_dof, int v_on_device) {
   if (!c) return CHFSI_ERR_ARG;
   if (!c->has_mesh) return fail(c, CHFSI_ERR_STATE, "set_potential before set_mesh");
@@ -288,6 +299,18 @@ extern "C" int chfsi_set_potential(chfsi_ctx *c, const double *v, int64_t n_dof,
   if (c->device >= 0)
     if (int r = set_dev(c)) return r;
   double vmax = -INFINITY;
+  std::vector<double> hv;
+  if (v_on_device && !on_device(c->device, v)) {
+    hv.resize(n_dof);
+    const hipError_t e = hipMemcpyAsync(hv.data(), v, n_dof * sizeof(double), hipMemcpyDeviceToHost, c->stream);
+    if (e != hipSuccess) {                         // (memory the runtime does not know)
+      (void)hipGetLastError();
+      return fail(c, CHFSI_ERR_HIP, std::string("set_potential: ") + hipGetErrorString(e));
+    }
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    v = hv.data();
+    v_on_device = 0;
+  }
   if (v_on_device) {
     // maximum and finiteness on the device (NaN in a partial maximum: a
     // non-finite value), the values stay there
