@@ -804,7 +804,7 @@ int jacobi_eigh_batch(const JacobiJob *jobs, int njobs, double tol, int max_swee
         hipSuccess)
       return -1;
     if (hipStreamSynchronize(s) != hipSuccess) return -1;
-    bool changed = false;
+    bool changed = false, left = false;
     for (int a = 0; a < nr; ++a) {
       const int k = ids[a];
       double off = 0, dg = 0;
@@ -816,13 +816,13 @@ int jacobi_eigh_batch(const JacobiJob *jobs, int njobs, double tol, int max_swee
       bool done = off <= tol * tol * tot;
       if (prev_off[k] >= 0 && off >= prev_off[k] && off <= 1e-20 * tot) done = true;  // stagnated at rounding
       prev_off[k] = off;
-      if (done) {
-        active[k] = 0;
-        changed = true;
-      }
+      if (done) active[k] = 0;
+      (done ? changed : left) = true;
     }
+    // (out of sweeps: the rest stay unconverged.  The stream has read the table's
+    // last copy by now, and no other is started that would outlive `run`.)
+    if (!left || sweep >= max_sweeps) break;
     if (changed && !set_table()) return -1;
-    if (run.empty() || sweep >= max_sweeps) break;  // (out of sweeps: the rest stay unconverged)
     for (int g = 0; g < rmax; ++g) {
       if (g == 0)
         hipLaunchKernelGGL((jacobi_inner_kernel<true>), dim3((unsigned)n_inner), dim3(512), 0, s, dtab, (int)run.size(), g);
