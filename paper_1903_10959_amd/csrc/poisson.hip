@@ -27,7 +27,7 @@
 // plus one, and both values let iteration it run.  The residual is kept as z =
 // r / diag(A), which the direction pass reads as it is; diag(A) itself is
 // recomputed in the update, from 1D values, and an iteration moves ten arrays
-// of n_dof values (24^3 cells of degree 6, which the last-level cache holds:
+// of n_dof values and the partials (24^3 cells of degree 6, which the last-level cache holds:
 // 20 + 15 + 19 us and 2 us between launches; 32 + 19 + 27 and 4 before, with the band
 // stencil, a third of the lanes idle in rows of 143, and r / diag(A) formed in
 // both vector passes).  The
@@ -285,10 +285,17 @@ __global__ __launch_bounds__(PB, 2) void poisson_stencil_kernel(const double *__
 // The two vector passes run over the values in memory order, VU per thread 256
 // apart: every lane works whatever n is.  The loads of the partials a pass sums
 // are issued first, then all of its values', so the global sum is formed while
-// they are in flight.
-constexpr int VU = 8;
+// they are in flight.  Every work-group reads every partial, so their number is
+// bounded: beyond MAXG blocks of values (4.2M) a work-group takes several (MORE), as
+// many as the others (us per iteration, one block each against so: 9.9M values 190
+// against 170, 59.8M 2,396 against 1,215; up to 4.2M the loop costs 2 to 3 %, 57.2
+// against 55.6 at 2.9M, and is left out).
+constexpr int VU = 8, VBLOCK = PB * VU;
 constexpr int PU = 4;   // partials per thread loaded ahead (the rest, if any, after)
-static dim3 vec_grid(int64_t nd) { return dim3((unsigned)((nd + PB * VU - 1) / (PB * VU))); }
+static dim3 vec_grid(int64_t nd) {
+  const int64_t blocks = (nd + VBLOCK - 1) / VBLOCK, each = (blocks + MAXG - 1) / MAXG;
+  return dim3((unsigned)((blocks + each - 1) / each));
+}
 // (I, J, K) of a value, and of the one 256 further on
 struct NodePos {
   int I, J, K;
@@ -344,6 +351,7 @@ __device__ __forceinline__ double parts_sum(const double *__restrict__ a, int na
 // Iteration it: alpha = r.z / p.q from the product's partials (work-group 0
 // keeps it for the direction pass); z -= alpha q / diag(A), the residual r =
 // diag(A) z not being stored; partials of r.z and r.r.
+template <bool MORE>
 __global__ __launch_bounds__(PB) void poisson_update_kernel(double *__restrict__ z, const double *__restrict__ q,
                                                             const double *__restrict__ m, int n, int64_t nd, double s,
                                                             double *__restrict__ scal, int it,
@@ -355,38 +363,47 @@ __global__ __launch_bounds__(PB) void poisson_update_kernel(double *__restrict__
   double pp[PU];
   parts_load(part_pq, npq, pp);
   for (int i = (int)threadIdx.x; i < 2 * n; i += PB) mt[i] = m[i];
-  const int64_t base = (int64_t)blockIdx.x * (PB * VU);
-  const int left = nd - base < PB * VU ? (int)(nd - base) : PB * VU;
-  double *zb = z + base;
-  const double *qb = q + base;
   double zv[VU], qv[VU];
+  auto load = [&](int64_t base) {
+    const int left = nd - base < VBLOCK ? (int)(nd - base) : VBLOCK;
 #pragma unroll
-  for (int u = 0; u < VU; ++u) {
-    const int e = (int)threadIdx.x + PB * u;
-    zv[u] = e < left ? zb[e] : 0.0;
-    qv[u] = e < left ? qb[e] : 0.0;
-  }
-  NodePos at(base, (int)threadIdx.x, n);
+    for (int u = 0; u < VU; ++u) {
+      const int e = (int)threadIdx.x + PB * u;
+      zv[u] = e < left ? z[base + e] : 0.0;
+      qv[u] = e < left ? q[base + e] : 0.0;
+    }
+  };
+  int64_t base = (int64_t)blockIdx.x * VBLOCK;
+  load(base);
   const int dJ = PB / n, dI = PB - dJ * n;
   const double pq = parts_sum(part_pq, npq, pp, sh);
   const double alpha = pq != 0 ? scal[S_RZ + (it & 1)] / pq : 0.0;
   if (blockIdx.x == 0 && threadIdx.x == 0) scal[S_ALPHA] = alpha;
   double rz = 0, rr = 0;
+  for (;;) {
+    const int left = nd - base < VBLOCK ? (int)(nd - base) : VBLOCK;
+    double *zb = z + base;
+    NodePos at(base, (int)threadIdx.x, n);
 #pragma unroll
-  for (int u = 0; u < VU; ++u) {
-    const int e = (int)threadIdx.x + PB * u;
-    if (e < left) {
-      const double d = diag_at(mt, n, s, at.I, at.J, at.K);
-      // 1 / d to an ulp: the hardware estimate and two Newton steps
-      double y = __builtin_amdgcn_rcp(d);
-      y = fma(fma(-d, y, 1.0), y, y);
-      y = fma(fma(-d, y, 1.0), y, y);
-      const double v = zv[u] - alpha * (qv[u] * y), r = d * v;
-      zb[e] = v;
-      rz += r * v;
-      rr += r * r;
+    for (int u = 0; u < VU; ++u) {
+      const int e = (int)threadIdx.x + PB * u;
+      if (e < left) {
+        const double d = diag_at(mt, n, s, at.I, at.J, at.K);
+        // 1 / d to an ulp: the hardware estimate and two Newton steps
+        double y = __builtin_amdgcn_rcp(d);
+        y = fma(fma(-d, y, 1.0), y, y);
+        y = fma(fma(-d, y, 1.0), y, y);
+        const double v = zv[u] - alpha * (qv[u] * y), r = d * v;
+        zb[e] = v;
+        rz += r * v;
+        rr += r * r;
+      }
+      at.advance(n, dI, dJ);
     }
-    at.advance(n, dI, dJ);
+    if (!MORE) break;
+    base += (int64_t)gridDim.x * VBLOCK;
+    if (base >= nd) break;
+    load(base);
   }
   const double a = block_sum(rz, sh);
   const double b = block_sum(rr, sh);
@@ -400,6 +417,7 @@ __global__ __launch_bounds__(PB) void poisson_update_kernel(double *__restrict__
 // update's alpha); unless r.r meets the tolerance, p = z + beta p, beta = r.z' /
 // r.z.  Work-group 0 keeps r.z' (the other parity slot), r.r, and the iteration
 // count once the tolerance is met.
+template <bool MORE>
 __global__ __launch_bounds__(PB) void poisson_dir_kernel(double *__restrict__ x, double *__restrict__ pv,
                                                          const double *__restrict__ z, int64_t nd,
                                                          double *__restrict__ scal, int it,
@@ -411,26 +429,25 @@ __global__ __launch_bounds__(PB) void poisson_dir_kernel(double *__restrict__ x,
   parts_load(part_rz, nparts, pz);
   parts_load(part_rr, nparts, pr);
   const double alpha = scal[S_ALPHA], rz_old = scal[S_RZ + (it & 1)], stop = scal[S_STOP];
-  const int64_t base = (int64_t)blockIdx.x * (PB * VU);
-  const int left = nd - base < PB * VU ? (int)(nd - base) : PB * VU;
-  double *xb = x + base, *pb = pv + base;
-  const double *zb = z + base;
   double pw[VU], zw[VU];
-  {
+  auto load_and_add = [&](int64_t base) {            // p and z of a block; x += alpha p
+    const int left = nd - base < VBLOCK ? (int)(nd - base) : VBLOCK;
     double xw[VU];
 #pragma unroll
     for (int u = 0; u < VU; ++u) {
       const int e = (int)threadIdx.x + PB * u;
-      pw[u] = e < left ? pb[e] : 0.0;
-      xw[u] = e < left ? xb[e] : 0.0;
-      zw[u] = e < left ? zb[e] : 0.0;
+      pw[u] = e < left ? pv[base + e] : 0.0;
+      xw[u] = e < left ? x[base + e] : 0.0;
+      zw[u] = e < left ? z[base + e] : 0.0;
     }
 #pragma unroll
     for (int u = 0; u < VU; ++u) {
       const int e = (int)threadIdx.x + PB * u;
-      if (e < left) xb[e] = fma(alpha, pw[u], xw[u]);
+      if (e < left) x[base + e] = fma(alpha, pw[u], xw[u]);
     }
-  }
+  };
+  int64_t base = (int64_t)blockIdx.x * VBLOCK;
+  load_and_add(base);
   const double rz = parts_sum(part_rz, nparts, pz, sh);
   const double rr = parts_sum(part_rr, nparts, pr, sh);
   const bool last = rr <= stop;
@@ -439,12 +456,21 @@ __global__ __launch_bounds__(PB) void poisson_dir_kernel(double *__restrict__ x,
     scal[S_RR] = rr;
     if (last) scal[S_STOPAT] = it + 1;
   }
-  if (last) return;
+  if (!MORE && last) return;
   const double beta = rz_old != 0 ? rz / rz_old : 0.0;
+  for (;;) {
+    if (!MORE || !last) {
+      const int left = nd - base < VBLOCK ? (int)(nd - base) : VBLOCK;
 #pragma unroll
-  for (int u = 0; u < VU; ++u) {
-    const int e = (int)threadIdx.x + PB * u;
-    if (e < left) pb[e] = fma(beta, pw[u], zw[u]);
+      for (int u = 0; u < VU; ++u) {
+        const int e = (int)threadIdx.x + PB * u;
+        if (e < left) pv[base + e] = fma(beta, pw[u], zw[u]);
+      }
+    }
+    if (!MORE) break;
+    base += (int64_t)gridDim.x * VBLOCK;
+    if (base >= nd) break;
+    load_and_add(base);
   }
 }
 
@@ -652,6 +678,7 @@ extern "C" int chfsi_poisson_solve(chfsi_ctx *c, const double *rho, int ncharges
   }
   const int64_t nb = std::min<int64_t>((nd + PB - 1) / PB, MAXG);   // element-wise grids (grid-stride)
   const int64_t nv = vec_grid(nd).x;                 // the two vector passes
+  const bool more = nv * VBLOCK < nd;
   const dim3 ga = apply_grid(M);
   const int64_t na = (int64_t)ga.x * ga.y * ga.z;  // product grid
   const int64_t npart = std::max(std::max(nb, na), nv);
@@ -694,10 +721,10 @@ extern "C" int chfsi_poisson_solve(chfsi_ctx *c, const double *rho, int ncharges
     const int k = std::min(std::min(std::max(launched / 4, 8), 32), max_iter - launched);
     for (int i = 0; i < k; ++i, ++launched) {
       poisson_stencil_launch(M, pv, q, kbs, m, scal, launched, pc, s);
-      hipLaunchKernelGGL(poisson_update_kernel, dim3((unsigned)nv), block, 2 * M.n * sizeof(double), s, z, q, m, M.n, nd, kInv4Pi, scal, launched,
-                         pc, (int)na, pa, pb);
-      hipLaunchKernelGGL(poisson_dir_kernel, dim3((unsigned)nv), block, 0, s, phi, pv, z, nd, scal, launched, pa, pb,
-                         (int)nv);
+      hipLaunchKernelGGL(more ? poisson_update_kernel<true> : poisson_update_kernel<false>, dim3((unsigned)nv), block,
+                         2 * M.n * sizeof(double), s, z, q, m, M.n, nd, kInv4Pi, scal, launched, pc, (int)na, pa, pb);
+      hipLaunchKernelGGL(more ? poisson_dir_kernel<true> : poisson_dir_kernel<false>, dim3((unsigned)nv), block, 0, s, phi,
+                         pv, z, nd, scal, launched, pa, pb, (int)nv);
     }
     HIPCHK(c, hipMemcpyAsync(hs, scal, sizeof(hs), hipMemcpyDeviceToHost, s));
     HIPCHK(c, hipStreamSynchronize(s));
