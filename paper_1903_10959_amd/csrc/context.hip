@@ -721,7 +721,7 @@ chfsi::JacobiJob chfsi::rr_eigen_job(chfsi_ctx *c, int ncols) {
 // The residuals of k rotated columns need Htilde applied to them: either HX is
 // rotated with X (a GEMM, 2 ncols flops per value at about 57 TFLOP/s: 0.035
 // ncols ps) or Htilde is applied again (about 5 ps per value of the tile
-// kernel's traffic, 25 of the general kernel's gathers).  Both give Htilde
+// kernel's traffic, 17 to 24 of the general kernel's gathers, p = 8 to 12).  Both give Htilde
 // times the rotated columns; the cheaper is taken unless the mode forces one.
 bool chfsi::rr_reapply(const chfsi_ctx *c, int ncols) {
   if (c->rr_residual != 0) return c->rr_residual == 2;

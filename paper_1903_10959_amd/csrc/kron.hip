@@ -633,50 +633,96 @@ __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(WAVES))) 
 // General kernel: any degree, size and row stride (row-major blocks).  One
 // thread per value of Y, lanes along the columns; the 3 (p + 2) values it
 // gathers come from the caches.  Used for degrees 8..12 and where a plane of
-// the block exceeds the tile kernel's 32-bit offsets.
+// the block exceeds the tile kernel's 32-bit offsets.  The coefficients, s1 times
+// an entry, wait in LDS.
+//
+// FP > 0: the degree, for blocks of more than 32 columns.  A wave's lanes are 64
+// columns of one node, whose index arithmetic is then scalar, and an element's
+// p + 1 values are all in flight at once: the latency of gathers one or two at a
+// time is what bounds the other form.  Columns come in groups of 64, the group
+// outermost, so that the planes a z line reaches stay in the last-level cache.
+// 16^3 cells x 128 columns, us per step, FP64 and FP32: p = 8 4,950 and 4,030, p =
+// 10 11,000 and 8,230 (with the degree at run time 7,270, 6,930, 18,260, 14,410;
+// dense cell products 13,390, 6,960, 35,030, 17,890).
 // ---------------------------------------------------------------------------
-template <typename T, bool CPLX>
-__global__ __launch_bounds__(256) void kron_general_kernel(KronProb<T> pr, int P, int lanes) {
+static constexpr int GEN_Q = 13;                     // nodes of an element's line, at most (p <= 12)
+template <typename T, bool CPLX, int FP>
+__global__ __launch_bounds__(256) void kron_general_kernel(KronProb<T> pr, int P_, int lanes_) {
+  static_assert(!(CPLX && FP > 0) && FP < GEN_Q, "complex blocks stop at degree 7");
+  const int P = FP > 0 ? FP : P_, lanes = FP > 0 ? 64 : lanes_;
   const int n = pr.n, n_el = pr.n_el, q = P + 1;
   const bool per = pr.periodic != 0;
-  const int rows = 256 / lanes;
-  const int64_t ncg = (pr.ncols + lanes - 1) / lanes;
+  __shared__ T cf[GEN_Q * GEN_Q], cc[CPLX ? GEN_Q * GEN_Q : 1];
+  __shared__ double cd[GEN_Q];                       // Ae's diagonal
+  for (int t = threadIdx.x; t < q * q; t += 256) {
+    cf[t] = (T)(pr.s1 * pr.ae[t]);
+    if (CPLX) cc[t] = (T)(pr.s1 * pr.ae[q * q + t]);
+    if (t % (q + 1) == 0) cd[t / (q + 1)] = pr.ae[t];
+  }
+  __syncthreads();
+  const int rows = 256 / lanes, lane = (int)threadIdx.x % lanes;
+  int row0 = (int)threadIdx.x / lanes;
+  if (FP > 0) row0 = __builtin_amdgcn_readfirstlane(row0);
+  const int ncg = (pr.ncols + lanes - 1) / lanes;
   const int64_t nd = (int64_t)n * n * n;
-  const int64_t nblk = (nd + rows - 1) / rows * ncg;
-  const double *ct = pr.ae + q * q;
+  const int64_t nrow = (nd + rows - 1) / rows, nblk = nrow * ncg;
+  auto rnd = [&](T x) -> T {
+    if constexpr (std::is_same<T, float>::value) return pr.bf16 ? (float)(__bf16)x : x;
+    else return x;
+  };
   for (int64_t w = blockIdx.x; w < nblk; w += gridDim.x) {
-    const int col = (int)(w % ncg) * lanes + threadIdx.x % lanes;
-    const int64_t d = w / ncg * rows + threadIdx.x / lanes;
-    if (col >= pr.ncols || d >= nd) continue;
-    const int id[3] = {(int)(d % n), (int)(d / n % n), (int)(d / n / n)};
-    const int64_t st[3] = {1, n, (int64_t)n * n};
-    auto at = [&](int64_t j) {
-      T x = pr.X[j * pr.ldx + col];
-      if constexpr (std::is_same<T, float>::value) x = pr.bf16 ? (float)(__bf16)x : x;
-      return x;
-    };
+    const int64_t cg = w / nrow, d = (w - cg * nrow) * rows + row0;
+    const int col = (int)cg * lanes + lane;
+    if (d >= nd || col >= pr.ncols) continue;
+    const int r = (int)(d / n), id[3] = {(int)(d - (int64_t)r * n), r % n, r / n};
+    const T *const own = pr.X + d * pr.ldx;
     T y = 0;
     double dg = pr.V[d] - pr.shift;
+    int64_t st = pr.ldx;                             // from one node of the line to the next
 #pragma unroll
     for (int dir = 0; dir < 3; ++dir) {
       const int I = id[dir] + (per ? 0 : 1), e = I / P, a = I - e * P;
-      const int64_t base = d - id[dir] * st[dir];
+      const T *const x0 = own - id[dir] * st;        // node 0 of the line
       T g = 0;
       // elements that hold the node: its own, and for an element end the one before
       for (int half = 0; half < (a == 0 ? 2 : 1); ++half) {
-        const int ee = e - half, row = half ? P : a;
-        dg += pr.ae[row * q + row];
-        for (int m = 0; m <= P; ++m) {
-          const int j = m == P ? line_dof(ee + 1, 0, P, n_el, per) : line_dof(ee, m, P, n_el, per);
-          if (j < 0 || m == row) continue;
-          const int64_t o = base + j * st[dir];
-          y = fma_t((T)(pr.s1 * pr.ae[row * q + m]), at(o), y);
-          if (CPLX) g = fma_t((T)(pr.s1 * ct[row * q + m]), pr.X[o * pr.ldx + (col ^ 1)], g);
+        const int row = half ? P : a, ee = e - half < 0 ? n_el - 1 : e - half;   // (before the first: periodic)
+        dg += cd[row];
+        // node m of the element is xe + m st, for m0 <= m <= m1 (Dirichlet ends
+        // left out); the last one of a periodic line is its first
+        const int m0 = !per && ee == 0 ? 1 : 0, m1 = per || ee + 1 < n_el ? P : P - 1;
+        const bool wrap = per && ee + 1 == n_el;
+        const T *const xe = x0 + (int64_t)(ee * P - (per ? 0 : 1)) * st;
+        const T *const ca = cf + row * q, *const cb = cc + (CPLX ? row * q : 0);
+        if constexpr (FP > 0) {
+          T v[FP + 1];
+#pragma unroll
+          for (int m = 0; m <= FP; ++m) {
+            const T *x = m == FP && wrap ? x0 : xe + m * st;
+            if (m < m0 || m > m1) x = own;           // (not used)
+            v[m] = x[col];
+          }
+#pragma unroll
+          for (int m = 0; m <= FP; ++m)
+            if (m >= m0 && m <= m1 && m != row) y = fma_t(ca[m], rnd(v[m]), y);
+        } else {
+          auto add = [&](int m, const T *x) {
+            y = fma_t(ca[m], rnd(x[col]), y);
+            if (CPLX) g = fma_t(cb[m], x[col ^ 1], g);
+          };
+          const T *x = xe + m0 * st;
+#pragma unroll 4
+          for (int m = m0; m < row; ++m, x += st) add(m, x);
+          x += st;
+#pragma unroll 4
+          for (int m = row + 1; m < P; ++m, x += st) add(m, x);
+          if (row < P && m1 == P) add(P, wrap ? x0 : x);
         }
       }
       if (CPLX) y = fma_t((T)((col & 1) ? -pr.k[dir] : pr.k[dir]), g, y);
+      st *= n;
     }
-    y = fma_t((T)(pr.s1 * dg), pr.X[d * pr.ldx + col], y);   // (the value itself, as in the tile kernel)
+    y = fma_t((T)(pr.s1 * dg), own[col], y);         // (the value itself, as in the tile kernel)
     if (pr.Xp) y = fma_t((T)pr.s2, pr.Xp[d * pr.ldy + col], y);
     pr.Y[d * pr.ldy + col] = y;
   }
@@ -841,8 +887,17 @@ static int launch(const KronArgs<T> &a, hipStream_t s) {
   while (lanes < 64 && lanes < a.ncols) lanes *= 2;
   const int64_t nd = (int64_t)pr.n * pr.n * pr.n;
   const int64_t blocks = (nd + 256 / lanes - 1) / (256 / lanes) * ((pr.ncols + lanes - 1) / lanes);
-  hipLaunchKernelGGL((kron_general_kernel<T, CPLX>), dim3((unsigned)std::min<int64_t>(blocks, 1 << 24)), dim3(256), 0, s,
-                     pr, a.p, lanes);
+  const dim3 g((unsigned)std::min<int64_t>(blocks, 1 << 24));
+  auto go = [&](auto kern) { hipLaunchKernelGGL(kern, g, dim3(256), 0, s, pr, a.p, lanes); };
+  if constexpr (!CPLX)
+    if (lanes == 64) switch (a.p) {
+        case 8: return go(kron_general_kernel<T, false, 8>), 0;
+        case 9: return go(kron_general_kernel<T, false, 9>), 0;
+        case 10: return go(kron_general_kernel<T, false, 10>), 0;
+        case 11: return go(kron_general_kernel<T, false, 11>), 0;
+        case 12: return go(kron_general_kernel<T, false, 12>), 0;
+      }
+  go(kron_general_kernel<T, CPLX, 0>);
   return 0;
 }
 int kron_launch(const KronArgs<double> &a, hipStream_t s) { return launch<double, false>(a, s); }
