@@ -235,7 +235,7 @@ int build_sweep(chfsi_batch *B, Sweep<T> &S, const std::vector<int> &ids, const 
   for (size_t m = 0; m < ids.size(); ++m) {
     const Prob &p = B->probs[ids[m]];
     if (copied[m])
-      copy_cols_launch<double, T>(ColBuf<double>{p.X, p.ld, 0}, INT32_MAX, hp[m].buf[0], group_of(p.c, sizeof(T)),
+      copy_cols_launch<double, T>(ColBuf<double>{p.X, p.ld, 0}, INT32_MAX, hp[m].buf[0], group_of(p.c, sizeof(T), p.o.nblock),
                                   p.c->mesh.n_dof, p.o.nblock, B->stream);
   }
   int lerr = 0;
@@ -247,7 +247,7 @@ int build_sweep(chfsi_batch *B, Sweep<T> &S, const std::vector<int> &ids, const 
     const Prob &p = B->probs[ids[m]];
     const int last = B->degree & 1;
     if (copied[m] || last)
-      copy_cols_launch<T, double>(hp[m].buf[last], group_of(p.c, sizeof(T)), ColBuf<double>{p.X, p.ld, 0}, INT32_MAX,
+      copy_cols_launch<T, double>(hp[m].buf[last], group_of(p.c, sizeof(T), p.o.nblock), ColBuf<double>{p.X, p.ld, 0}, INT32_MAX,
                                   p.c->mesh.n_dof, p.o.nblock, B->stream);
   }
   hipError_t ce = hipStreamEndCapture(B->stream, &S.graph);

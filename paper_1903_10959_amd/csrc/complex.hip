@@ -155,7 +155,7 @@ int filter_c(chfsi_ctx *c, double *X, int64_t ld, int ncols, int degree, double 
       if (int r = cheb_step_c(c, {in.p, in.ld, in.cg}, k > 0 ? out.p : nullptr, out, w, f.s1, f.s2, f.shift)) return r;
     }
     if (degree & 1)
-      copy_cols_launch<double, double>(buf[1], group_of(c, sizeof(double), 2 * ld), buf[0], INT32_MAX, nd, 2 * w,
+      copy_cols_launch<double, double>(buf[1], group_of(c, sizeof(double), 2 * w, 2 * ld), buf[0], INT32_MAX, nd, 2 * w,
                                        c->stream);
   }
   HIPCHK(c, c->flag.ensure(4 * sizeof(int)));

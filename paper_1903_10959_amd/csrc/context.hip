@@ -67,8 +67,10 @@ KronArgs<T> kron_args(const chfsi_ctx *c, int ncols) {
 }  // namespace
 
 size_t chfsi::work_bytes(const chfsi_ctx *c, int w, size_t elem) {
-  const int g = kron_group(c->mesh.p, elem);
-  const size_t cols = g ? (size_t)(w + g - 1) / g * g : (size_t)w;
+  // (a narrower block that is grouped where w columns are not has whole groups of
+  // fewer than w columns)
+  const int g = group_of(c, elem, w);
+  const size_t cols = g == INT32_MAX ? (size_t)w : (size_t)(w + g - 1) / g * g;
   return (size_t)c->mesh.n_dof * cols * elem;
 }
 
@@ -509,7 +511,7 @@ extern "C" int chfsi_apply(chfsi_ctx *c, const double *X, double *Y, int64_t ld,
   for (int j0 = 0; j0 < ncols; j0 += bw) {
     const int w = std::min(bw, ncols - j0);
     const ColBuf<float> x = work_block<float>(c, c->fbuf[0].as<float>(), w), y = work_block<float>(c, c->fbuf[1].as<float>(), w);
-    const int gw = group_of(c, sizeof(float));
+    const int gw = group_of(c, sizeof(float), w);
     copy_cols_launch<double, float>({const_cast<double *>(X) + j0, ld, 0}, INT32_MAX, x, gw, nd, w, c->stream);
     if (int r = cheb_step_t<float>(c, {x.p, x.ld, x.cg}, nullptr, y, w, 1.0, 0.0, 0.0, bf)) return r;
     copy_cols_launch<float, double>(y, gw, {Y + j0, ld, 0}, INT32_MAX, nd, w, c->stream);
@@ -556,13 +558,13 @@ extern "C" int chfsi_chebyshev_filter(chfsi_ctx *c, double *X, int64_t ld, int n
       const ColBuf<double> buf[2] = {row_major<double>(c, X + j0, ld), work_block<double>(c, c->fbuf[0].as<double>(), w, ld)};
       if (int r = filter_block<double>(c, buf, w, degree, a, b, a0)) return r;
       if (degree & 1)
-        copy_cols_launch<double, double>(buf[1], group_of(c, sizeof(double), ld), buf[0], INT32_MAX, nd, w, c->stream);
+        copy_cols_launch<double, double>(buf[1], group_of(c, sizeof(double), w, ld), buf[0], INT32_MAX, nd, w, c->stream);
     }
   } else {
     for (int i = 0; i < 2; ++i) HIPCHK(c, c->fbuf[i].ensure(work_bytes(c, bw, sizeof(float))));
-    const int gw = group_of(c, sizeof(float));
     for (int j0 = 0; j0 < ncols; j0 += bw) {
       const int w = std::min(bw, ncols - j0);
+      const int gw = group_of(c, sizeof(float), w);
       const ColBuf<float> buf[2] = {work_block<float>(c, c->fbuf[0].as<float>(), w),
                                     work_block<float>(c, c->fbuf[1].as<float>(), w)};
       const ColBuf<double> x{X + j0, ld, 0};

@@ -134,21 +134,27 @@ template <typename T>
 inline ColBuf<T> row_major(const chfsi_ctx *c, T *p, int64_t ld) {
   return ColBuf<T>{p, ld, kron_group(c->mesh.p, sizeof(T))};
 }
-// Columns to a group of the library's own block (INT32_MAX: row-major): grouped
-// where the tile kernel runs, also on the row-major block of stride ld that it
-// alternates with.
-inline int group_of(const chfsi_ctx *c, size_t elem, int64_t ld = 1) {
-  return kron_tiled(c->mesh.p, c->mesh.n, std::max<int64_t>(ld, 32), elem) ? kron_group(c->mesh.p, elem) : INT32_MAX;
+// Columns to a group of the library's own block of w columns (INT32_MAX:
+// row-major): grouped where the tile kernel runs, also on the row-major block of
+// stride ld that it alternates with, unless whole groups (one such block in FP64, two
+// in FP32) take 16 MiB more than three blocks of w columns would: a column of a large
+// mesh in FP32 would otherwise take 32 times its memory.  (Row-major is also the
+// faster there, 32^3 cells of degree 5, FP32, 10 steps of 1 and 33 columns 4.1 -> 3.1
+// and 9.2 -> 8.1 ms, but not on small meshes, 8^3 of degree 4 x 33 155 -> 170 us.)
+inline int group_of(const chfsi_ctx *c, size_t elem, int w, int64_t ld = 1) {
+  const int g = kron_group(c->mesh.p, elem);
+  if (g == 0 || !kron_tiled(c->mesh.p, c->mesh.n, std::max<int64_t>(ld, 32), elem)) return INT32_MAX;
+  const int64_t extra = (elem == 8 ? 1 : 2) * ((w + g - 1) / g * g) - 3 * w;   // columns
+  return extra * c->mesh.n_dof * (int64_t)elem > (16 << 20) ? INT32_MAX : g;
 }
 // A w-column block of the library's own.
 template <typename T>
 inline ColBuf<T> work_block(const chfsi_ctx *c, T *p, int w, int64_t ld = 1) {
-  const int g = group_of(c, sizeof(T), ld);
+  const int g = group_of(c, sizeof(T), w, ld);
   if (g == INT32_MAX) return row_major<T>(c, p, w);
   return ColBuf<T>{p, g, c->mesh.n_dof * g};
 }
-// Device bytes of a w-column block of the library's own (columns padded to
-// whole groups).
+// Device bytes of a block of the library's own of w columns or fewer.
 size_t work_bytes(const chfsi_ctx *c, int w, size_t elem);
 // Y = s1 (Htilde_k - shift) X + s2 Xp on complex blocks seen as 2 ncols real
 // columns (Xp in Y's layout, or null).
