@@ -398,13 +398,15 @@ const char *chfsi_batch_last_error(const chfsi_batch *b);
 int chfsi_batch_set_threads(chfsi_batch *b, int threads);
 /* Device bytes a context holds once it is in a batch session with nblock
  * vectors (mesh and potential tables, the CholGS / Rayleigh-Ritz workspaces,
- * three FP64-sized recursion buffers and HX), not counting the caller's block
+ * the recursion's two blocks, FP64-sized, and HX), not counting the caller's block
  * (pure; no device access; 0 for arguments outside the supported range). */
 size_t chfsi_batch_footprint_bytes(int n_el, int p, int nblock);
 
 /* ---- admission / diagnostics ---------------------------------------------
- * Device bytes a context needs for (n_el, p) and a solve of nblock vectors with
- * the given filter block width and precision (pure; no device access). */
+ * Device bytes that suffice a context for (n_el, p) and a solve of nblock vectors
+ * with the given filter block width and precision: an upper bound, with room for
+ * three filter blocks where the recursion alternates one or two (pure; no device
+ * access). */
 size_t chfsi_footprint_bytes(int n_el, int p, int nblock, int block_width, chfsi_prec prec);
 /* Device bytes the context holds right now (its buffers only grow until
  * destroy, so a reused context may hold more than a new problem needs). */

@@ -424,9 +424,9 @@ extern "C" int chfsi_batch_add(chfsi_batch *b, chfsi_ctx *c, const chfsi_opts *o
     if (!p.done && p.c == c) return bfail(b, CHFSI_ERR_ARG, "batch: the context is already in the session");
   if (int r = ensure_small(c, o->nblock)) return bfail(b, r, "batch: " + c->err);
   const size_t bytes = (size_t)c->mesh.n_dof * o->nblock * sizeof(double);
-  // FP64-sized for any rung, columns padded to whole groups
+  // the two blocks of the recursion, FP64-sized for any rung
   const size_t wbytes = std::max(work_bytes(c, o->nblock, sizeof(double)), work_bytes(c, o->nblock, sizeof(float)));
-  for (int k = 0; k < 3; ++k)
+  for (int k = 0; k < 2; ++k)
     if (c->fbuf[k].ensure(wbytes) != hipSuccess) return bfail(b, CHFSI_ERR_OOM, "batch: filter buffers");
   if (c->HX.ensure(bytes) != hipSuccess) return bfail(b, CHFSI_ERR_OOM, "batch: HX buffer");
   Prob p;
@@ -569,8 +569,8 @@ extern "C" size_t chfsi_batch_footprint_bytes(int n_el, int p, int nblock) {
   b += rmul_scratch_elems((int64_t)nd, nblock) * 8;
   b += gram_part_elems((int64_t)nd, nblock) * 8;
   b += (size_t)resid_nchunk((int64_t)nd) * nb * 8;
-  // the session's three recursion buffers (FP64-sized for either rung, columns
-  // in whole groups) and HX
-  b += 3 * nd * std::max((nb + 15) / 16 * 16 * 8, (nb + 31) / 32 * 32 * 4) + nd * nb * 8;
+  // the two blocks of the recursion (FP64-sized for either rung, columns in whole
+  // groups) and HX
+  b += 2 * nd * std::max((nb + 15) / 16 * 16 * 8, (nb + 31) / 32 * 32 * 4) + nd * nb * 8;
   return b;
 }

@@ -1028,7 +1028,7 @@ extern "C" size_t chfsi_footprint_bytes(int n_el, int p, int nblock, int block_w
   const size_t bw = (size_t)std::min(block_width > 0 ? block_width : 128, nblock);
   const size_t elem = prec == CHFSI_FP64 ? 8 : 4;
   size_t b = nd * 16;                                              // M^-1/2 and V
-  // filter buffers: at most two blocks of columns padded to whole groups
+  // filter buffers: at most two blocks of columns padded to whole groups, and room
   b += 2 * nd * ((bw + 31) / 32 * 32) * elem + nd * bw * elem;
   b += nd * nblock * 8;                                            // HX
   const size_t nn = (size_t)nblock * nblock;

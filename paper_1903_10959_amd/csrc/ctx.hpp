@@ -56,7 +56,7 @@ struct chfsi_ctx {
   int rr_residual = 0;    // Ritz residuals: 0 cost model, 1 rotate HX, 2 apply Htilde again
   int jac_sweeps = 40;    // cap on Jacobi sweeps of the projected eigensolve
   // workspaces
-  chfsi::DevBuf fbuf[3];      // filter recursion buffers
+  chfsi::DevBuf fbuf[2];      // the filter recursion's blocks
   chfsi::DevBuf occ_d;    // density: fr occupancy weights
   double kvec[3] = {0, 0, 0};
   double kin_k = 0;       // sum over directions of lambda_max of the 1D Bloch operators at kvec
@@ -81,7 +81,7 @@ struct chfsi_ctx {
   // every device buffer the context owns
   template <typename F> void each_buf(F f) {
     chfsi::DevBuf *all[] = {&minv64, &V64, &vpart, &ae64, &fbuf[0],
-                            &fbuf[1], &fbuf[2], &gram_part, &Smat, &dinv, &Zmat, &Wmat, &jac_work, &evals_d,
+                            &fbuf[1], &gram_part, &Smat, &dinv, &Zmat, &Wmat, &jac_work, &evals_d,
                             &resid_part, &resid_d, &flag, &HX, &diag0, &minratio, &rscratch, &occ_d, &kgroup_d, &pois_kb, &pois_m, &pois_work, &pois_q, &csel};
     for (chfsi::DevBuf *b : all) f(*b);
   }
