@@ -424,8 +424,8 @@ int chfsi_last_filter_timing(chfsi_ctx *ctx, double *ms_cells, int *n_launches, 
 /* Tile of the Chebyshev-step kernel (Sec. 3.3 leaves the blocking to the
  * implementation): -1 = built-in choice (default), 0 = 2 x 2 cells per
  * work-group, 1 = 4 x 2 cells where that tile exists (FP64, degrees 3..5; else
- * as 0).  Every variant computes the same bits; an autotuner times them per
- * degree and precision and sets the faster.  Applies to later filter/apply
+ * as 0).  Every variant computes the same bits; an autotuner times them where
+ * there are two, per degree, mesh and column count.  Applies to later filter/apply
  * calls and to batch sweeps built after it (set it before adding the context
  * to a batch session).  Errors: CHFSI_ERR_ARG for a null ctx or a variant
  * outside -1..1. */
