@@ -95,8 +95,8 @@ void nonfinite_launch(const T *X, int64_t ld, int64_t nrows, int ncols, int *fla
 // G = A^T B over nrows rows, lower-triangular tiles, split over rows; partial
 // tiles go to `part` and are summed in a fixed order into G (n x n, row-major,
 // lower triangle mirrored to upper).  mixed: 64x64 diagonal blocks in FP64, the
-// rest with FP32 inputs/products.  The number of splits follows the device's
-// resident work-groups; gram_part_elems bounds the partial buffer of any launch.
+// rest with FP32 inputs/products.  The number of splits follows from the rows and
+// columns; gram_part_elems bounds the partial buffer of any launch.
 size_t gram_part_elems(int64_t nrows, int n);
 void gram_launch(const double *A, int64_t lda, const double *B, int64_t ldb, int64_t nrows, int n, double *part,
                  double *G, int mixed, hipStream_t s);
