@@ -200,8 +200,8 @@ int build_sweep(chfsi_batch *B, Sweep<T> &S, const std::vector<int> &ids, const 
     if (tiles < 0) return bfail(B, CHFSI_ERR_ARG, "batch: no step kernel for a problem's degree");
     total += tiles * c->mesh.n_el * c->mesh.p;
   }
-  BCHK(B, S.coef.ensure((size_t)4 * B->degree * ids.size() * sizeof(double)));
-  for (size_t m = 0; m < hp.size(); ++m) hp[m].coef = S.coef.template as<double>() + (size_t)4 * B->degree * m;
+  BCHK(B, S.coef.ensure((size_t)3 * B->degree * ids.size() * sizeof(double)));
+  for (size_t m = 0; m < hp.size(); ++m) hp[m].coef = S.coef.template as<double>() + (size_t)3 * B->degree * m;
   // (degree, tile variant) -> work items; a problem's z chunks as if it had its
   // share of the chip
   std::map<std::pair<int, int>, std::vector<int4>> lists;
@@ -273,19 +273,19 @@ int run_sweep(chfsi_batch *B, Sweep<T> &S, const std::vector<int> &ids, float *m
     B->build_ms += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
   }
   const int m_deg = B->degree;
-  S.hcoef.assign((size_t)4 * m_deg * ids.size(), 0.0);
+  S.hcoef.assign((size_t)3 * m_deg * ids.size(), 0.0);
   for (size_t m = 0; m < ids.size(); ++m) {
     Prob &p = B->probs[ids[m]];
     const int nb = p.o.nblock;
     const double a = p.evals[nb - 1], a0 = p.evals[0], b = p.c->ub;
     if (!(a0 < a && a < b)) return bfail(B, CHFSI_ERR_STATE, "batch: internal: unchecked filter bounds");
     ChebRecursion rec(a, b, a0);
-    double *tc = S.hcoef.data() + (size_t)4 * m_deg * m;
-    for (int k = 0; k < m_deg; ++k, tc += 4) {
+    double *tc = S.hcoef.data() + (size_t)3 * m_deg * m;
+    for (int k = 0; k < m_deg; ++k) {
       const ChebRecursion::Step f = rec.next();
-      tc[0] = f.s1;
-      tc[1] = f.s2;
-      split_shift(f.shift, p.c->mesh.dia_quantum, tc[2], tc[3]);
+      tc[3 * k] = f.s1;
+      tc[3 * k + 1] = f.s2;
+      tc[3 * k + 2] = f.shift;
     }
   }
   BCHK(B, hipMemcpyAsync(S.coef.p, S.hcoef.data(), S.hcoef.size() * sizeof(double), hipMemcpyHostToDevice, B->stream));

@@ -59,7 +59,6 @@ KronArgs<T> kron_args(const chfsi_ctx *c, int ncols) {
   a.s1 = 1;
   a.s2 = 0;
   a.shift = 0;
-  a.quantum = M.dia_quantum;
   a.variant = c->tile_variant;
   return a;
 }
@@ -152,7 +151,6 @@ static int set_mesh_impl(chfsi_ctx *c, double L, int n_el, int p, bool periodic)
   const MeshTables &M = c->mesh;
   std::vector<double> ae(M.ae);
   ae.insert(ae.end(), M.ce.begin(), M.ce.end());
-  ae.insert(ae.end(), M.dia.begin(), M.dia.end());
   HIPCHK(c, c->ae64.ensure(ae.size() * sizeof(double)));
   HIPCHK(c, hipMemcpyAsync(c->ae64.p, ae.data(), ae.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
   std::vector<double> mi(M.n_dof);
@@ -469,8 +467,7 @@ int chfsi::cheb_step_c(chfsi_ctx *c, const ColBuf<const double> &X, const double
   a.s1 = s1;
   a.s2 = s2;
   // the diagonal of Htilde_k is V + |k|^2 / 2
-  a.shift = shift;
-  a.shift2 = -0.5 * (c->kvec[0] * c->kvec[0] + c->kvec[1] * c->kvec[1] + c->kvec[2] * c->kvec[2]);
+  a.shift = shift - 0.5 * (c->kvec[0] * c->kvec[0] + c->kvec[1] * c->kvec[1] + c->kvec[2] * c->kvec[2]);
   for (int d = 0; d < 3; ++d) a.k[d] = c->kvec[d];
   if (kron_launch_complex(a, c->stream) != 0) return fail(c, CHFSI_ERR_ARG, "Htilde_k step: block too large for one launch");
   if (c->timing) c->cell_vecs += (int64_t)c->mesh.n_cells * 2 * ncols;

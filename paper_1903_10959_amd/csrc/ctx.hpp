@@ -51,7 +51,7 @@ struct chfsi_ctx {
   // device tables
   chfsi::DevBuf minv64, V64;
   chfsi::DevBuf vpart; // partial maxima of a potential given on the device
-  chfsi::DevBuf ae64;  // 1D element matrices Ae and C of the Chebyshev step and A's diagonal in two parts
+  chfsi::DevBuf ae64;  // 1D element matrices Ae and C of the Chebyshev step, (p+1)^2 each
   int tile_variant = -1;  // tile of the step kernel (-1: built-in choice)
   int rr_residual = 0;    // Ritz residuals: 0 cost model, 1 rotate HX, 2 apply Htilde again
   int jac_sweeps = 40;    // cap on Jacobi sweeps of the projected eigensolve

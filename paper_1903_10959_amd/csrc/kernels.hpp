@@ -1,7 +1,6 @@
 // Host-side launchers of the device kernels (internal interface of the library).
 #pragma once
 #include <hip/hip_runtime.h>
-#include <cmath>
 #include <cstdint>
 #include <vector>
 
@@ -33,11 +32,9 @@ struct KronArgs {
   const T *Xp;
   ColBuf<T> Y;
   const double *V;     // [n_dof]
-  const double *ae;    // 1D element matrices Ae and C, (p+1)^2 each, and A's diagonal in two parts, 2 p
+  const double *ae;    // 1D element matrices Ae and C, (p+1)^2 each
   int n_el, p, n, periodic, ncols;
   double s1, s2, shift;
-  double shift2 = 0;   // added to the shift, small against it
-  double quantum;      // what the diagonal's first parts are multiples of
   int variant = -1;    // tile: -1 built-in choice, 0 2 x 2 cells, 1 4 x 2 where available
   int bf16 = 0;        // float: X enters the products with the 1D matrices' off-diagonal entries rounded to BF16
   double k[3] = {0, 0, 0};   // complex: Bloch vector
@@ -45,19 +42,12 @@ struct KronArgs {
 int kron_launch(const KronArgs<double> &a, hipStream_t s);
 int kron_launch(const KronArgs<float> &a, hipStream_t s);
 // Complex blocks as interleaved (re, im) real columns (a.ncols even), a.k the
-// Bloch vector of the -i k.G term (its |k|^2/2 is the caller's, in a.shift2).
+// Bloch vector of the -i k.G term (its |k|^2/2 is the caller's, in a.shift).
 int kron_launch_complex(const KronArgs<double> &a, hipStream_t s);
 // A group of nk k-points (kv: 3 nk values on the device, host_kv on the host)
 // in one launch: block g at X + g xstride (Y + g ystride, real elements).
 int kron_launch_kpts(const KronArgs<double> &a, int nk, const double *kv, const double *host_kv, int64_t xstride,
                      int64_t ystride, hipStream_t s);
-// The two parts of a shift as the kernels add them to the diagonal's: a multiple of
-// quantum (a power of two) and the rest.
-inline void split_shift(double shift, double quantum, double &hi, double &lo) {
-  const double n = shift / quantum;
-  hi = std::fabs(n) < 0x1p52 ? std::rint(n) * quantum : shift;
-  lo = shift - hi;
-}
 // Cells per z chunk of a march by `tiles` tiles.
 int kron_zlen(int n_el, int p, int64_t tiles);
 
@@ -67,7 +57,7 @@ template <typename T>
 struct KronBatchProblem {
   ColBuf<T> buf[2];
   const double *V, *ae;
-  const double *coef;  // [degree x 4]: s1, s2 and the shift's two parts per step
+  const double *coef;  // [degree x 3]: s1, s2, shift per step
   int n_el, n, periodic, ncols, bf16;
 };
 // The tile variant a problem runs (its context's setting, or for -1 the

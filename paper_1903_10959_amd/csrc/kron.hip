@@ -117,25 +117,11 @@ struct KronProb {
   // coefficients stay in double until they are complete (s1 times an entry of
   // Ae, s1 times a whole diagonal entry), also for float blocks
   const double *V;    // [n_dof]
-  const double *ae;   // Ae [(P+1)^2], the first-derivative matrix C [(P+1)^2], A's diagonal [2 P] (see Diag)
+  const double *ae;   // Ae [(P+1)^2], then the first-derivative matrix C [(P+1)^2]
   int n_el, n, periodic, ncols;
-  double s1, s2;
-  double sh, sl;      // the shift in two parts (see Diag)
+  double s1, s2, shift;
   int bf16;           // (BF tiles) round the values that enter the products to BF16
   double k[3];        // complex: Bloch vector
-};
-
-// A's diagonal at node a of an element (0 <= a < P) is hi(a) + lo(a): a multiple of a
-// power of two, coarse enough for sums of three of them and of a shift of their size,
-// split the same way, to be exact, and the rest.  Summed as plain doubles the
-// diagonal's rounding errors, the same at every such node, were most of a filter's
-// error (degree 20 at p = 7: 6.8e-15 of the block, 2.3e-15 so).
-struct Diag {
-  const double *tab;
-  int P;
-  __device__ __forceinline__ Diag(const double *ae, int p) : tab(ae + 2 * (p + 1) * (p + 1)), P(p) {}
-  __device__ __forceinline__ double hi(int a) const { return tab[a]; }
-  __device__ __forceinline__ double lo(int a) const { return tab[P + a]; }
 };
 
 // DoF index along a line of local node `a` of element e (e may lie one beyond
@@ -168,8 +154,8 @@ __device__ __forceinline__ int line_dof(int e, int a, int P, int n_el, bool peri
 //     plane adds to all of them, and the finished planes are stored when the
 //     next element's first plane arrives;
 //   * the whole diagonal (the three directions', V and the shift, which
-//     cancel in part) is summed in double, once per node and with one rounding
-//     besides V's, and applied as one coefficient.
+//     cancel in part) is summed in double, once per node, and applied as one
+//     coefficient.
 // The scheduling barriers keep the LDS reads of one output row from being
 // hoisted over the others': without them the register need grows past two
 // work-groups' share (measured, FP64 p = 5: 209 against 168 registers).  A
@@ -220,7 +206,7 @@ __device__ __forceinline__ void kron_tile(const KronProb<typename C::T> &pr, int
   constexpr bool CPLX = C::CPLX;
   __shared__ __align__(16) char lds[C::W * C::H * C::NODE];
   __shared__ T dlds[C::NN];          // this plane's diagonal coefficients
-  __shared__ double dxy[C::NN], lxy[C::NN];   // the x and y parts of the diagonal less the shift, and their rest
+  __shared__ double dxy[C::NN];      // the x and y parts of the diagonal less the shift
   __shared__ T xdl[C::XD_LDS ? NA * C::NT : 1];      // a thread's own values, NT apart
   const int t = threadIdx.x;
   const int row = __builtin_amdgcn_readfirstlane(t / C::L);    // wave row
@@ -256,7 +242,7 @@ __device__ __forceinline__ void kron_tile(const KronProb<typename C::T> &pr, int
   auto A = [&](int i, int j) -> T { return ae[canon(P, i, j)]; };
   auto Cc = [&](int i, int j) -> T { return canon_sign(P, i, j) > 0 ? ce[canon(P, i, j)] : -ce[canon(P, i, j)]; };
   const T s2 = uniform((T)pr.s2);
-  const Diag dia(pr.ae, P);
+  auto diag1 = [&](int i) { return i == 0 ? 2.0 * pr.ae[0] : pr.ae[i * (P + 1) + i]; };   // of the assembled 1D operator
   // -i k g: re += k g_im, im -= k g_re, with re and im in neighbouring lanes
   const T sgn = (cl & 1) ? T(-1) : T(1);
   auto mul_ik = [&](int dir, T g) -> T { return (sgn * (T)pr.k[dir]) * swap_pair(g); };
@@ -278,8 +264,7 @@ __device__ __forceinline__ void kron_tile(const KronProb<typename C::T> &pr, int
     const int va = t % P, vc = t / P % (CX * CY), vb = t / P / (CX * CY);
     const int vx = line_dof(ex0 + vc % CX, va, P, n_el, per), vy = line_dof(ey0 + vc / CX, vb, P, n_el, per);
     if (vx >= 0 && vy >= 0) ov = (unsigned)(vy * n + vx) * 8u;
-    dxy[t] = dia.hi(va) + dia.hi(vb) - pr.sh;                    // (read by this thread only)
-    lxy[t] = dia.lo(va) + dia.lo(vb) - pr.sl;
+    dxy[t] = diag1(va) + diag1(vb) - pr.shift;                   // (read by this thread only)
   }
   const T *own_d = dlds + (b * CX * CY + cell) * P;
 
@@ -440,7 +425,7 @@ __device__ __forceinline__ void kron_tile(const KronProb<typename C::T> &pr, int
         }
         int td = t;
         asm("" : "+v"(td));                        // (the sum is not kept per plane)
-        if (t < C::NN) dlds[t] = (T)(pr.s1 * ((vv + (lxy[td] + dia.lo(c))) + (dxy[td] + dia.hi(c))));
+        if (t < C::NN) dlds[t] = (T)(pr.s1 * (vv + (dxy[td] + diag1(c))));
 #pragma unroll
         for (int a = 0; a < NO; ++a) dg[a] = s2 * xp[a];
         if (c == 0) {
@@ -587,8 +572,7 @@ __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(WAVES))) 
 
 // Batched: work item (problem, tx | ty << 16, z0 | nz << 16, column group);
 // the step's buffer roles (in, out = previous) are the same for every problem,
-// its coefficients come from the problem's table (s1, s2 and the shift's two parts
-// per step).
+// its coefficients come from the problem's table (s1, s2, shift per step).
 template <typename C, int WAVES>
 __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(WAVES))) void kron_batch_kernel(
     const KronBatchProblem<typename C::T> *__restrict__ probs, const int4 *__restrict__ work, int step) {
@@ -610,11 +594,10 @@ __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(WAVES))) 
   p.n = B.n;
   p.periodic = B.periodic;
   p.ncols = B.ncols;
-  const double *coef = B.coef + 4 * step;
+  const double *coef = B.coef + 3 * step;
   p.s1 = coef[0];
   p.s2 = coef[1];
-  p.sh = coef[2];
-  p.sl = coef[3];
+  p.shift = coef[2];
   p.bf16 = B.bf16;
   kron_tile<C>(p, w.y & 0xffff, w.y >> 16, w.z & 0xffff, w.z >> 16, w.w);
 }
@@ -642,7 +625,7 @@ __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(WAVES))) 
     pr.k[d] = kv[3 * g + d];
     k2 += pr.k[d] * pr.k[d];
   }
-  pr.sl = -0.5 * k2;
+  pr.shift = -0.5 * k2;
   kron_tile<C>(pr, tx, ty, z0, nz, cg);
 }
 
@@ -670,11 +653,12 @@ __global__ __launch_bounds__(256) void kron_general_kernel(KronProb<T> pr, int P
   const int n = pr.n, n_el = pr.n_el, q = P + 1;
   const bool per = pr.periodic != 0;
   __shared__ T cf[GEN_Q * GEN_Q], cc[CPLX ? GEN_Q * GEN_Q : 1];
+  __shared__ double cd[GEN_Q];                       // Ae's diagonal
   for (int t = threadIdx.x; t < q * q; t += 256) {
     cf[t] = (T)(pr.s1 * pr.ae[t]);
     if (CPLX) cc[t] = (T)(pr.s1 * pr.ae[q * q + t]);
+    if (t % (q + 1) == 0) cd[t / (q + 1)] = pr.ae[t];
   }
-  const Diag dia(pr.ae, P);
   __syncthreads();
   const int rows = 256 / lanes, lane = (int)threadIdx.x % lanes;
   int row0 = (int)threadIdx.x / lanes;
@@ -693,18 +677,17 @@ __global__ __launch_bounds__(256) void kron_general_kernel(KronProb<T> pr, int P
     const int r = (int)(d / n), id[3] = {(int)(d - (int64_t)r * n), r % n, r / n};
     const T *const own = pr.X + d * pr.ldx;
     T y = 0;
-    double dh = -pr.sh, dl = -pr.sl;
+    double dg = pr.V[d] - pr.shift;
     int64_t st = pr.ldx;                             // from one node of the line to the next
 #pragma unroll
     for (int dir = 0; dir < 3; ++dir) {
       const int I = id[dir] + (per ? 0 : 1), e = I / P, a = I - e * P;
       const T *const x0 = own - id[dir] * st;        // node 0 of the line
       T g = 0;
-      dh += dia.hi(a);
-      dl += dia.lo(a);
       // elements that hold the node: its own, and for an element end the one before
       for (int half = 0; half < (a == 0 ? 2 : 1); ++half) {
         const int row = half ? P : a, ee = e - half < 0 ? n_el - 1 : e - half;   // (before the first: periodic)
+        dg += cd[row];
         // node m of the element is xe + m st, for m0 <= m <= m1 (Dirichlet ends
         // left out); the last one of a periodic line is its first
         const int m0 = !per && ee == 0 ? 1 : 0, m1 = per || ee + 1 < n_el ? P : P - 1;
@@ -739,7 +722,6 @@ __global__ __launch_bounds__(256) void kron_general_kernel(KronProb<T> pr, int P
       if (CPLX) y = fma_t((T)((col & 1) ? -pr.k[dir] : pr.k[dir]), g, y);
       st *= n;
     }
-    const double dg = (pr.V[d] + dl) + dh;
     y = fma_t((T)(pr.s1 * dg), own[col], y);         // (the value itself, as in the tile kernel)
     if (pr.Xp) y = fma_t((T)pr.s2, pr.Xp[d * pr.ldy + col], y);
     pr.Y[d * pr.ldy + col] = y;
@@ -842,8 +824,7 @@ static KronProb<T> prob_of(const KronArgs<T> &a) {
   p.ncols = a.ncols;
   p.s1 = a.s1;
   p.s2 = a.s2;
-  split_shift(a.shift, a.quantum, p.sh, p.sl);
-  p.sl += a.shift2;
+  p.shift = a.shift;
   p.bf16 = a.bf16;
   for (int d = 0; d < 3; ++d) p.k[d] = a.k[d];
   return p;
@@ -959,7 +940,7 @@ int kron_launch_kpts(const KronArgs<double> &a, int nk, const double *kv, const 
       b.k[d] = host_kv[3 * g + d];
       k2 += b.k[d] * b.k[d];
     }
-    b.shift2 = -0.5 * k2;
+    b.shift = -0.5 * k2;
     if (int r = kron_launch_complex(b, s)) return r;
   }
   return 0;

@@ -3,7 +3,6 @@
 
 #include <algorithm>
 #include <cmath>
-#include <cstring>
 
 namespace chfsi {
 
@@ -219,23 +218,6 @@ std::string build_mesh(double L, int n_el, int p, MeshTables &m, bool periodic) 
       if (a != b) m.ce[i] = (double)(w[a] * D[i] * s);
       m.km[i] = (double)(2 / h * K1[i] / mass1(a));
     }
-  // (hi: 50 bits for the largest, so that three of them and a shift of up to four
-  // times that size add up in 53)
-  std::vector<ext> dg(p);
-  ext dmax = 0;
-  for (int a = 0; a < p; ++a) {
-    dg[a] = K1[(size_t)a * q + a] / (h * mass1(a)) * (a == 0 ? 2 : 1);
-    dmax = std::max(dmax, dg[a]);
-  }
-  int ex = 0;
-  std::frexp(dmax, &ex);
-  const ext quantum = std::ldexp((ext)1, ex - 50);
-  m.dia.resize(2 * p);
-  for (int a = 0; a < p; ++a) {
-    m.dia[a] = (double)(std::rint(dg[a] / quantum) * quantum);
-    m.dia[p + a] = (double)(dg[a] - m.dia[a]);
-  }
-  m.dia_quantum = (double)quantum;
 
   // 1D operator A = 1/2 M1^-1/2 K1D M1^-1/2 on the n interior nodes, for the
   // spectral upper bound; n <= 2000 keeps the host Jacobi affordable only for
@@ -326,37 +308,15 @@ double bloch_1d_max(const MeshTables &m, double k) {
 // error of xi0 multiplies the whole block by T_m's derivative there (20 steps at p = 5
 // and 7: errors of 4.5e-15 and 1.1e-14 of the block with factors computed in double,
 // 1.7e-15 and 3.7e-15 so).
-namespace {
-typedef __float128 quad;
-template <typename Q> quad get(const Q &q) {
-  quad v;
-  std::memcpy(&v, q.bytes, sizeof v);
-  return v;
-}
-template <typename Q> void put(Q &q, quad v) { std::memcpy(q.bytes, &v, sizeof v); }
-}  // namespace
-
-ChebRecursion::ChebRecursion(double a, double b, double a0) {
-  const quad c = ((quad)a + b) / 2, ie = 2 / ((quad)b - a);
-  put(xi0_, (a0 - c) * ie);
-  put(ie_, ie);
-  c_ = (double)c;
-}
-
 ChebRecursion::Step ChebRecursion::next() {
-  const quad xi0 = get(xi0_), ie = get(ie_);
-  quad rho = 0, s2 = 0;
-  if (first_) {
-    rho = 1 / xi0;
-  } else {
-    const quad prev = get(rho_);
-    rho = 1 / (2 * xi0 - prev);
-    s2 = rho * prev;
-  }
-  const double s1 = (double)(rho * ie) * (first_ ? 1 : 2);
-  first_ = false;
-  put(rho_, rho);
-  return {s1, -(double)s2, c_};
+  typedef __float128 quad;
+  const quad c = ((quad)a_ + b_) / 2, e = ((quad)b_ - a_) / 2, xi0 = (a0_ - c) / e;
+  const quad rho = (quad)rho_[0] + rho_[1];
+  const bool first = rho_[0] == 0;
+  const quad rn = 1 / (first ? xi0 : 2 * xi0 - rho);
+  rho_[0] = (double)rn;
+  rho_[1] = (double)(rn - rho_[0]);
+  return {(double)((first ? 1 : 2) * rn / e), first ? 0.0 : (double)(-rn * rho), (double)c};
 }
 
 void dof_coords(const MeshTables &m, double *xyz) {

@@ -26,10 +26,6 @@ struct MeshTables {
   // of d/dx (zero diagonal: the ends' entries cancel between elements); with
   // A = sum of ae over the elements, Htilde = A (+) A (+) A + diag(V)
   std::vector<double> ae, ce;
-  // A's diagonal at node a < p of an element, exactly hi[a] + lo[a]: hi multiples of
-  // a power of two, lo the rest
-  std::vector<double> dia;
-  double dia_quantum = 0;
   std::vector<double> km;          // (2 / h) K1[a][b] / mass of node a (an end's: both elements'), (p+1)^2
   double lam1d_max = 0;            // largest eigenvalue of the assembled 1D operator
   // periodic cell [0, L)^3: node index I = (ex p + a) mod (n_el p), n = n_el p,
@@ -52,19 +48,15 @@ double bloch_1d_max(const MeshTables &m, double k);
 // Z_{k+1} = s1 (H - shift) Z_k + s2 Z_{k-1}, correctly rounded.
 class ChebRecursion {
  public:
-  ChebRecursion(double a, double b, double a0);
+  ChebRecursion(double a, double b, double a0) : a_(a), b_(b), a0_(a0) {}
   struct Step {
     double s1, s2, shift;
   };
   Step next();
 
  private:
-  struct alignas(16) Quad {        // a 113-bit number, which only host code can name
-    unsigned char bytes[16];
-  };
-  Quad xi0_, ie_, rho_;            // xi0, 1 / e, rho_k
-  double c_;
-  bool first_ = true;
+  double a_, b_, a0_;
+  double rho_[2] = {0, 0};         // rho_k, its rounding and the rest (no step yet: 0)
 };
 
 // x,y,z of every interior node in dof order.
