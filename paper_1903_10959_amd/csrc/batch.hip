@@ -279,13 +279,24 @@ int run_sweep(chfsi_batch *B, Sweep<T> &S, const std::vector<int> &ids, float *m
     const int nb = p.o.nblock;
     const double a = p.evals[nb - 1], a0 = p.evals[0], b = p.c->ub;
     if (!(a0 < a && a < b)) return bfail(B, CHFSI_ERR_STATE, "batch: internal: unchecked filter bounds");
-    ChebRecursion rec(a, b, a0);
+    // normalised recursion: rho_1 = 1/xi0, rho_{k+1} = 1/(2 xi0 - rho_k)
+    const double cc = 0.5 * (a + b), e = 0.5 * (b - a), xi0 = (a0 - cc) / e;
+    double rho = 1.0 / xi0;
     double *tc = S.hcoef.data() + (size_t)3 * m_deg * m;
     for (int k = 0; k < m_deg; ++k) {
-      const ChebRecursion::Step f = rec.next();
-      tc[3 * k] = f.s1;
-      tc[3 * k + 1] = f.s2;
-      tc[3 * k + 2] = f.shift;
+      double s1, s2;
+      if (k == 0) {
+        s1 = rho / e;
+        s2 = 0.0;
+      } else {
+        const double rn = 1.0 / (2.0 * xi0 - rho);
+        s1 = 2.0 * rn / e;
+        s2 = -rn * rho;
+        rho = rn;
+      }
+      tc[3 * k] = s1;
+      tc[3 * k + 1] = s2;
+      tc[3 * k + 2] = cc;
     }
   }
   BCHK(B, hipMemcpyAsync(S.coef.p, S.hcoef.data(), S.hcoef.size() * sizeof(double), hipMemcpyHostToDevice, B->stream));

@@ -140,6 +140,7 @@ int check_complex(chfsi_ctx *c, const void *X, int64_t ld, int ncols) {
 }
 
 int filter_c(chfsi_ctx *c, double *X, int64_t ld, int ncols, int degree, double a, double b, double a0, int bw) {
+  const double cc = 0.5 * (a + b), e = 0.5 * (b - a), xi0 = (a0 - cc) / e;
   const int64_t nd = c->mesh.n_dof;
   bw = std::min(bw > 0 ? bw : 64, ncols);
   HIPCHK(c, c->fbuf[0].ensure(work_bytes(c, 2 * bw, sizeof(double))));
@@ -148,11 +149,20 @@ int filter_c(chfsi_ctx *c, double *X, int64_t ld, int ncols, int degree, double 
     // two buffers alternate, Z_{k+1} overwriting Z_{k-1} (complex w columns are 2 w doubles)
     const ColBuf<double> buf[2] = {row_major<double>(c, X + 2 * j0, 2 * ld),
                                    work_block<double>(c, c->fbuf[0].as<double>(), 2 * w, 2 * ld)};
-    ChebRecursion rec(a, b, a0);
+    double rho = 1.0 / xi0;
     for (int k = 0; k < degree; ++k) {
-      const ChebRecursion::Step f = rec.next();
+      double s1, s2;
+      if (k == 0) {
+        s1 = rho / e;
+        s2 = 0.0;
+      } else {
+        const double rn = 1.0 / (2.0 * xi0 - rho);
+        s1 = 2.0 * rn / e;
+        s2 = -rn * rho;
+        rho = rn;
+      }
       const ColBuf<double> &in = buf[k & 1], &out = buf[(k & 1) ^ 1];
-      if (int r = cheb_step_c(c, {in.p, in.ld, in.cg}, k > 0 ? out.p : nullptr, out, w, f.s1, f.s2, f.shift)) return r;
+      if (int r = cheb_step_c(c, {in.p, in.ld, in.cg}, k > 0 ? out.p : nullptr, out, w, s1, s2, cc)) return r;
     }
     if (degree & 1)
       copy_cols_launch<double, double>(buf[1], group_of(c, sizeof(double), 2 * w, 2 * ld), buf[0], INT32_MAX, nd, 2 * w,

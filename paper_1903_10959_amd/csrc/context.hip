@@ -525,12 +525,23 @@ extern "C" int chfsi_apply(chfsi_ctx *c, const double *X, double *Y, int64_t ld,
 template <typename T>
 static int filter_block(chfsi_ctx *c, const ColBuf<T> (&buf)[2], int ncols, int degree, double a, double b, double a0,
                         int bf = 0) {
-  ChebRecursion rec(a, b, a0);
+  // normalised recursion: rho_1 = 1/xi0, rho_{k+1} = 1/(2 xi0 - rho_k);
+  // Z_1 = (rho_1/e)(H - c) Z_0;  Z_{k+1} = (2 rho_{k+1}/e)(H - c) Z_k - rho_{k+1} rho_k Z_{k-1}
+  const double cc = 0.5 * (a + b), e = 0.5 * (b - a), xi0 = (a0 - cc) / e;
+  double rho = 1.0 / xi0;
   for (int k = 0; k < degree; ++k) {
-    const ChebRecursion::Step f = rec.next();
+    double s1, s2;
+    if (k == 0) {
+      s1 = rho / e;
+      s2 = 0.0;
+    } else {
+      double rn = 1.0 / (2.0 * xi0 - rho);
+      s1 = 2.0 * rn / e;
+      s2 = -rn * rho;
+      rho = rn;
+    }
     const ColBuf<T> &in = buf[k & 1], &out = buf[(k & 1) ^ 1];
-    if (int r = cheb_step_t<T>(c, {in.p, in.ld, in.cg}, k > 0 ? out.p : nullptr, out, ncols, f.s1, f.s2, f.shift, bf))
-      return r;
+    if (int r = cheb_step_t<T>(c, {in.p, in.ld, in.cg}, k > 0 ? out.p : nullptr, out, ncols, s1, s2, cc, bf)) return r;
   }
   return 0;
 }

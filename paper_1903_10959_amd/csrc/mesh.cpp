@@ -302,23 +302,6 @@ double bloch_1d_max(const MeshTables &m, double k) {
   return g;
 }
 
-// c = (a + b) / 2, e = (b - a) / 2, xi0 = (a0 - c) / e; rho_1 = 1 / xi0, rho_{k+1} =
-// 1 / (2 xi0 - rho_k); Z_1 = (rho_1 / e) (H - c) Z_0, Z_{k+1} = (2 rho_{k+1} / e)
-// (H - c) Z_k - rho_{k+1} rho_k Z_{k-1}.  In 113 bits, each factor rounded once: an
-// error of xi0 multiplies the whole block by T_m's derivative there (20 steps at p = 5
-// and 7: errors of 4.5e-15 and 1.1e-14 of the block with factors computed in double,
-// 1.7e-15 and 3.7e-15 so).
-ChebRecursion::Step ChebRecursion::next() {
-  typedef __float128 quad;
-  const quad c = ((quad)a_ + b_) / 2, e = ((quad)b_ - a_) / 2, xi0 = (a0_ - c) / e;
-  const quad rho = (quad)rho_[0] + rho_[1];
-  const bool first = rho_[0] == 0;
-  const quad rn = 1 / (first ? xi0 : 2 * xi0 - rho);
-  rho_[0] = (double)rn;
-  rho_[1] = (double)(rn - rho_[0]);
-  return {(double)((first ? 1 : 2) * rn / e), first ? 0.0 : (double)(-rn * rho), (double)c};
-}
-
 void dof_coords(const MeshTables &m, double *xyz) {
   std::vector<double> x1(m.n);
   const int I0 = m.periodic ? 0 : 1;   // periodic unknowns start at the node x = 0

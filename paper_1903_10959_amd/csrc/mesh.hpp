@@ -44,21 +44,6 @@ std::string build_mesh(double L, int n_el, int p, MeshTables &m, bool periodic =
 // plus max V bounds lambda_max(Htilde_k) (Weyl, Kronecker sum).
 double bloch_1d_max(const MeshTables &m, double k);
 
-// The factors of the filter's recursion scaled by T_m(xi0), step by step:
-// Z_{k+1} = s1 (H - shift) Z_k + s2 Z_{k-1}, correctly rounded.
-class ChebRecursion {
- public:
-  ChebRecursion(double a, double b, double a0) : a_(a), b_(b), a0_(a0) {}
-  struct Step {
-    double s1, s2, shift;
-  };
-  Step next();
-
- private:
-  double a_, b_, a0_;
-  double rho_[2] = {0, 0};         // rho_k, its rounding and the rest (no step yet: 0)
-};
-
 // x,y,z of every interior node in dof order.
 void dof_coords(const MeshTables &m, double *xyz);
 
