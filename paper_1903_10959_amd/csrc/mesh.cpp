@@ -8,62 +8,49 @@ namespace chfsi {
 
 namespace {
 
-// The 1D tables are computed in extended precision and rounded once: the step and
-// Poisson kernels repeat an entry's error at every node, where it adds up over a
-// filter or a solve (entries of D^T W D summed in double were off by up to 5e-15 of
-// themselves at p = 6 and 7, 4e-14 at p = 11).
-typedef long double ext;
-
 // Legendre values P_{k}(x) for k = 0..kmax by Bonnet's recurrence.
-void legendre_all(int kmax, ext x, std::vector<ext> &P) {
-  P.assign(kmax + 1, 0);
-  P[0] = 1;
+void legendre_all(int kmax, double x, std::vector<double> &P) {
+  P.assign(kmax + 1, 0.0);
+  P[0] = 1.0;
   if (kmax >= 1) P[1] = x;
-  for (int k = 1; k < kmax; ++k) P[k + 1] = ((2 * k + 1) * x * P[k] - k * P[k - 1]) / (k + 1);
+  for (int k = 1; k < kmax; ++k) P[k + 1] = ((2.0 * k + 1.0) * x * P[k] - k * P[k - 1]) / (k + 1.0);
 }
+
+}  // namespace
 
 // GLL nodes are the zeros of (1 - x^2) P_p'(x), which is proportional to
 // P_{p-1}(x) - P_{p+1}(x).  Newton's method on f = P_{p+1} - P_{p-1} uses
 // f' = (2p+1) P_p.  Weights: 2 / (p (p+1) P_p(x)^2).
-void gll_rule_ext(int p, std::vector<ext> &xi, std::vector<ext> &w) {
+void gll_rule(int p, std::vector<double> &xi, std::vector<double> &w) {
   const double pi = 3.14159265358979323846;
-  xi.assign(p + 1, 0);
-  w.assign(p + 1, 0);
-  std::vector<ext> P;
+  xi.assign(p + 1, 0.0);
+  w.assign(p + 1, 0.0);
+  std::vector<double> P;
   for (int k = 1; k < p; ++k) {
-    ext x = -std::cos(pi * k / p);
+    double x = -std::cos(pi * k / p);
     for (int it = 0; it < 100; ++it) {
       legendre_all(p + 1, x, P);
-      const ext dx = (P[p + 1] - P[p - 1]) / ((2 * p + 1) * P[p]);
+      double f = P[p + 1] - P[p - 1];
+      double df = (2.0 * p + 1.0) * P[p];
+      double dx = f / df;
       x -= dx;
-      if (std::fabs(dx) < 1e-20L) break;
+      if (std::fabs(dx) < 1e-17) break;
     }
     xi[k] = x;
   }
-  xi[0] = -1;
-  xi[p] = 1;
+  xi[0] = -1.0;
+  xi[p] = 1.0;
   // symmetrise (the rule is symmetric about 0; removes last-bit asymmetry)
   for (int k = 0; k <= p / 2; ++k) {
-    const ext s = (xi[p - k] - xi[k]) / 2;
+    double s = 0.5 * (xi[p - k] - xi[k]);
     xi[k] = -s;
     xi[p - k] = s;
   }
-  if (p % 2 == 0) xi[p / 2] = 0;
+  if (p % 2 == 0) xi[p / 2] = 0.0;
   for (int k = 0; k <= p; ++k) {
     legendre_all(p, xi[k], P);
-    w[k] = 2 / (p * (p + 1) * P[p] * P[p]);
+    w[k] = 2.0 / (p * (p + 1.0) * P[p] * P[p]);
   }
-}
-
-void round_to(std::vector<double> &out, const std::vector<ext> &in) { out.assign(in.begin(), in.end()); }
-
-}  // namespace
-
-void gll_rule(int p, std::vector<double> &xi, std::vector<double> &w) {
-  std::vector<ext> x, v;
-  gll_rule_ext(p, x, v);
-  round_to(xi, x);
-  round_to(w, v);
 }
 
 // (aligned: its loops ran 28 % slower, 59 against 46 ms for a Bloch vector at
@@ -120,38 +107,33 @@ std::string build_mesh(double L, int n_el, int p, MeshTables &m, bool periodic) 
   m.n_dof = (int64_t)m.n * m.n * m.n;
   m.n_cells = (int64_t)n_el * n_el * n_el;
   const int q = m.q;
-  std::vector<ext> xi, w;
-  gll_rule_ext(p, xi, w);
-  round_to(m.xi, xi);
-  round_to(m.w, w);
+  gll_rule(p, m.xi, m.w);
 
   // D[qq][a] = l_a'(xi_qq): P_p(xi_qq) / (P_p(xi_a) (xi_qq - xi_a)) off the
   // diagonal; -p(p+1)/4 and +p(p+1)/4 at the two ends; 0 elsewhere on the diagonal.
-  std::vector<ext> Pp(q), P;
+  std::vector<double> Pp(q), P;
   for (int k = 0; k < q; ++k) {
-    legendre_all(p, xi[k], P);
+    legendre_all(p, m.xi[k], P);
     Pp[k] = P[p];
   }
-  std::vector<ext> D((size_t)q * q);
+  m.D.assign((size_t)q * q, 0.0);
   for (int i = 0; i < q; ++i)
     for (int a = 0; a < q; ++a) {
-      ext v;
-      if (i != a) v = Pp[i] / (Pp[a] * (xi[i] - xi[a]));
-      else if (i == 0) v = -(ext)(p * (p + 1)) / 4;
-      else if (i == p) v = (ext)(p * (p + 1)) / 4;
-      else v = 0;
-      D[(size_t)i * q + a] = v;
+      double v;
+      if (i != a) v = Pp[i] / (Pp[a] * (m.xi[i] - m.xi[a]));
+      else if (i == 0) v = -p * (p + 1.0) / 4.0;
+      else if (i == p) v = p * (p + 1.0) / 4.0;
+      else v = 0.0;
+      m.D[(size_t)i * q + a] = v;
     }
-  round_to(m.D, D);
   // K1 = D^T W D
-  std::vector<ext> K1((size_t)q * q);
+  m.K1.assign((size_t)q * q, 0.0);
   for (int a = 0; a < q; ++a)
     for (int b = 0; b < q; ++b) {
-      ext s = 0;
-      for (int i = 0; i < q; ++i) s += w[i] * D[(size_t)i * q + a] * D[(size_t)i * q + b];
-      K1[(size_t)a * q + b] = s;
+      double s = 0;
+      for (int i = 0; i < q; ++i) s += m.w[i] * m.D[(size_t)i * q + a] * m.D[(size_t)i * q + b];
+      m.K1[(size_t)a * q + b] = s;
     }
-  round_to(m.K1, K1);
   // cell stiffness 1/2 (h/2) [K1 (x) W (x) W + W (x) K1 (x) W + W (x) W (x) K1],
   // local node l = a + q b + q^2 c.
   const int nl = m.n_loc;
@@ -204,19 +186,15 @@ std::string build_mesh(double L, int n_el, int p, MeshTables &m, bool periodic) 
 
   // 1D element matrices in the mass-scaled basis (an element end shares its
   // mass with the neighbour)
-  // and, for the Poisson operator, its row over the row's mass
   m.ae.assign((size_t)q * q, 0.0);
   m.ce.assign((size_t)q * q, 0.0);
-  m.km.assign((size_t)q * q, 0.0);
-  const ext h = m.h;
-  auto mass1 = [&](int a) { return h / 2 * w[a] * (a == 0 || a == p ? 2 : 1); };
   for (int a = 0; a < q; ++a)
     for (int b = 0; b < q; ++b) {
-      const size_t i = (size_t)a * q + b;
-      const ext s = 1 / std::sqrt(mass1(a) * mass1(b));
-      m.ae[i] = (double)(K1[i] / h * s);
-      if (a != b) m.ce[i] = (double)(w[a] * D[i] * s);
-      m.km[i] = (double)(2 / h * K1[i] / mass1(a));
+      const double ma = (m.h / 2.0) * m.w[a] * (a == 0 || a == p ? 2.0 : 1.0);
+      const double mb = (m.h / 2.0) * m.w[b] * (b == 0 || b == p ? 2.0 : 1.0);
+      const double s = 1.0 / std::sqrt(ma * mb);
+      m.ae[(size_t)a * q + b] = 0.5 * (2.0 / m.h) * m.K1[(size_t)a * q + b] * s;
+      if (a != b) m.ce[(size_t)a * q + b] = m.w[a] * m.D[(size_t)a * q + b] * s;
     }
 
   // 1D operator A = 1/2 M1^-1/2 K1D M1^-1/2 on the n interior nodes, for the

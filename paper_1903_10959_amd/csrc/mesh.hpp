@@ -26,7 +26,6 @@ struct MeshTables {
   // of d/dx (zero diagonal: the ends' entries cancel between elements); with
   // A = sum of ae over the elements, Htilde = A (+) A (+) A + diag(V)
   std::vector<double> ae, ce;
-  std::vector<double> km;          // (2 / h) K1[a][b] / mass of node a (an end's: both elements'), (p+1)^2
   double lam1d_max = 0;            // largest eigenvalue of the assembled 1D operator
   // periodic cell [0, L)^3: node index I = (ex p + a) mod (n_el p), n = n_el p,
   // no Dirichlet nodes
