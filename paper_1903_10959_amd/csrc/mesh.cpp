@@ -53,6 +53,57 @@ void gll_rule(int p, std::vector<double> &xi, std::vector<double> &w) {
   }
 }
 
+namespace {
+
+// MeshTables::m1 and km in extended precision, rounded once: the Poisson product repeats
+// an entry's error at every node, where the smooth solution collects it (entries of
+// D^T W D summed in double are off by up to 5e-15 of themselves at p = 6 and 7; a
+// solve to 1e-13 on 24^3 cells of degree 6 by 2.0e-12, so by 1.0e-12).  The step
+// kernels keep the K1 summed in double: from one that differs in the last digits,
+// Rayleigh-Ritz returns some vectors of a dense block with the other sign.
+void poisson_rows(int p, double h, std::vector<double> &m1, std::vector<double> &km) {
+  typedef long double ext;
+  const int q = p + 1;
+  const ext pi = 3.14159265358979323846L;
+  std::vector<ext> P(p + 2), x(q), w(q), Pp(q), D((size_t)q * q);
+  auto legendre = [&](ext t) {                      // P_0 .. P_{p+1}
+    P[0] = 1;
+    P[1] = t;
+    for (int k = 1; k <= p; ++k) P[k + 1] = ((2 * k + 1) * t * P[k] - k * P[k - 1]) / (k + 1);
+  };
+  for (int k = 0; k <= p; ++k) {
+    ext t = -std::cos(pi * k / p);
+    for (int it = 0; it < 100 && k > 0 && k < p; ++it) {   // as gll_rule
+      legendre(t);
+      const ext dt = (P[p + 1] - P[p - 1]) / ((2 * p + 1) * P[p]);
+      t -= dt;
+      if (std::fabs(dt) < 1e-20L) break;
+    }
+    x[k] = k == 0 ? -1 : k == p ? 1 : 2 * k == p ? 0 : t;
+  }
+  for (int k = 0; k <= p; ++k) {
+    legendre(x[k]);
+    Pp[k] = P[p];
+    w[k] = 2 / (p * (p + 1) * P[p] * P[p]);
+  }
+  for (int i = 0; i < q; ++i)
+    for (int a = 0; a < q; ++a)
+      D[(size_t)i * q + a] = i != a ? Pp[i] / (Pp[a] * (x[i] - x[a])) : (ext)(p * (p + 1)) / 4 * ((i == p) - (i == 0));
+  m1.resize(q);
+  km.resize((size_t)q * q);
+  for (int a = 0; a < q; ++a) {
+    const ext mass = (ext)h / 2 * w[a] * (a == 0 || a == p ? 2 : 1);
+    m1[a] = (double)mass;
+    for (int b = 0; b < q; ++b) {
+      ext s = 0;
+      for (int i = 0; i < q; ++i) s += w[i] * D[(size_t)i * q + a] * D[(size_t)i * q + b];
+      km[(size_t)a * q + b] = (double)(2 / (ext)h * s / mass);
+    }
+  }
+}
+
+}  // namespace
+
 // (aligned: its loops ran 28 % slower, 59 against 46 ms for a Bloch vector at
 // n = 72, where a change elsewhere in the library had moved them by 32 bytes)
 __attribute__((aligned(64))) void sym_eigvals(std::vector<double> a, int n, std::vector<double> &out) {
@@ -196,6 +247,8 @@ std::string build_mesh(double L, int n_el, int p, MeshTables &m, bool periodic) 
       m.ae[(size_t)a * q + b] = 0.5 * (2.0 / m.h) * m.K1[(size_t)a * q + b] * s;
       if (a != b) m.ce[(size_t)a * q + b] = m.w[a] * m.D[(size_t)a * q + b] * s;
     }
+
+  poisson_rows(p, m.h, m.m1, m.km);
 
   // 1D operator A = 1/2 M1^-1/2 K1D M1^-1/2 on the n interior nodes, for the
   // spectral upper bound; n <= 2000 keeps the host Jacobi affordable only for

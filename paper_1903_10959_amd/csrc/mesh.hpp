@@ -26,6 +26,8 @@ struct MeshTables {
   // of d/dx (zero diagonal: the ends' entries cancel between elements); with
   // A = sum of ae over the elements, Htilde = A (+) A (+) A + diag(V)
   std::vector<double> ae, ce;
+  // Poisson: 1D mass of node a (an end's: both elements'), and (2 / h) K1[a][b] over it, (p+1)^2
+  std::vector<double> m1, km;
   double lam1d_max = 0;            // largest eigenvalue of the assembled 1D operator
   // periodic cell [0, L)^3: node index I = (ex p + a) mod (n_el p), n = n_el p,
   // no Dirichlet nodes

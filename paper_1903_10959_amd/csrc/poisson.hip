@@ -74,8 +74,7 @@ __device__ __forceinline__ double block_sum(double v, double *sh) {
   return s;
 }
 
-// The symmetric, centrosymmetric table T(k, l) = (2 / h) K1(k, l) / m(k) of a
-// cell, m the assembled 1D mass (a vertex's on both ends): row k of A's 1D part
+// The centrosymmetric table T(k, l) = (2 / h) K1(k, l) / m(k) of a cell, m the assembled 1D mass (a vertex's on both ends): row k of A's 1D part
 // divided by the mass, so that a node's sum over the three directions is
 // multiplied by s m_I m_J m_K once.
 template <int P> struct CellTable {
@@ -551,25 +550,25 @@ __global__ __launch_bounds__(PR) void poisson_setup_reduce_kernel(const double *
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
-// 1D Laplacian stiffness (band, half-width p) and GLL mass on the interior
-// nodes, assembled from the reference matrices.
+// 1D Laplacian stiffness (band, half-width p, each row over its mass) and GLL mass
+// on the interior nodes.  A band entry of two nodes of one element is that
+// element's; an element end's diagonal is twice its half.
 static void poisson_tables(const MeshTables &M, std::vector<double> &kb, std::vector<double> &m1) {
-  const int p = M.p, q = M.q, n = M.n, n1 = M.n_el * p + 1, bw = 2 * p + 1;
-  std::vector<double> K((size_t)n1 * n1, 0.0), mm(n1, 0.0);
-  for (int e = 0; e < M.n_el; ++e)
-    for (int a = 0; a < q; ++a) {
-      mm[e * p + a] += (M.h / 2.0) * M.w[a];
-      for (int b = 0; b < q; ++b) K[(size_t)(e * p + a) * n1 + (e * p + b)] += (2.0 / M.h) * M.K1[(size_t)a * q + b];
-    }
-  kb.assign((size_t)n * bw, 0.0);                  // the band over the row's mass
+  const int p = M.p, q = M.q, n = M.n, bw = 2 * p + 1;
+  kb.assign((size_t)n * bw, 0.0);
   m1.resize(2 * (size_t)n);                        // the mass, then the band's diagonal over it
   for (int i = 0; i < n; ++i) {
-    m1[i] = mm[i + 1];
-    m1[n + i] = K[(size_t)(i + 1) * n1 + (i + 1)] / m1[i];
-    for (int d = -p; d <= p; ++d) {
-      const int j = i + d;
-      if (j >= 0 && j < n) kb[(size_t)i * bw + d + p] = K[(size_t)(i + 1) * n1 + (j + 1)] / m1[i];
+    const int e = (i + 1) / p, a = (i + 1) % p;    // node a of element e
+    m1[i] = M.m1[a];
+    auto put = [&](int row, int b, int node) {     // entry (row, b) of an element, b at grid node `node`
+      const int j = node - 1;
+      if (j >= 0 && j < n) kb[(size_t)i * bw + (j - i) + p] += M.km[(size_t)row * q + b];
+    };
+    for (int b = 0; b <= p; ++b) {
+      put(a, b, e * p + b);
+      if (a == 0) put(p, b, (e - 1) * p + b);
     }
+    m1[n + i] = kb[(size_t)i * bw + p];
   }
 }
 
@@ -596,7 +595,7 @@ static int poisson_ready(chfsi_ctx *c) {
   return 0;
 }
 
-static const double kInv4Pi = 0.25 / 3.14159265358979323846;
+static const double kInv4Pi = 0.079577471545947667884;   // 1 / (4 pi)
 
 // Work-groups of the stencil at zl cell layers each.  Two layers save the reads
 // of the one before (24^3 cells of degree 6: 19.6 against 21.1 us; 32^3 of degree
@@ -618,11 +617,7 @@ template <int P>
 static void poisson_stencil_go(const MeshTables &M, const double *x, double *y, const double *kbs, const double *m,
                                const double *scal, int it, double *part, hipStream_t s) {
   CellTable<P> T;
-  for (int i = 0; i < CellTable<P>::N; ++i) {
-    const int k = i / (P + 1), l = i % (P + 1);
-    const double mass = (M.h / 2.0) * (k == 0 || k == P ? M.w[0] + M.w[P] : M.w[k]);
-    T.t[i] = (2.0 / M.h) * M.K1[(size_t)k * (P + 1) + l] / mass;
-  }
+  for (int i = 0; i < CellTable<P>::N; ++i) T.t[i] = M.km[i];
   const dim3 g = apply_grid(M), b(PB);
   const int zl = stencil_zl(M.n, M.n_el, M.p);
   if (part)
