@@ -74,9 +74,10 @@ __device__ __forceinline__ double block_sum(double v, double *sh) {
   return s;
 }
 
-// The centrosymmetric table T(k, l) = (2 / h) K1(k, l) / m(k) of a cell, m the assembled 1D mass (a vertex's on both ends): row k of A's 1D part
-// divided by the mass, so that a node's sum over the three directions is
-// multiplied by s m_I m_J m_K once.
+// The centrosymmetric table T(k, l) = (2 / h) K1(k, l) / m(k) of a cell, m the
+// assembled 1D mass (a vertex's on both ends): row k of A's 1D part divided by
+// the mass, so that a node's sum over the three directions is multiplied by
+// s m_I m_J m_K once.
 template <int P> struct CellTable {
   static constexpr int N = ((P + 1) * (P + 1) + 1) / 2;
   double t[N];
