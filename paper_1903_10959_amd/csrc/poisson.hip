@@ -366,15 +366,17 @@ __global__ __launch_bounds__(PB) void poisson_update_kernel(double *__restrict__
   double zv[VU], qv[VU];
   auto load = [&](int64_t base) {
     const int left = nd - base < VBLOCK ? (int)(nd - base) : VBLOCK;
+    const double *zb = z + base, *qb = q + base;
 #pragma unroll
     for (int u = 0; u < VU; ++u) {
       const int e = (int)threadIdx.x + PB * u;
-      zv[u] = e < left ? z[base + e] : 0.0;
-      qv[u] = e < left ? q[base + e] : 0.0;
+      zv[u] = e < left ? zb[e] : 0.0;
+      qv[u] = e < left ? qb[e] : 0.0;
     }
   };
   int64_t base = (int64_t)blockIdx.x * VBLOCK;
   load(base);
+  NodePos at(base, (int)threadIdx.x, n);
   const int dJ = PB / n, dI = PB - dJ * n;
   const double pq = parts_sum(part_pq, npq, pp, sh);
   const double alpha = pq != 0 ? scal[S_RZ + (it & 1)] / pq : 0.0;
@@ -383,7 +385,6 @@ __global__ __launch_bounds__(PB) void poisson_update_kernel(double *__restrict__
   for (;;) {
     const int left = nd - base < VBLOCK ? (int)(nd - base) : VBLOCK;
     double *zb = z + base;
-    NodePos at(base, (int)threadIdx.x, n);
 #pragma unroll
     for (int u = 0; u < VU; ++u) {
       const int e = (int)threadIdx.x + PB * u;
@@ -404,6 +405,7 @@ __global__ __launch_bounds__(PB) void poisson_update_kernel(double *__restrict__
     base += (int64_t)gridDim.x * VBLOCK;
     if (base >= nd) break;
     load(base);
+    at = NodePos(base, (int)threadIdx.x, n);
   }
   const double a = block_sum(rz, sh);
   const double b = block_sum(rr, sh);
@@ -432,18 +434,20 @@ __global__ __launch_bounds__(PB) void poisson_dir_kernel(double *__restrict__ x,
   double pw[VU], zw[VU];
   auto load_and_add = [&](int64_t base) {            // p and z of a block; x += alpha p
     const int left = nd - base < VBLOCK ? (int)(nd - base) : VBLOCK;
+    double *xb = x + base, *pb = pv + base;
+    const double *zb = z + base;
     double xw[VU];
 #pragma unroll
     for (int u = 0; u < VU; ++u) {
       const int e = (int)threadIdx.x + PB * u;
-      pw[u] = e < left ? pv[base + e] : 0.0;
-      xw[u] = e < left ? x[base + e] : 0.0;
-      zw[u] = e < left ? z[base + e] : 0.0;
+      pw[u] = e < left ? pb[e] : 0.0;
+      xw[u] = e < left ? xb[e] : 0.0;
+      zw[u] = e < left ? zb[e] : 0.0;
     }
 #pragma unroll
     for (int u = 0; u < VU; ++u) {
       const int e = (int)threadIdx.x + PB * u;
-      if (e < left) x[base + e] = fma(alpha, pw[u], xw[u]);
+      if (e < left) xb[e] = fma(alpha, pw[u], xw[u]);
     }
   };
   int64_t base = (int64_t)blockIdx.x * VBLOCK;
@@ -461,10 +465,11 @@ __global__ __launch_bounds__(PB) void poisson_dir_kernel(double *__restrict__ x,
   for (;;) {
     if (!MORE || !last) {
       const int left = nd - base < VBLOCK ? (int)(nd - base) : VBLOCK;
+      double *pb = pv + base;
 #pragma unroll
       for (int u = 0; u < VU; ++u) {
         const int e = (int)threadIdx.x + PB * u;
-        if (e < left) pv[base + e] = fma(beta, pw[u], zw[u]);
+        if (e < left) pb[e] = fma(beta, pw[u], zw[u]);
       }
     }
     if (!MORE) break;
